@@ -31,7 +31,9 @@ hipError_t launch_coo_features(const StepArgs &a, const uint64_t *keys, const ui
 hipError_t launch_intensity(const StepArgs &a, uint32_t grid, int fp64, void *table, uint32_t table_rows,
                             hipStream_t st);
 uint32_t neighbourhood_lds_bytes(uint32_t ng, int any_volume);
-hipError_t launch_neighbourhood(const StepArgs &a, uint32_t grid, int fp64, uint32_t alpha, int any_volume,
-                                void *table, uint32_t table_rows, hipStream_t st);
+uint64_t neighbourhood_slot_bytes(uint32_t ng, int any_volume);
+uint32_t neighbourhood_tile_vox(uint64_t total_vox, uint32_t n_cu, uint32_t ng, int any_volume);
+hipError_t launch_neighbourhood(const StepArgs &a, uint32_t items, uint32_t n_cu, int fp64, uint32_t alpha,
+                                int any_volume, uint32_t *gtab, void *table, uint32_t table_rows, hipStream_t st);
 
 }  // namespace nyx

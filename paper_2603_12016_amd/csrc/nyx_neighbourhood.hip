@@ -19,20 +19,32 @@
 //     denominators vanish (a flat texture), and NaN when no voxel has a
 //     neighbour.
 //
-// One work-group per ROI.  The scan gathers each ROI voxel's neighbours
-// (label and level) and counts, with LDS atomics, S(i, k), n_i and the exact
-// integers A(i, W) = sum |i W - sum of the W neighbour levels| per level i
-// and neighbour count W, so s_i = sum_W A(i, W) / W needs no floating sum
-// during the scan.  The features then come from exact integer moments of S
-// (GLM, GLV, DCM, DCV, the non-uniformities, energy) and double sums (the
-// weighted emphases, entropy, and the NGTDM pair sums over the levels
-// present).
+// The queue of the batch kernel hands out tiles: a ROI above a share of the
+// voxels is cut into several (blocks of bbox rows), so a few large regions
+// fill the chip.  A tile is walked by row blocks: a lane owns a column and
+// slides a 3 x 3 (x 3 planes) window of levels down it, so each voxel costs
+// one (volume: three) loads and one lane exchange per side instead of a
+// gather of 8 (26) labels and values.  A voxel outside the ROI holds
+// kNbOut in the window: one sum over the neighbours then gives both their
+// count W and their level total.  LDS atomics count S(i, k), the voxels
+// without neighbours, and the exact integers A(i, W) = sum |i W - sum of
+// the W neighbour levels| per level i and neighbour count W, so
+// s_i = sum_W A(i, W) / W needs no floating sum during the scan.  The tables
+// of a ROI in one tile become its features at once; those of a split ROI are
+// added to its table in global memory, and k_nb_split finishes them.  The
+// features come from exact integer moments of S (GLM, GLV, DCM, DCV, the
+// non-uniformities, energy) and double sums (the weighted emphases, entropy,
+// and the NGTDM pair sums over the levels present).  Bound by instructions
+// (26 compares a voxel) and LDS atomics; 60 regions of 10^3-60^3 voxels in a
+// 128 x 256 x 256 volume at 32 levels took 8.85 ms a call with one work-group
+// per region and gathered neighbours (60 work-groups on 256 CUs), 0.94 ms so.
 #include <hip/hip_runtime.h>
 #include <math.h>
 
 #include "nyx_device.h"
 #include "nyx_features.h"
 #include "nyx_launch.h"
+#include "nyx_queue.h"
 
 namespace nyx {
 
@@ -40,6 +52,9 @@ namespace {
 
 constexpr int kNbBlock = 256;
 constexpr int kNbWaves = kNbBlock / kWave;
+constexpr int kNbRows = 8;                     // rows a lane's column walk covers per unit
+constexpr uint32_t kNbOut = 1u << 20;          // window value of a voxel outside the ROI (26 levels sum below it)
+constexpr uint32_t kNbMinTile = 2048u;         // voxels per tile of a split ROI, at least
 
 enum NbFeat : int {
     // NGLDM
@@ -53,194 +68,270 @@ enum NbFeat : int {
 };
 static_assert(NB_COUNT == kNumNeighbourFeat, "column count");
 
+// Static LDS: with the dynamic tables it stays below the CU's 160 KB, whose
+// last kilobyte the host leaves free.
 struct NbShared {
-    uint64_t red[kNbWaves];
+    uint64_t red[kNbWaves * 8];
+    uint32_t misc[128];      // queue state (nyx_queue.h)
     uint32_t n_occ;          // levels present in the NGTDM
+    uint32_t n_items;
+};
+static_assert(sizeof(NbShared) <= 1024, "static LDS");
+
+// Words of a ROI's integer tables: A (u64, ng * nn) | S (u32, ng * (nn + 1)) |
+// voxels without a neighbour (u32, ng).
+__host__ __device__ inline uint32_t nb_tab_words(uint32_t ng, uint32_t nn) { return ng * nn * 2u + ng * (nn + 1u) + ng; }
+
+// The tables in LDS.
+struct NbTab {
+    uint64_t *A;
+    uint32_t *Sd, *iso, *occ;
+    double *sl;
+    __device__ __forceinline__ NbTab(uint8_t *smem, uint32_t ng, uint32_t nn) {
+        A = reinterpret_cast<uint64_t *>(smem);                 // ng * nn
+        Sd = reinterpret_cast<uint32_t *>(A + ng * nn);         // ng * (nn + 1) dependence matrix
+        iso = Sd + ng * (nn + 1u);                              // ng: voxels without a neighbour, then with one
+        occ = iso + ng;                                         // ng: levels present (compacted)
+        // (8-byte aligned: the words before it number an even multiple of ng, plus ng (nn + 1))
+        uint32_t *e = occ + ng;
+        sl = reinterpret_cast<double *>(e + ((ng * (nn + 3u)) & 1u));   // ng: s_i
+    }
 };
 
-}  // namespace
-
-// LDS bytes of the per-ROI tables for ng levels and nn neighbours.
-__host__ __device__ inline uint32_t nb_lds_bytes(uint32_t ng, uint32_t nn) {
-    // A (u64, ng * nn) | S (u32, ng * (nn + 1)) | n (u32, ng) | occupied levels (u32, ng) | s (double, ng)
-    return ng * nn * 8u + ng * (nn + 1u) * 4u + ng * 4u + ng * 4u + ng * 8u + 16u;
+// Sums of N (at most 8) 8-byte values over the work-group, in every thread:
+// one pair of barriers for all of them.
+template <int N, class T>
+__device__ __forceinline__ void block_sums(T (&v)[N], uint64_t *red) {
+    static_assert(sizeof(T) == 8 && N <= 8, "eight 8-byte values");
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = wave_sum(v[k]);
+    __syncthreads();
+    if (lane() == 0)
+#pragma unroll
+        for (int k = 0; k < N; ++k) reinterpret_cast<T *>(red)[(threadIdx.x / kWave) * 8 + k] = v[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        T s = reinterpret_cast<const T *>(red)[k];
+#pragma unroll
+        for (int w = 1; w < kNbWaves; ++w) s += reinterpret_cast<const T *>(red)[w * 8 + k];
+        v[k] = s;
+    }
 }
 
-// One work-group per ROI: the kNumNeighbourFeat features of ROI blockIdx.x.
-// nn_max: neighbours per voxel the LDS tables are laid out for (8 or 26).
-template <class OutT>
-__global__ __launch_bounds__(kNbBlock) void k_neighbourhood(const ImgDesc *imgs, int n_images, const RoiDesc *rois,
-                                                            const uint32_t *n_rois_ptr, uint32_t roi_cap,
-                                                            uint32_t ng, uint32_t alpha, uint32_t nn_max,
-                                                            OutT *table, uint32_t table_rows, uint32_t *err) {
-    __shared__ NbShared S;
-    extern __shared__ __align__(16) uint8_t smem[];
-    const uint32_t r = blockIdx.x;
-    const uint32_t n_rois = min(*n_rois_ptr, roi_cap);
-    if (r >= n_rois) return;
-    if (r >= table_rows) {
-        if (threadIdx.x == 0) atomicOr(err, (uint32_t)E_TABLE_CAP);
-        return;
-    }
-    const RoiDesc rd = rois[r];
-    if (rd.image >= (uint32_t)n_images) return;
-    const ImgDesc im = imgs[rd.image];
-    if (rd.x0 < 0 || rd.y0 < 0 || rd.z0 < 0 || rd.x1 >= im.nx || rd.y1 >= im.ny || rd.z1 >= im.nz ||
-        rd.x0 > rd.x1 || rd.y0 > rd.y1 || rd.z0 > rd.z1)
-        return;
-    OutT *out = table + (uint64_t)r * kNumNeighbourFeat;
-    const bool vol = im.nz > 1;
-    const uint32_t nn = vol ? 26u : 8u, nk = nn + 1u;
-    if (nn > nn_max) {
-        if (threadIdx.x == 0) atomicOr(err, (uint32_t)E_LIST_CAP);
-        return;
-    }
-    uint64_t *A = reinterpret_cast<uint64_t *>(smem);              // ng * nn
-    uint32_t *Sd = reinterpret_cast<uint32_t *>(A + ng * nn);       // ng * nk dependence matrix
-    uint32_t *cnt = Sd + ng * nk;                                   // ng: voxels with a neighbour
-    uint32_t *occ = cnt + ng;                                       // ng: levels present (compacted)
-    double *sl = reinterpret_cast<double *>(occ + ng + ((ng & 1u) ? 1u : 0u));   // ng: s_i
-    for (uint32_t i = threadIdx.x; i < ng * nn; i += kNbBlock) A[i] = 0ull;
-    for (uint32_t i = threadIdx.x; i < ng * nk; i += kNbBlock) Sd[i] = 0u;
-    for (uint32_t i = threadIdx.x; i < ng; i += kNbBlock) cnt[i] = 0u;
-    if (threadIdx.x == 0) S.n_occ = 0u;
-    __syncthreads();
+__device__ __forceinline__ uint32_t nb_prev(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x138, 0xF, 0xF, true);   // wave_shr1; lane 0 reads 0
+}
+__device__ __forceinline__ uint32_t nb_next(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x130, 0xF, 0xF, true);   // wave_shl1; lane 63 reads 0
+}
 
-    const uint32_t W = (uint32_t)(rd.x1 - rd.x0 + 1), H = (uint32_t)(rd.y1 - rd.y0 + 1),
+// Counts the voxels of bbox rows [ra, rb) (rows of all planes, flattened) and
+// bbox columns [ca, cb) into the LDS tables.  A unit is a strip of columns x
+// kNbRows rows of one plane; a wavefront takes 1, 2 or 4 units at a time on
+// groups of 64, 32 or 16 lanes (whichever needs the fewest strip steps for
+// the width; the first and last lane of a group only supply neighbours).
+// Every lane makes every exchange: loads are predicated, not branched.
+template <bool VOL>
+__device__ void nb_scan(const RoiDesc &rd, const ImgDesc &im, uint32_t ra, uint32_t rb, uint32_t ca, uint32_t cb,
+                        uint32_t ng, uint32_t alpha, const NbTab &t) {
+    constexpr uint32_t nn = VOL ? 26u : 8u, nk = nn + 1u;
+    constexpr int P = VOL ? 3 : 1;
+    const uint32_t Wb = (uint32_t)(rd.x1 - rd.x0 + 1), H = (uint32_t)(rd.y1 - rd.y0 + 1),
                    Dz = (uint32_t)(rd.z1 - rd.z0 + 1);
     const uint32_t nx = (uint32_t)im.nx, plane = (uint32_t)im.ny * nx;
-    const uint32_t label = rd.label, vmin = rd.vmin, D = rd.vmax - rd.vmin;
-    const float rcpD = D ? 1.0f / (float)D : 0.0f;
-    const int zlo = vol ? -1 : 0, zhi = vol ? 1 : 0;
-    for (BoxWalk<kNbBlock> b(W, H, Dz); b.ok(); b.next()) {
-        const int32_t X = rd.x0 + (int32_t)b.x, Y = rd.y0 + (int32_t)b.y, Z = rd.z0 + (int32_t)b.z;
-        const uint32_t v = (uint32_t)Z * plane + (uint32_t)Y * nx + (uint32_t)X;
-        if (ldg(im.L, v) != label) continue;
-        const uint32_t bv = fbn_level(ldg(im.I, v), vmin, D, rcpD, ng);
-        uint32_t wn = 0, tot = 0, dep = 1;
-        for (int dz = zlo; dz <= zhi; ++dz) {
-            const int32_t wz = Z + dz;
-            if (wz < 0 || wz >= im.nz) continue;
-            for (int dy = -1; dy <= 1; ++dy) {
-                const int32_t wy = Y + dy;
-                if (wy < 0 || wy >= im.ny) continue;
+    const uint32_t v00 = (uint32_t)rd.z0 * plane + (uint32_t)rd.y0 * nx + (uint32_t)rd.x0;
+    const uint32_t label = rd.label, vmin = rd.vmin;
+    const double rcp = fbn_rcp_up(rd.vmax > vmin ? rd.vmax - vmin : 1u);
+    const uint32_t W = cb - ca;
+    uint32_t lg = 0, best = ((W + 61u) / 62u) << 2;
+    for (uint32_t q = 1; q <= 2u; ++q) {
+        const uint32_t wo = (64u >> q) - 2u, steps = ((W + wo - 1u) / wo) << (2u - q);
+        if (steps < best) { best = steps; lg = q; }
+    }
+    const uint32_t Wl = 64u >> lg, Wo = Wl - 2u, S = 1u << lg;
+    const uint32_t ln = (uint32_t)lane(), sub = ln >> (6u - lg), col = ln & (Wl - 1u);
+    const uint32_t nstrip = (W + Wo - 1u) / Wo, nch = (H + (uint32_t)kNbRows - 1u) / (uint32_t)kNbRows;
+    const uint32_t z_lo = ra / H, z_n = (rb - 1u) / H - z_lo + 1u;
+    const uint32_t units = nstrip * nch * z_n;
+    const uint32_t w = threadIdx.x / kWave;
+    for (uint32_t u0 = w * S; u0 < units; u0 += (uint32_t)kNbWaves * S) {
+        const uint32_t u = u0 + sub;
+        uint32_t strip = 0u, z = z_lo;
+        int32_t y0 = 0, lo = 0, hi = 0;   // owned rows [lo, hi) of the unit's rows [y0, y0 + kNbRows)
+        if (u < units) {
+            const uint32_t q = u / nstrip, zq = q / nch;
+            strip = u - q * nstrip;
+            z = z_lo + zq;
+            y0 = (int32_t)((q - zq * nch) * (uint32_t)kNbRows);
+            lo = max(y0, (int32_t)ra - (int32_t)(z * H));
+            hi = min(min(y0 + kNbRows, (int32_t)H), (int32_t)rb - (int32_t)(z * H));
+        }
+        if (__ballot(lo < hi) == 0ull) continue;
+        const int32_t x = (int32_t)(ca + Wo * strip + col) - 1;     // bbox column of the lane
+        const bool xin = lo < hi && x >= 0 && x < (int32_t)Wb;
+        const bool owner = col >= 1u && col <= Wo && x < (int32_t)cb;
+        uint32_t lab[P][kNbRows + 2], val[P][kNbRows + 2];
 #pragma unroll
-                for (int dx = -1; dx <= 1; ++dx) {
-                    const int32_t wx = X + dx;
-                    if ((dz | dy | dx) == 0 || wx < 0 || wx >= im.nx) continue;
-                    const uint32_t w = (uint32_t)wz * plane + (uint32_t)wy * nx + (uint32_t)wx;
-                    if (ldg(im.L, w) != label) continue;
-                    const uint32_t bw = fbn_level(ldg(im.I, w), vmin, D, rcpD, ng);
-                    ++wn;
-                    tot += bw;
-                    dep += (bw > bv ? bw - bv : bv - bw) <= alpha;
+        for (int p = 0; p < P; ++p) {
+            const int32_t zz = VOL ? (int32_t)z + p - 1 : (int32_t)z;
+            const bool pin = xin && zz >= 0 && zz < (int32_t)Dz;
+#pragma unroll
+            for (int j = 0; j < kNbRows + 2; ++j) {
+                const int32_t y = y0 + j - 1;
+                lab[p][j] = 0u;
+                val[p][j] = 0u;
+                if (pin && y >= lo - 1 && y <= hi && y >= 0 && y < (int32_t)H) {
+                    const uint32_t v = v00 + (uint32_t)zz * plane + (uint32_t)y * nx + (uint32_t)x;
+                    lab[p][j] = ldg(im.L, v);
+                    val[p][j] = ldg(im.I, v);
                 }
             }
         }
-        atomicAdd(&Sd[(bv - 1u) * nk + dep - 1u], 1u);
-        if (wn) {
-            atomicAdd(&cnt[bv - 1u], 1u);
-            const uint32_t iw = bv * wn;
-            atomicAdd(reinterpret_cast<unsigned long long *>(&A[(bv - 1u) * nn + wn - 1u]),
-                      (unsigned long long)(iw > tot ? iw - tot : tot - iw));
+        // window rows j - 1, j, j + 1 at index (row mod 3): left, own, right
+        uint32_t win[P][3][3], sum[P][3];
+#pragma unroll
+        for (int j = 0; j < kNbRows + 2; ++j) {
+            const int at = j % 3;
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                const uint32_t lv = fbn_level_rd(val[p][j], vmin, rcp, ng);
+                const uint32_t c = lab[p][j] == label ? lv : kNbOut;   // (label 0 is never a ROI's)
+                win[p][at][1] = c;
+                win[p][at][0] = nb_prev(c);
+                win[p][at][2] = nb_next(c);
+                sum[p][at] = c + win[p][at][0] + win[p][at][2];
+            }
+            if (j < 2) continue;
+            const int mid = (j - 1) % 3;
+            const uint32_t bv = win[VOL ? 1 : 0][mid][1];
+            uint32_t tot = 0u, dep = 0u;
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+#pragma unroll
+                for (int r = 0; r < 3; ++r) {
+                    tot += sum[p][r];
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        const uint32_t o = win[p][r][k];
+                        // (the voxel itself counts: k = 1 + its dependent neighbours)
+                        dep += (o > bv ? o - bv : bv - o) <= alpha ? 1u : 0u;
+                    }
+                }
+            const int32_t y = y0 + j - 2;
+            if (owner && bv < kNbOut && y >= lo && y < hi) {
+                tot -= bv;
+                const uint32_t wn = nn - (tot >> 20);
+                tot &= kNbOut - 1u;
+                atomicAdd(&t.Sd[(bv - 1u) * nk + dep - 1u], 1u);
+                if (wn) {
+                    const uint32_t iw = bv * wn;
+                    atomicAdd(reinterpret_cast<unsigned long long *>(&t.A[(bv - 1u) * nn + wn - 1u]),
+                              (unsigned long long)(iw > tot ? iw - tot : tot - iw));
+                } else {
+                    atomicAdd(&t.iso[bv - 1u], 1u);
+                }
+            }
         }
     }
-    __syncthreads();
+}
 
+// The 37 features of a ROI from its integer tables in LDS, by the whole
+// work-group (thread 0 writes the row).
+template <class OutT>
+__device__ void nb_features(const NbTab &t, NbShared &S, uint32_t ng, uint32_t nn, OutT *out) {
+    const uint32_t nk = nn + 1u;
+    if (threadIdx.x == 0) S.n_occ = 0u;
+    __syncthreads();
     // ---- dependence matrix: exact integer moments and double emphases
-    uint64_t Ns = 0, e2 = 0, si = 0, si2 = 0, sk = 0, sk2 = 0, sik2 = 0, rows2 = 0;
-    double ent = 0.0, hdl = 0.0, lde = 0.0, ldh = 0.0, ldl = 0.0, lgl = 0.0;
+    uint64_t m[8] = {};   // Ns, energy, si, si2, sk, sk2, sik2, rows2
+    uint64_t c2[1] = {0};
+    double e[6] = {};     // entropy, hdl, lde, ldh, ldl, lgl
     for (uint32_t c = threadIdx.x; c < ng * nk; c += kNbBlock) {
-        const uint32_t q = Sd[c];
+        const uint32_t q = t.Sd[c];
         if (!q) continue;
         const uint32_t i0 = c / nk, k = c - i0 * nk + 1u, i = i0 + 1u;
         const uint64_t ii = (uint64_t)i * i, kk = (uint64_t)k * k;
-        Ns += q;
-        e2 += (uint64_t)q * q;
-        si += (uint64_t)i * q;
-        si2 += ii * q;
-        sk += (uint64_t)k * q;
-        sk2 += kk * q;
-        sik2 += ii * kk * q;
+        m[0] += q;
+        m[1] += (uint64_t)q * q;
+        m[2] += (uint64_t)i * q;
+        m[3] += ii * q;
+        m[4] += (uint64_t)k * q;
+        m[5] += kk * q;
+        m[6] += ii * kk * q;
         const double qd = (double)q, id = (double)ii, kd = (double)kk;
-        ent += qd * log2(qd);
-        hdl += qd * kd / id;
-        lde += qd / kd;
-        ldh += qd * id / kd;
-        ldl += qd / (id * kd);
-        lgl += qd / id;
+        e[0] += qd * log2(qd);
+        e[1] += qd * kd / id;
+        e[2] += qd / kd;
+        e[3] += qd * id / kd;
+        e[4] += qd / (id * kd);
+        e[5] += qd / id;
     }
+    // rows of S, and with them the voxels with a neighbour, s_i and the list
+    // of levels present (one thread per level owns its entries)
     for (uint32_t i = threadIdx.x; i < ng; i += kNbBlock) {
         uint64_t row = 0;
-        for (uint32_t k = 0; k < nk; ++k) row += Sd[i * nk + k];
-        rows2 += row * row;
-    }
-    uint64_t cols2 = 0;
-    for (uint32_t k = threadIdx.x; k < nk; k += kNbBlock) {
-        uint64_t col = 0;
-        for (uint32_t i = 0; i < ng; ++i) col += Sd[i * nk + k];
-        cols2 += col * col;
-    }
-    Ns = block_sum<kNbWaves>(Ns, S.red);
-    e2 = block_sum<kNbWaves>(e2, S.red);
-    si = block_sum<kNbWaves>(si, S.red);
-    si2 = block_sum<kNbWaves>(si2, S.red);
-    sk = block_sum<kNbWaves>(sk, S.red);
-    sk2 = block_sum<kNbWaves>(sk2, S.red);
-    sik2 = block_sum<kNbWaves>(sik2, S.red);
-    rows2 = block_sum<kNbWaves>(rows2, S.red);
-    cols2 = block_sum<kNbWaves>(cols2, S.red);
-    ent = block_sum<kNbWaves>(ent, S.red);
-    hdl = block_sum<kNbWaves>(hdl, S.red);
-    lde = block_sum<kNbWaves>(lde, S.red);
-    ldh = block_sum<kNbWaves>(ldh, S.red);
-    ldl = block_sum<kNbWaves>(ldl, S.red);
-    lgl = block_sum<kNbWaves>(lgl, S.red);
-
-    // ---- NGTDM: s_i and the list of levels present
-    for (uint32_t i = threadIdx.x; i < ng; i += kNbBlock) {
+        for (uint32_t k = 0; k < nk; ++k) row += t.Sd[i * nk + k];
+        m[7] += row * row;
+        const uint32_t with = (uint32_t)row - t.iso[i];
+        t.iso[i] = with;
         double s = 0.0;
         for (uint32_t w = 0; w < nn; ++w) {
-            const uint64_t a = A[i * nn + w];
+            const uint64_t a = t.A[i * nn + w];
             if (a) s += (double)a / (double)(w + 1u);
         }
-        sl[i] = s;
-        if (cnt[i]) occ[atomicAdd(&S.n_occ, 1u)] = i;
+        t.sl[i] = s;
+        if (with) t.occ[atomicAdd(&S.n_occ, 1u)] = i;
     }
-    __syncthreads();
-    const uint32_t ngp = S.n_occ;
-    uint64_t nvp = 0;
-    double ps = 0.0, ssum = 0.0;
-    for (uint32_t q = threadIdx.x; q < ngp; q += kNbBlock) {
-        const uint32_t i = occ[q];
-        nvp += cnt[i];
-        ssum += sl[i];
+    // columns of S: eight threads per column
+    {
+        const uint32_t k = threadIdx.x >> 3;
+        uint64_t part = 0;
+        if (k < nk)
+            for (uint32_t i = threadIdx.x & 7u; i < ng; i += 8u) part += t.Sd[i * nk + k];
+        part += __shfl_xor(part, 1);
+        part += __shfl_xor(part, 2);
+        part += __shfl_xor(part, 4);
+        if (k < nk && (threadIdx.x & 7u) == 0u) c2[0] = part * part;
     }
-    nvp = block_sum<kNbWaves>(nvp, S.red);
-    ssum = block_sum<kNbWaves>(ssum, S.red);
-    const double nvpd = (double)nvp, inv_nvp = nvp ? 1.0 / nvpd : 0.0;
-    for (uint32_t q = threadIdx.x; q < ngp; q += kNbBlock) {
-        const uint32_t i = occ[q];
-        ps += (double)cnt[i] * inv_nvp * sl[i];
-    }
-    ps = block_sum<kNbWaves>(ps, S.red);
-    // pair sums over the levels present (both orders, as the definitions run)
-    double con = 0.0, bden = 0.0, cpx = 0.0, str = 0.0;
-    for (uint32_t q = threadIdx.x; q < ngp * ngp; q += kNbBlock) {
-        const uint32_t a = q / ngp, c = q - a * ngp;
-        const uint32_t i = occ[a], j = occ[c];
-        const double pi = (double)cnt[i] * inv_nvp, pj = (double)cnt[j] * inv_nvp;
-        const double li = (double)(i + 1u), lj = (double)(j + 1u), d = li - lj;
-        con += pi * pj * d * d;
-        bden += fabs(li * pi - lj * pj);
-        cpx += fabs(d) * (pi * sl[i] + pj * sl[j]) / (pi + pj);
-        str += (pi + pj) * d * d;
-    }
-    con = block_sum<kNbWaves>(con, S.red);
-    bden = block_sum<kNbWaves>(bden, S.red);
-    cpx = block_sum<kNbWaves>(cpx, S.red);
-    str = block_sum<kNbWaves>(str, S.red);
+    block_sums(m, S.red);
+    block_sums(e, S.red);
+    block_sums(c2, S.red);   // (its barriers also publish iso, sl and occ)
+    const uint64_t Ns = m[0], e2 = m[1], si = m[2], si2 = m[3], sk = m[4], sk2 = m[5], sik2 = m[6], rows2 = m[7];
+    const uint64_t cols2 = c2[0];
+    const double ent = e[0], hdl = e[1], lde = e[2], ldh = e[3], ldl = e[4], lgl = e[5];
 
+    // ---- NGTDM over the levels present
+    const uint32_t ngp = S.n_occ;
+    uint64_t v1[1] = {0};
+    for (uint32_t q = threadIdx.x; q < ngp; q += kNbBlock) v1[0] += t.iso[t.occ[q]];
+    block_sums(v1, S.red);
+    const uint64_t nvp = v1[0];
+    const double inv_nvp = nvp ? 1.0 / (double)nvp : 0.0;
+    double g[6] = {};   // sum p s, sum s, then the pair sums: contrast, busyness denominator, complexity, strength
+    for (uint32_t q = threadIdx.x; q < ngp; q += kNbBlock) {
+        const uint32_t i = t.occ[q];
+        g[0] += (double)t.iso[i] * inv_nvp * t.sl[i];
+        g[1] += t.sl[i];
+    }
+    // pair sums: every term is symmetric and vanishes for i = j, so each
+    // unordered pair is visited once (a wavefront per first level) and
+    // counted twice
+    for (uint32_t a = threadIdx.x / kWave; a < ngp; a += (uint32_t)kNbWaves) {
+        const uint32_t i = t.occ[a];
+        const double pi = (double)t.iso[i] * inv_nvp, li = (double)(i + 1u), si_ = t.sl[i];
+        for (uint32_t c = a + 1u + (uint32_t)lane(); c < ngp; c += (uint32_t)kWave) {
+            const uint32_t j = t.occ[c];
+            const double pj = (double)t.iso[j] * inv_nvp, lj = (double)(j + 1u), d = li - lj;
+            g[2] += pi * pj * d * d;
+            g[3] += fabs(li * pi - lj * pj);
+            g[4] += fabs(d) * (pi * si_ + pj * t.sl[j]) / (pi + pj);
+            g[5] += (pi + pj) * d * d;
+        }
+    }
+    block_sums(g, S.red);
+    const double ps = g[0], ssum = g[1], con = 2.0 * g[2], bden = 2.0 * g[3], cpx = 2.0 * g[4], str = 2.0 * g[5];
+    __syncthreads();   // every thread is done with the tables
     if (threadIdx.x != 0) return;
     double f[NB_COUNT];
     const double nsd = (double)Ns, inv = 1.0 / nsd, ns2 = nsd * nsd;
@@ -288,27 +379,164 @@ __global__ __launch_bounds__(kNbBlock) void k_neighbourhood(const ImgDesc *imgs,
     for (int k = 0; k < NB_COUNT; ++k) out[k] = (OutT)f[k];
 }
 
+}  // namespace
+
+// LDS bytes of the per-ROI tables for ng levels and nn neighbours.
+__host__ __device__ inline uint32_t nb_lds_bytes(uint32_t ng, uint32_t nn) {
+    // the integer tables | occupied levels (u32, ng) | s (double, ng), 8-byte aligned
+    return nb_tab_words(ng, nn) * 4u + ng * 4u + ng * 8u + 16u;
+}
+
+// Persistent: the tiles of the queue, one work-group each.  nn_max:
+// neighbours per voxel the LDS tables are laid out for (8 or 26); gtab:
+// tables of split ROIs, one per split slot, zero on entry.
+template <class OutT>
+__global__ __launch_bounds__(kNbBlock) void k_neighbourhood(StepArgs a, uint32_t alpha, uint32_t nn_max,
+                                                            uint32_t *gtab, OutT *table, uint32_t table_rows) {
+    __shared__ NbShared S;
+    extern __shared__ __align__(16) uint8_t smem[];
+    const uint32_t ng = (uint32_t)a.ng;
+    uint32_t *const words = reinterpret_cast<uint32_t *>(smem);
+    ticket_load(S.misc, a.counters + C_CLASS, a.bucket_cap, threadIdx.x);
+    __syncthreads();
+    if (threadIdx.x == 0) ticket_prefix(S.misc);
+    __syncthreads();
+    for (;;) {
+        if (threadIdx.x == 0) {
+            const uint32_t lanes = min(kTicketLanes, gridDim.x), tl = blockIdx.x % lanes;
+            S.n_items = ticket_claim(S.misc, &a.counters[C_TICKETS + tl * kTicketStride], tl, lanes, a.buckets,
+                                     a.bucket_cap);
+        }
+        __syncthreads();
+        const uint32_t n_items = S.n_items;
+        if (n_items == 0u) break;
+        for (uint32_t q = 0; q < n_items; ++q) {
+            const uint32_t r = S.misc[2u * q], tile = S.misc[2u * q + 1u];
+            if (r >= min(a.counters[C_NROIS], a.roi_cap)) continue;
+            if (r >= table_rows) {
+                if (threadIdx.x == 0) atomicOr(&a.counters[C_ERR], (uint32_t)E_TABLE_CAP);
+                continue;
+            }
+            const RoiDesc rd = a.rois[r];
+            if (rd.image >= (uint32_t)a.n_images || tile >= rd.n_tiles) continue;
+            const ImgDesc im = a.imgs[rd.image];
+            if (rd.x0 < 0 || rd.y0 < 0 || rd.z0 < 0 || rd.x1 >= im.nx || rd.y1 >= im.ny || rd.z1 >= im.nz ||
+                rd.x0 > rd.x1 || rd.y0 > rd.y1 || rd.z0 > rd.z1 || rd.tcols == 0u)
+                continue;
+            const bool vol = im.nz > 1;
+            const uint32_t nn = vol ? 26u : 8u, nw = nb_tab_words(ng, nn);
+            if (nn > nn_max) {
+                if (threadIdx.x == 0) atomicOr(&a.counters[C_ERR], (uint32_t)E_LIST_CAP);
+                continue;
+            }
+            for (uint32_t i = threadIdx.x; i < nw; i += kNbBlock) words[i] = 0u;
+            __syncthreads();
+            const NbTab t(smem, ng, nn);
+            uint32_t ra, rb, ca, cb;
+            tile_bounds(rd.rows, (uint32_t)(rd.x1 - rd.x0 + 1), rd.n_tiles, rd.tcols, tile, &ra, &rb, &ca, &cb);
+            if (ra < rb && ca < cb) {
+                if (vol) nb_scan<true>(rd, im, ra, rb, ca, cb, ng, alpha, t);
+                else nb_scan<false>(rd, im, ra, rb, ca, cb, ng, alpha, t);
+            }
+            __syncthreads();
+            if (rd.gslot == kNone) {
+                nb_features(t, S, ng, nn, table + (uint64_t)r * kNumNeighbourFeat);
+            } else if (rd.gslot < a.g_cap) {
+                uint32_t *G = gtab + (uint64_t)rd.gslot * nb_tab_words(ng, nn_max);
+                const uint32_t n64 = ng * nn;   // leading 64-bit entries
+                for (uint32_t i = threadIdx.x; i < n64; i += kNbBlock)
+                    if (t.A[i])
+                        atomicAdd(reinterpret_cast<unsigned long long *>(G) + i, (unsigned long long)t.A[i]);
+                for (uint32_t i = 2u * n64 + threadIdx.x; i < nw; i += kNbBlock)
+                    if (words[i]) atomicAdd(&G[i], words[i]);
+            }
+            __syncthreads();   // the tables are cleared for the next tile
+        }
+        __syncthreads();       // every thread has read the ticket's entries
+    }
+}
+
+// Split ROIs: the features from the tables their tiles were added to.
+template <class OutT>
+__global__ __launch_bounds__(kNbBlock) void k_nb_split(StepArgs a, uint32_t nn_max, const uint32_t *gtab, OutT *table,
+                                                       uint32_t table_rows) {
+    __shared__ NbShared S;
+    extern __shared__ __align__(16) uint8_t smem[];
+    const uint32_t ng = (uint32_t)a.ng, used = min(a.counters[C_NSPLIT], a.g_cap);
+    uint32_t *const words = reinterpret_cast<uint32_t *>(smem);
+    for (uint32_t slot = blockIdx.x; slot < used; slot += gridDim.x) {
+        const uint32_t r = a.split_roi[slot];
+        if (r >= a.roi_cap || r >= table_rows || a.rois[r].image >= (uint32_t)a.n_images) continue;
+        const uint32_t nn = a.imgs[a.rois[r].image].nz > 1 ? 26u : 8u, nw = nb_tab_words(ng, nn);
+        if (nn > nn_max) continue;
+        const uint32_t *G = gtab + (uint64_t)slot * nb_tab_words(ng, nn_max);
+        for (uint32_t i = threadIdx.x; i < nw; i += kNbBlock) words[i] = G[i];
+        __syncthreads();
+        const NbTab t(smem, ng, nn);
+        nb_features(t, S, ng, nn, table + (uint64_t)r * kNumNeighbourFeat);
+        __syncthreads();
+    }
+}
+
+// Zeroes the tables of the split slots in use.
+__global__ __launch_bounds__(256) void k_nb_zero(StepArgs a, uint32_t *gtab, uint32_t slot_words) {
+    const uint64_t n = (uint64_t)min(a.counters[C_NSPLIT], a.g_cap) * slot_words;
+    for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < n; i += gridDim.x * 256ull) gtab[i] = 0u;
+}
+
 uint32_t neighbourhood_lds_bytes(uint32_t ng, int any_volume) { return nb_lds_bytes(ng, any_volume ? 26u : 8u); }
 
-hipError_t launch_neighbourhood(const StepArgs &a, uint32_t grid, int fp64, uint32_t alpha, int any_volume,
-                                void *table, uint32_t table_rows, hipStream_t st) {
-    if (grid == 0) return hipSuccess;
-    const uint32_t nn = any_volume ? 26u : 8u;
+uint64_t neighbourhood_slot_bytes(uint32_t ng, int any_volume) {
+    return (uint64_t)nb_tab_words(ng, any_volume ? 26u : 8u) * 4u;
+}
+
+// Voxels per tile of a split ROI: a sixteenth of a CU's share of the image
+// voxels (an even spread whatever part of them is ROI), but no fewer than a
+// merge of the tables is worth (a quarter of their bytes).
+uint32_t neighbourhood_tile_vox(uint64_t total_vox, uint32_t n_cu, uint32_t ng, int any_volume) {
+    const uint64_t share = total_vox / (16ull * (n_cu ? n_cu : 1u));
+    const uint64_t least = neighbourhood_slot_bytes(ng, any_volume) / 4u;
+    uint64_t t = share > kNbMinTile ? share : kNbMinTile;
+    if (t < least) t = least;
+    return (uint32_t)(t < (1u << 20) ? t : (1u << 20));
+}
+
+template <class OutT>
+static hipError_t launch_nb(const StepArgs &a, uint32_t items, uint32_t n_cu, uint32_t alpha, uint32_t nn,
+                            uint32_t *gtab, OutT *table, uint32_t table_rows, hipStream_t st) {
     const uint32_t lds = nb_lds_bytes((uint32_t)a.ng, nn);
-    const void *f = fp64 ? reinterpret_cast<const void *>(&k_neighbourhood<double>)
-                         : reinterpret_cast<const void *>(&k_neighbourhood<float>);
     // the dynamic tables plus the static NbShared stay within the CU's 160 KB
-    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    if (fp64)
-        hipLaunchKernelGGL(k_neighbourhood<double>, dim3(grid), dim3(kNbBlock), lds, st, a.imgs, a.n_images, a.rois,
-                           a.counters + C_NROIS, a.roi_cap, (uint32_t)a.ng, alpha, nn,
-                           reinterpret_cast<double *>(table), table_rows, a.counters + C_ERR);
-    else
-        hipLaunchKernelGGL(k_neighbourhood<float>, dim3(grid), dim3(kNbBlock), lds, st, a.imgs, a.n_images, a.rois,
-                           a.counters + C_NROIS, a.roi_cap, (uint32_t)a.ng, alpha, nn,
-                           reinterpret_cast<float *>(table), table_rows, a.counters + C_ERR);
+    for (const void *f : {reinterpret_cast<const void *>(&k_neighbourhood<OutT>),
+                          reinterpret_cast<const void *>(&k_nb_split<OutT>)}) {
+        hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    // levels differ by less than ng: a larger alpha means the same, and stays below kNbOut
+    const uint32_t al = alpha < (uint32_t)a.ng ? alpha : (uint32_t)a.ng;
+    const uint32_t per_cu = 160u * 1024u / (lds + 1024u);
+    uint32_t grid = n_cu * (per_cu < 1u ? 1u : (per_cu > 4u ? 4u : per_cu));
+    if (grid > items) grid = items;
+    if (a.g_cap) {
+        const uint32_t slot_words = nb_tab_words((uint32_t)a.ng, nn);
+        hipLaunchKernelGGL(k_nb_zero, dim3(2u * n_cu), dim3(256), 0, st, a, gtab, slot_words);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_neighbourhood<OutT>, dim3(grid), dim3(kNbBlock), lds, st, a, al, nn, gtab, table, table_rows);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !a.g_cap) return e;
+    const uint32_t fin = a.g_cap < 4u * n_cu ? a.g_cap : 4u * n_cu;
+    hipLaunchKernelGGL(k_nb_split<OutT>, dim3(fin), dim3(kNbBlock), lds, st, a, nn, gtab, table, table_rows);
     return hipGetLastError();
+}
+
+hipError_t launch_neighbourhood(const StepArgs &a, uint32_t items, uint32_t n_cu, int fp64, uint32_t alpha,
+                                int any_volume, uint32_t *gtab, void *table, uint32_t table_rows, hipStream_t st) {
+    if (items == 0u) return hipSuccess;
+    const uint32_t nn = any_volume ? 26u : 8u;
+    if (fp64)
+        return launch_nb(a, items, n_cu, alpha, nn, gtab, reinterpret_cast<double *>(table), table_rows, st);
+    return launch_nb(a, items, n_cu, alpha, nn, gtab, reinterpret_cast<float *>(table), table_rows, st);
 }
 
 }  // namespace nyx

@@ -818,6 +818,28 @@ nyx_status setup_step(nyx_ctx *ctx, Work &w, const Config &cfg, const nyx_offset
     return NYX_OK;
 }
 
+// Work queue of a family whose items are tiles of about tile_vox voxels: the
+// compaction cuts every ROI above tile_vox into fewer than 2 ceil(n / tile_vox)
+// tiles (tiles_for), so the image's voxels bound the entries and the split
+// ROIs, which get one slot of slot_bytes each.
+nyx_status setup_tiles(nyx_ctx *ctx, Work &w, StepArgs &a, uint32_t tile_vox, uint64_t slot_bytes, DevBuf &slots,
+                       uint32_t *items) {
+    const uint64_t n_split = std::min<uint64_t>(w.n_rois, w.total_vox / tile_vox);
+    const uint64_t n_items = w.n_rois + 4u * (w.total_vox / tile_vox);
+    if (n_items >= (1ull << 31)) return fail(ctx, NYX_ERR_UNSUPPORTED, "too many work items");
+    HIPC(ctx, w.buckets.alloc((size_t)kClasses * std::max<uint64_t>(n_items, 1u) * sizeof(uint2)));
+    HIPC(ctx, w.split_roi.alloc(std::max<uint64_t>(n_split, 1u) * 4u));
+    HIPC(ctx, slots.alloc(n_split * slot_bytes));
+    a.buckets = w.buckets.as<uint2>();
+    a.bucket_cap = (uint32_t)std::max<uint64_t>(n_items, 1u);
+    a.split_roi = w.split_roi.as<uint32_t>();
+    a.g_cap = (uint32_t)n_split;
+    a.split_vox = a.tile_vox = tile_vox;
+    a.enqueue = 1;
+    *items = (uint32_t)n_items;
+    return NYX_OK;
+}
+
 nyx_status set_outputs(nyx_ctx *ctx, StepArgs &a, nyx_roi_table *rois, void *table, uint32_t table_rows) {
     a.table = table;
     a.table_rows = table_rows;
@@ -1160,12 +1182,17 @@ nyx_status nyx_neighbourhood_features(nyx_ctx *ctx, const nyx_image *imgs, int32
     if (n > 0 && !table) return fail(ctx, NYX_ERR_INVALID, "table is NULL");
     StepArgs a = w.args;
     a.ng = n_bins;
-    a.enqueue = 0;
+    DevBuf gtab;
+    uint32_t items = 0;
+    if ((s = setup_tiles(ctx, w, a, neighbourhood_tile_vox(w.total_vox, (uint32_t)ctx->n_cu, (uint32_t)n_bins, any_volume),
+                         neighbourhood_slot_bytes((uint32_t)n_bins, any_volume), gtab, &items)) != NYX_OK)
+        return s;
     set_outputs(ctx, a, rois, nullptr, 0);
     HIPC(ctx, launch_reset(a, w.n_counters, st));
     HIPC(ctx, launch_scan(a, st));
-    HIPC(ctx, launch_compact(a, 0u, 0u, st));
-    HIPC(ctx, launch_neighbourhood(a, (uint32_t)n, prec == NYX_FP64, (uint32_t)alpha, any_volume, table,
+    HIPC(ctx, launch_compact(a, 0u, 0xFFFFFFFFu, st));
+    HIPC(ctx, launch_neighbourhood(a, items, (uint32_t)ctx->n_cu, prec == NYX_FP64, (uint32_t)alpha, any_volume,
+                                   gtab.as<uint32_t>(), table,
                                    (uint32_t)std::min<int64_t>(table_capacity_rows, 0xFFFFFFFFll), st));
     return check_counters(ctx, w, st);
 }

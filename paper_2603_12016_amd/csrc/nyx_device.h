@@ -242,22 +242,45 @@ __device__ __forceinline__ T block_sum(T v, uint64_t *red) {
     return block_reduce<NW>(v, red, OpAdd());
 }
 
+// Sums of N (at most 8) 8-byte values over a work-group of NW wavefronts, in
+// every thread: one pair of barriers for all of them.  red is LDS room for
+// 8 NW 8-byte values.
+template <int NW, int N, class T>
+__device__ __forceinline__ void block_sums(T (&v)[N], uint64_t *red) {
+    static_assert(sizeof(T) == 8 && N <= 8, "eight 8-byte values");
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = wave_sum(v[k]);
+    __syncthreads();
+    if (lane() == 0)
+#pragma unroll
+        for (int k = 0; k < N; ++k) reinterpret_cast<T *>(red)[(threadIdx.x / kWave) * 8 + k] = v[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        T s = reinterpret_cast<const T *>(red)[k];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) s += reinterpret_cast<const T *>(red)[w * 8 + k];
+        v[k] = s;
+    }
+}
+
 // ------------------------------------------------------------ box walk
-// Walks the voxels of a bounding box of W x H x D voxels, BS at a time:
-// thread t visits f = t + k BS in x-fastest order, tracked as (column, row,
-// plane) offsets without divisions after the first step.
+// Walks the voxels of bbox rows [ra, rb) (rows of H per plane, all planes
+// flattened) over W columns, BS at a time: thread t visits f = t + k BS in
+// x-fastest order, tracked as (column, row, plane) without divisions after
+// the first step.
 template <uint32_t BS>
-struct BoxWalk {
+struct RowWalk {
     uint32_t W, H, n, f, x, y, z, dq, dx;
-    __device__ __forceinline__ BoxWalk(uint32_t W_, uint32_t H_, uint32_t D_) : W(W_), H(H_) {
-        n = W * H * D_;
+    __device__ __forceinline__ RowWalk(uint32_t W_, uint32_t H_, uint32_t ra, uint32_t rb) : W(W_), H(H_) {
+        n = W * (rb - ra);
         f = threadIdx.x;
         dq = BS / W;
         dx = BS - dq * W;
-        x = f % W;
-        const uint32_t r = f / W;
-        y = r % H;
+        const uint32_t q = f / W, r = ra + q;
+        x = f - q * W;
         z = r / H;
+        y = r - z * H;
     }
     __device__ __forceinline__ bool ok() const { return f < n; }
     __device__ __forceinline__ void next() {

@@ -28,8 +28,11 @@ hipError_t launch_coo_emit(const StepArgs &a, uint32_t n_slots, const uint64_t *
                            uint64_t *vals, hipStream_t st);
 hipError_t launch_coo_features(const StepArgs &a, const uint64_t *keys, const uint64_t *vals, uint64_t nnz,
                                uint32_t n_rois, uint64_t *seg, DirSums *sums, DirSumsY *sums_y, hipStream_t st);
-hipError_t launch_intensity(const StepArgs &a, uint32_t grid, int fp64, void *table, uint32_t table_rows,
-                            hipStream_t st);
+uint64_t intensity_slot_bytes();
+uint64_t intensity_sums_bytes(uint32_t n_rois);
+uint32_t intensity_tile_vox(uint64_t total_vox);
+hipError_t launch_intensity(const StepArgs &a, uint32_t items, uint32_t n_cu, int fp64, void *slots, void *sums,
+                            void *table, uint32_t table_rows, hipStream_t st);
 uint32_t neighbourhood_lds_bytes(uint32_t ng, int any_volume);
 uint64_t neighbourhood_slot_bytes(uint32_t ng, int any_volume);
 uint32_t neighbourhood_tile_vox(uint64_t total_vox, uint32_t n_cu, uint32_t ng, int any_volume);

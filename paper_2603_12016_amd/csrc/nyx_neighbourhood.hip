@@ -98,27 +98,6 @@ struct NbTab {
     }
 };
 
-// Sums of N (at most 8) 8-byte values over the work-group, in every thread:
-// one pair of barriers for all of them.
-template <int N, class T>
-__device__ __forceinline__ void block_sums(T (&v)[N], uint64_t *red) {
-    static_assert(sizeof(T) == 8 && N <= 8, "eight 8-byte values");
-#pragma unroll
-    for (int k = 0; k < N; ++k) v[k] = wave_sum(v[k]);
-    __syncthreads();
-    if (lane() == 0)
-#pragma unroll
-        for (int k = 0; k < N; ++k) reinterpret_cast<T *>(red)[(threadIdx.x / kWave) * 8 + k] = v[k];
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        T s = reinterpret_cast<const T *>(red)[k];
-#pragma unroll
-        for (int w = 1; w < kNbWaves; ++w) s += reinterpret_cast<const T *>(red)[w * 8 + k];
-        v[k] = s;
-    }
-}
-
 __device__ __forceinline__ uint32_t nb_prev(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x138, 0xF, 0xF, true);   // wave_shr1; lane 0 reads 0
 }
@@ -294,9 +273,9 @@ __device__ void nb_features(const NbTab &t, NbShared &S, uint32_t ng, uint32_t n
         part += __shfl_xor(part, 4);
         if (k < nk && (threadIdx.x & 7u) == 0u) c2[0] = part * part;
     }
-    block_sums(m, S.red);
-    block_sums(e, S.red);
-    block_sums(c2, S.red);   // (its barriers also publish iso, sl and occ)
+    block_sums<kNbWaves>(m, S.red);
+    block_sums<kNbWaves>(e, S.red);
+    block_sums<kNbWaves>(c2, S.red);   // (its barriers also publish iso, sl and occ)
     const uint64_t Ns = m[0], e2 = m[1], si = m[2], si2 = m[3], sk = m[4], sk2 = m[5], sik2 = m[6], rows2 = m[7];
     const uint64_t cols2 = c2[0];
     const double ent = e[0], hdl = e[1], lde = e[2], ldh = e[3], ldl = e[4], lgl = e[5];
@@ -305,7 +284,7 @@ __device__ void nb_features(const NbTab &t, NbShared &S, uint32_t ng, uint32_t n
     const uint32_t ngp = S.n_occ;
     uint64_t v1[1] = {0};
     for (uint32_t q = threadIdx.x; q < ngp; q += kNbBlock) v1[0] += t.iso[t.occ[q]];
-    block_sums(v1, S.red);
+    block_sums<kNbWaves>(v1, S.red);
     const uint64_t nvp = v1[0];
     const double inv_nvp = nvp ? 1.0 / (double)nvp : 0.0;
     double g[6] = {};   // sum p s, sum s, then the pair sums: contrast, busyness denominator, complexity, strength
@@ -329,7 +308,7 @@ __device__ void nb_features(const NbTab &t, NbShared &S, uint32_t ng, uint32_t n
             g[5] += (pi + pj) * d * d;
         }
     }
-    block_sums(g, S.red);
+    block_sums<kNbWaves>(g, S.red);
     const double ps = g[0], ssum = g[1], con = 2.0 * g[2], bden = 2.0 * g[3], cpx = 2.0 * g[4], str = 2.0 * g[5];
     __syncthreads();   // every thread is done with the tables
     if (threadIdx.x != 0) return;

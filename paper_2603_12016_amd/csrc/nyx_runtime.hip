@@ -1139,12 +1139,16 @@ nyx_status nyx_intensity_features(nyx_ctx *ctx, const nyx_image *imgs, int32_t n
     if (n > 0 && !table) return fail(ctx, NYX_ERR_INVALID, "table is NULL");
     StepArgs a = w.args;
     a.ng = n_bins;
-    a.enqueue = 0;
+    DevBuf slots, sums;
+    uint32_t items = 0;
+    if ((s = setup_tiles(ctx, w, a, intensity_tile_vox(w.total_vox), intensity_slot_bytes(), slots, &items)) != NYX_OK)
+        return s;
+    HIPC(ctx, sums.alloc(intensity_sums_bytes(w.n_rois)));
     set_outputs(ctx, a, rois, nullptr, 0);
     HIPC(ctx, launch_reset(a, w.n_counters, st));
     HIPC(ctx, launch_scan(a, st));
-    HIPC(ctx, launch_compact(a, 0u, 0u, st));
-    HIPC(ctx, launch_intensity(a, (uint32_t)n, prec == NYX_FP64, table,
+    HIPC(ctx, launch_compact(a, 0u, 0xFFFFFFFFu, st));
+    HIPC(ctx, launch_intensity(a, items, (uint32_t)ctx->n_cu, prec == NYX_FP64, slots.p, sums.p, table,
                                (uint32_t)std::min<int64_t>(table_capacity_rows, 0xFFFFFFFFll), st));
     return check_counters(ctx, w, st);
 }

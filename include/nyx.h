@@ -155,7 +155,10 @@ typedef struct nyx_extract_opts {
 } nyx_extract_opts;
 
 /* Context on one device (hipSetDevice ordinal).  NYX_ERR_DEVICE if absent.
- * Owns the library's scratch for the one-shot calls; not thread-safe. */
+ * Owns the library's scratch for the one-shot calls (one device block, made
+ * by the first of them, of what the largest call asked for between 32 and
+ * 512 MiB; larger calls allocate and free the rest) and some pinned host
+ * memory, all given back by nyx_destroy; not thread-safe. */
 nyx_status nyx_create(nyx_ctx **out, int device_ordinal);
 void nyx_destroy(nyx_ctx *ctx);
 const char *nyx_last_error(const nyx_ctx *ctx);

@@ -42,7 +42,7 @@
 // and leaves the values of a box of at most kFoArea voxels in LDS, with one
 // membership bit each, for the other passes (a larger box is read again).
 // The tiles of a split ROI add their integer sums and the full histogram of
-// their values (65536 counters a slot) to global memory; k_intensity_split
+// their values (one counter per value of the range) to global memory; k_intensity_split
 // takes every statistic from the histogram.  Either way the sums of a ROI end
 // in a FoSums record, and k_intensity_rows forms the 37 values with one lane
 // per ROI.  The family is bound by VALU issue, and for the usual small region
@@ -74,7 +74,6 @@ constexpr uint32_t kFoSmall = 2048u;       // box voxels of a ROI that one wavef
 constexpr int kFoSplitBlock = 512;        // split ROIs: threads of the histogram kernel
 constexpr int kFoSplitWaves = kFoSplitBlock / kWave;
 constexpr uint32_t kFoMinTile = 4096u;     // voxels per tile of a split ROI, at least
-constexpr uint32_t kFoMaxSlots = 256u;     // split ROIs at most (their histograms: 256 KB each)
 
 enum FoFeat : int {
     FO_MEAN, FO_MIN, FO_MAX, FO_RANGE, FO_INTEGRATED, FO_ENERGY, FO_RMS, FO_VARIANCE, FO_STDDEV,
@@ -125,13 +124,17 @@ struct FoSums {
     double pct[kFoPct];
 };
 
-// A split ROI's slot: the integer sums of its tiles and the histogram of
-// (I - vmin).
+// A split ROI's slot: the integer sums of its tiles.  The histograms of
+// (I - vmin), vmax - vmin + 1 counters each, follow the slots in blocks of 64
+// counters, a ROI's at block RoiDesc::aux.
 struct FoSlot {
     uint64_t s[8];                         // n | ne << 32, S1, S2, CX, CY, CZ, ES1, ES2
     uint32_t emin, emax, pad[14];
-    uint32_t hist[65536];
 };
+static_assert(sizeof(FoSlot) % 128 == 0, "the histograms start on a cache line");
+__device__ __forceinline__ uint32_t *fo_hist(FoSlot *slots, uint32_t n_slots, const RoiDesc &rd) {
+    return reinterpret_cast<uint32_t *>(slots + n_slots) + 64ull * rd.aux;
+}
 // (n and ne share a word: a ROI has fewer than 2^31 voxels)
 
 struct Centred {
@@ -549,7 +552,7 @@ __device__ void fo_small(const RoiDesc &rd, const ImgDesc &im, uint32_t ng, FoWa
 // One tile of a split ROI: integer sums and value histogram into its slot.
 // Counts of the first kFoWindow values above the ROI's minimum go through an
 // LDS window, wider ones straight to global memory.
-__device__ void fo_tile(const RoiDesc &rd, const ImgDesc &im, uint32_t tile, FoShared &S, FoSlot *G) {
+__device__ void fo_tile(const RoiDesc &rd, const ImgDesc &im, uint32_t tile, FoShared &S, FoSlot *G, uint32_t *hist) {
     uint32_t ra, rb, ca, cb;
     tile_bounds(rd.rows, (uint32_t)(rd.x1 - rd.x0 + 1), rd.n_tiles, rd.tcols, tile, &ra, &rb, &ca, &cb);
     if (ra >= rb || ca >= cb) return;
@@ -559,7 +562,7 @@ __device__ void fo_tile(const RoiDesc &rd, const ImgDesc &im, uint32_t tile, FoS
     FoPart s = fo_scan<kFoBlock>(rd, im, ra, rb, ca, cb, [&](uint32_t, uint32_t x, bool in) {
         if (!in) return;
         const uint32_t q = x - rd.vmin;
-        atomicAdd(q < kFoWindow ? &S.window[q] : &G->hist[q], 1u);
+        atomicAdd(q < kFoWindow ? &S.window[q] : &hist[q], 1u);
     });
     s.emin = wave_min(s.emin);
     s.emax = wave_max(s.emax);
@@ -573,7 +576,7 @@ __device__ void fo_tile(const RoiDesc &rd, const ImgDesc &im, uint32_t tile, FoS
         atomicAdd(reinterpret_cast<unsigned long long *>(&G->s[threadIdx.x]), (unsigned long long)mine);
     }
     for (uint32_t i = threadIdx.x; i < bins; i += kFoBlock)
-        if (S.window[i]) atomicAdd(&G->hist[i], S.window[i]);
+        if (S.window[i]) atomicAdd(&hist[i], S.window[i]);
 }
 
 }  // namespace
@@ -631,7 +634,7 @@ __global__ __launch_bounds__(kFoBlock, 5) void k_intensity(StepArgs a, FoSlot *s
                 continue;
             }
             if (rd.gslot == kNone) fo_roi(rd, im, (uint32_t)a.ng, S, reinterpret_cast<uint32_t *>(smem), sums + r);
-            else if (rd.gslot < a.g_cap) fo_tile(rd, im, tile, S, slots + rd.gslot);
+            else if (rd.gslot < a.g_cap) fo_tile(rd, im, tile, S, slots + rd.gslot, fo_hist(slots, a.g_cap, rd));
             __syncthreads();   // the scratch is reused by the next item
         }
         __syncthreads();       // every thread has read the ticket's entries
@@ -640,7 +643,7 @@ __global__ __launch_bounds__(kFoBlock, 5) void k_intensity(StepArgs a, FoSlot *s
 
 // Split ROIs: every statistic from the slot's sums and histogram.  Dynamic
 // LDS: the level histogram (ng u32).
-__global__ __launch_bounds__(kFoSplitBlock) void k_intensity_split(StepArgs a, const FoSlot *slots, FoSums *sums) {
+__global__ __launch_bounds__(kFoSplitBlock) void k_intensity_split(StepArgs a, FoSlot *slots, FoSums *sums) {
     extern __shared__ __align__(16) uint8_t smem[];
     uint32_t *lev = reinterpret_cast<uint32_t *>(smem);
     __shared__ uint64_t red[kFoSplitWaves * 8], best;
@@ -651,6 +654,7 @@ __global__ __launch_bounds__(kFoSplitBlock) void k_intensity_split(StepArgs a, c
         const uint32_t r = a.split_roi[slot];
         if (r >= a.roi_cap) continue;
         const FoSlot &G = slots[slot];
+        const uint32_t *hist = fo_hist(slots, a.g_cap, a.rois[r]);
         const uint32_t vmin = a.rois[r].vmin, vmax = a.rois[r].vmax, D = vmax - vmin;
         const double rcp = fbn_rcp_up(D ? D : 1u);
         const uint64_t n = G.s[0] & 0xFFFFFFFFu, S1 = G.s[1];
@@ -666,7 +670,7 @@ __global__ __launch_bounds__(kFoSplitBlock) void k_intensity_split(StepArgs a, c
         const uint32_t per = (D + (uint32_t)kFoSplitBlock) / (uint32_t)kFoSplitBlock;
         const uint32_t b0 = min(threadIdx.x * per, D + 1u), b1 = min(b0 + per, D + 1u);
         uint32_t own = 0;
-        for (uint32_t b = b0; b < b1; ++b) own += G.hist[b];
+        for (uint32_t b = b0; b < b1; ++b) own += hist[b];
         const uint32_t incl = wave_incl_scan(own);
         if (lane() == kWave - 1) wave_tot[threadIdx.x / kWave] = incl;
         __syncthreads();
@@ -677,12 +681,12 @@ __global__ __launch_bounds__(kFoSplitBlock) void k_intensity_split(StepArgs a, c
                 const uint32_t rk = rank[k];
                 if (rk < e0 || rk >= e0 + own) continue;
                 uint32_t in = rk - e0, b = b0;
-                while (b + 1u < b1 && in >= G.hist[b]) in -= G.hist[b++];
+                while (b + 1u < b1 && in >= hist[b]) in -= hist[b++];
                 rank_val[k] = vmin + b;
             }
         Centred cm;
         for (uint32_t b = threadIdx.x; b <= D; b += kFoSplitBlock) {
-            const uint32_t h = G.hist[b];
+            const uint32_t h = hist[b];
             if (!h) continue;
             cm.add((double)(vmin + b) - mean, (double)h);
             atomicAdd(&lev[fbn_level_rd(vmin + b, vmin, rcp, ng) - 1u], h);
@@ -693,7 +697,7 @@ __global__ __launch_bounds__(kFoSplitBlock) void k_intensity_split(StepArgs a, c
         const double med = pct[3], p10 = pct[1], p90 = pct[5];
         double c[3] = {};
         for (uint32_t b = threadIdx.x; b <= D; b += kFoSplitBlock) {
-            const double x = (double)(vmin + b), h = (double)G.hist[b];
+            const double x = (double)(vmin + b), h = (double)hist[b];
             c[0] += h * fabs(x - med);
             if (x >= p10 && x <= p90) { c[1] += h; c[2] += h * x; }
         }
@@ -702,7 +706,7 @@ __global__ __launch_bounds__(kFoSplitBlock) void k_intensity_split(StepArgs a, c
         double e[3] = {};
         if (c[1] > 0.0)
             for (uint32_t b = threadIdx.x; b <= D; b += kFoSplitBlock) {
-                const double x = (double)(vmin + b), h = (double)G.hist[b];
+                const double x = (double)(vmin + b), h = (double)hist[b];
                 if (x >= p10 && x <= p90) e[2] += h * fabs(x - mus);
             }
         fo_levels(lev, ng, nd, kFoSplitBlock, e, &best);
@@ -728,8 +732,9 @@ __global__ __launch_bounds__(256) void k_intensity_zero(StepArgs a, FoSlot *slot
         const uint32_t r = a.split_roi[slot];
         if (r >= a.roi_cap) continue;
         FoSlot &G = slots[slot];
+        uint32_t *hist = fo_hist(slots, a.g_cap, a.rois[r]);
         const uint32_t D = a.rois[r].vmax - a.rois[r].vmin, t = blockIdx.x * 256u + threadIdx.x;
-        for (uint32_t b = t; b <= D; b += gridDim.x * 256u) G.hist[b] = 0u;
+        for (uint32_t b = t; b <= D; b += gridDim.x * 256u) hist[b] = 0u;
         if (t < 8u) G.s[t] = 0ull;
         if (t == 8u) { G.emin = 0xFFFFFFFFu; G.emax = 0u; }
     }
@@ -813,16 +818,18 @@ __global__ __launch_bounds__(kWave) void k_intensity_rows(StepArgs a, const FoSu
     for (uint32_t i = threadIdx.x; i < n_out * (uint32_t)kNumIntensityFeat; i += kWave) out[i] = rows[i];
 }
 
-uint64_t intensity_slot_bytes() { return sizeof(FoSlot); }
+uint64_t intensity_slot_bytes(uint32_t n_split, uint32_t n_aux) {
+    return (uint64_t)n_split * sizeof(FoSlot) + 256ull * n_aux;
+}
 uint64_t intensity_sums_bytes(uint32_t n_rois) { return (uint64_t)n_rois * sizeof(FoSums); }
 
-// Voxels per tile of a split ROI: small enough to spread a few large regions
-// over the chip, large enough that at most kFoMaxSlots regions are split
-// (their histograms stay within 256 MB); in images that large the many tiles
-// fill the chip anyway.
-uint32_t intensity_tile_vox(uint64_t total_vox) {
-    const uint64_t t = (total_vox + kFoMaxSlots - 1u) / kFoMaxSlots;
-    return (uint32_t)(t > kFoMinTile ? (t < (1u << 30) ? t : (1u << 30)) : kFoMinTile);
+// Voxels per tile of a split ROI: a sixteenth of a CU's share of the image
+// voxels, so that no region's tail outlasts the rest (with regions of up to
+// 128 K voxels in one work-group the tail was most of 589 us on eight
+// 2048 x 2048 images), but no fewer than a histogram's merge is worth.
+uint32_t intensity_tile_vox(uint64_t total_vox, uint32_t n_cu) {
+    const uint64_t t = total_vox / (16ull * (n_cu ? n_cu : 1u));
+    return (uint32_t)(t > kFoMinTile ? (t < (1u << 20) ? t : (1u << 20)) : kFoMinTile);
 }
 
 hipError_t launch_intensity(const StepArgs &a, uint32_t items, uint32_t n_cu, int fp64, void *slots, void *sums,

@@ -6,10 +6,12 @@
 
 namespace nyx {
 
-hipError_t launch_max_label(const ImgDesc *imgs, int n_images, uint32_t *out, hipStream_t st);
+hipError_t launch_max_label(const ImgDesc *imgs, int n_images, uint64_t total_vox, uint32_t *out, hipStream_t st);
 hipError_t launch_label_collect(const ImgDesc *imgs, int n_images, uint64_t max_vox, uint64_t *list, uint32_t cap,
                                 uint32_t *count, hipStream_t st);
 hipError_t launch_reset(const StepArgs &a, uint32_t n_counters, hipStream_t st);
+hipError_t launch_reset_counters(const StepArgs &a, uint32_t n_counters, hipStream_t st);
+hipError_t launch_roi_out(const StepArgs &a, hipStream_t st);
 hipError_t launch_fill_u64(uint64_t *p, uint64_t n, uint64_t v, hipStream_t st);
 hipError_t launch_zero_split(const StepArgs &a, hipStream_t st);
 hipError_t launch_scan(const StepArgs &a, hipStream_t st);
@@ -28,9 +30,9 @@ hipError_t launch_coo_emit(const StepArgs &a, uint32_t n_slots, const uint64_t *
                            uint64_t *vals, hipStream_t st);
 hipError_t launch_coo_features(const StepArgs &a, const uint64_t *keys, const uint64_t *vals, uint64_t nnz,
                                uint32_t n_rois, uint64_t *seg, DirSums *sums, DirSumsY *sums_y, hipStream_t st);
-uint64_t intensity_slot_bytes();
+uint64_t intensity_slot_bytes(uint32_t n_split, uint32_t n_aux);
 uint64_t intensity_sums_bytes(uint32_t n_rois);
-uint32_t intensity_tile_vox(uint64_t total_vox);
+uint32_t intensity_tile_vox(uint64_t total_vox, uint32_t n_cu);
 hipError_t launch_intensity(const StepArgs &a, uint32_t items, uint32_t n_cu, int fp64, void *slots, void *sums,
                             void *table, uint32_t table_rows, hipStream_t st);
 uint32_t neighbourhood_lds_bytes(uint32_t ng, int any_volume);

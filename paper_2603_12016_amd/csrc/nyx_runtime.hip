@@ -53,6 +53,15 @@ constexpr uint32_t kRingMin = 2048u, kRingMax = 32768u;   // staged-accumulation
 constexpr uint32_t kMaxGroupsPerCu = 5u;                  // k_batch, single precision: 5 waves per SIMD
 constexpr uint32_t kMaxNgFused = 8191u;         // hash keys carry 13-bit levels
 constexpr uint64_t kMaxLabelEntries = 1ull << 26;
+// A context's block for the one-shot calls: what the largest call so far
+// asked for, between these bounds (what exceeds it is allocated and freed by
+// the call).
+constexpr size_t kPoolMin = 32u << 20, kPoolMax = 512u << 20;
+// Pinned staging memory: image descriptors up, counters and ROI descriptors down.
+constexpr size_t kPinBytes = 512u << 10, kPinUp = 128u << 10, kPinDown = kPinBytes - kPinUp;
+// Discovery fills the ROI descriptors (and the tile queue) in one go, sized by
+// the label table, up to this many entries; above, the ROIs are counted first.
+constexpr uint32_t kOnePassLabels = 1u << 17;
 // Banded accumulation (hash mode, symmetric matrices): ROIs above
 // kBandMinVox voxels (and above the split size), LDS band of at most
 // kBandLds bytes, work items of about kBandTile bbox voxels.
@@ -67,21 +76,31 @@ int log_level() {
     return lvl;
 }
 
-// A bump allocator over a fixed device region (the no-allocation entry
-// point's scratch): carving never calls the HIP allocator, and the region is
-// reused from its start by the next call.
+// A bump allocator over a device region, reused from its start by the next
+// call: the fixed scratch of the no-allocation entry point, or a context's
+// own block for the one-shot calls (spill: requests that do not fit come from
+// hipMalloc, and the block grows to the call's demand before the next one).
 struct Arena {
     uint8_t *base = nullptr;
     size_t cap = 0, used = 0;
     size_t wanted = 0;   // bytes the failed request would have needed in total
+    size_t demand = 0;   // bytes asked for since the arena was last started
+    bool spill = false;
+    static size_t up(size_t n) { return (n + 255u) & ~(size_t)255u; }
     void *carve(size_t n) {
-        const size_t at = (used + 255u) & ~(size_t)255u;
+        const size_t at = up(used);
+        demand += up(n);
         if (at + n > cap) {
             wanted = at + n;
             return nullptr;
         }
         used = at + n;
         return base + at;
+    }
+    bool fits(size_t n) const { return up(used) + n <= cap; }
+    // gives back the tail of the latest request
+    void trim(const void *p, size_t from, size_t to) {
+        if (base && static_cast<const uint8_t *>(p) + from == base + used) used -= from - to;
     }
 };
 
@@ -107,9 +126,11 @@ struct DevBuf {
         if (n == 0) n = 16;
         if (arena) {
             p = arena->carve(n);
-            if (!p) return hipErrorOutOfMemory;
-            bytes = n;
-            return hipSuccess;
+            if (p) {
+                bytes = n;
+                return hipSuccess;
+            }
+            if (!arena->spill) return hipErrorOutOfMemory;
         }
         hipError_t e = hipMalloc(&p, n);
         if (e == hipSuccess) {
@@ -119,6 +140,13 @@ struct DevBuf {
             p = nullptr;
         }
         return e;
+    }
+    // keeps the first n bytes
+    void shrink(size_t n) {
+        if (n == 0) n = 16;
+        if (!p || n >= bytes) return;
+        if (arena && !owned) arena->trim(p, bytes, n);
+        bytes = n;
     }
     template <class T> T *as() const { return reinterpret_cast<T *>(p); }
 };
@@ -163,22 +191,26 @@ struct nyx_ctx {
     std::string err;
     hipStream_t capture_stream = nullptr;
     uint8_t *scratch = nullptr;   // this device's no-allocation scratch (device address)
+    Arena pool;                   // device block of the one-shot calls
+    uint8_t *pin = nullptr;       // kPinBytes of pinned host memory for the calls' small copies
 };
 
 // All device state of one discovery/step over a batch of images.
 struct Work {
     std::vector<ImgDesc> h_imgs;
-    DevBuf imgs, tab[10], counters, rois, buckets, G, dsums, dsums_y, split_roi, band_roi, smarg, stot, splp, vox_base,
-        dict;
+    DevBuf imgs, tab[10], counters, rois, buckets, G, dsums, dsums_y, split_roi, band_roi, smarg, stot, splp, dict;
+    uint64_t *vox_base = nullptr;      // first voxel of each image (device, behind the image descriptors)
+    uint32_t n_split = 0, n_aux = 0;   // split ROIs and their extra storage (tile queue)
     uint32_t tab_total = 0, n_blocks = 0, n_counters = 0, total_chunks = 0;
     uint32_t n_rois = 0;
     uint64_t total_vox = 0;
     std::vector<RoiDesc> h_rois;
     StepArgs args{};
+    bool have_rois = false;            // h_rois holds the descriptors
     // Carve every buffer from `ar` (nullptr: hipMalloc).
     void use_arena(Arena *ar) {
         for (DevBuf *b : {&imgs, &counters, &rois, &buckets, &G, &dsums, &dsums_y, &split_roi, &band_roi, &smarg, &stot,
-                          &splp, &vox_base, &dict})
+                          &splp, &dict})
             b->arena = ar;
         for (DevBuf &b : tab) b.arena = ar;
     }
@@ -306,12 +338,87 @@ nyx_status build_label_dict(nyx_ctx *ctx, Work &w, int32_t n, hipStream_t st) {
     return NYX_OK;
 }
 
-// Label tables, ROI discovery and the ROI table (no work items).
-nyx_status discover(nyx_ctx *ctx, const nyx_image *imgs, int32_t n, Work &w, hipStream_t st) {
+// A one-shot call: its buffers come from the context's block, which earlier
+// calls have finished with (each waits for its stream before it returns, and
+// this guard waits where one fails on the way).
+struct OneShot {
+    hipStream_t st;
+    bool done = false;
+    OneShot(nyx_ctx *ctx, hipStream_t s) : st(s) {
+        Arena &p = ctx->pool;
+        const size_t want = std::min(std::max(p.demand + p.demand / 4u, kPoolMin), kPoolMax);
+        if (!p.base || (p.demand > p.cap && want > p.cap)) {
+            if (p.base) (void)hipFree(p.base);
+            p.base = nullptr;
+            p.cap = 0;
+            void *q = nullptr;
+            if (hipMalloc(&q, want) == hipSuccess) {
+                p.base = static_cast<uint8_t *>(q);
+                p.cap = want;
+            } else {
+                (void)hipGetLastError();   // every request spills
+            }
+        }
+        p.spill = true;
+        p.used = p.demand = p.wanted = 0;
+    }
+    ~OneShot() {
+        if (!done) (void)hipStreamSynchronize(st);
+    }
+    nyx_status end(nyx_status s) {
+        done = s == NYX_OK;
+        return s;
+    }
+};
+
+// Host to device through the pinned staging memory (at offset `at` of its
+// upward part) where it fits there; the copy is then asynchronous and the
+// staged bytes stay until the next synchronisation of the stream.
+hipError_t copy_up(nyx_ctx *ctx, void *dst, const void *src, size_t n, size_t at, hipStream_t st) {
+    if (at + n > kPinUp) return hipMemcpyAsync(dst, src, n, hipMemcpyHostToDevice, st);
+    memcpy(ctx->pin + at, src, n);
+    return hipMemcpyAsync(dst, ctx->pin + at, n, hipMemcpyHostToDevice, st);
+}
+
+// Tile queue asked of discovery: ROIs above tile_vox voxels are split.
+struct TileQueue {
+    uint32_t tile_vox = 0;
+    int aux_values = 0;   // split ROIs get storage for one counter per value of their range
+};
+
+// Work queue of a family whose items are tiles of about tile_vox voxels: the
+// compaction cuts every ROI above tile_vox into fewer than 2 ceil(n / tile_vox)
+// tiles (tiles_for), so the image's voxels bound the entries and the split
+// ROIs.
+nyx_status setup_tiles(nyx_ctx *ctx, Work &w, uint32_t roi_cap, const TileQueue &q) {
+    StepArgs &a = w.args;
+    const uint64_t n_split = std::min<uint64_t>(roi_cap, w.total_vox / q.tile_vox);
+    const uint64_t n_items = roi_cap + 4u * (w.total_vox / q.tile_vox);
+    if (n_items >= (1ull << 31)) return fail(ctx, NYX_ERR_UNSUPPORTED, "too many work items");
+    HIPC(ctx, w.buckets.alloc((size_t)kClasses * std::max<uint64_t>(n_items, 1u) * sizeof(uint2)));
+    HIPC(ctx, w.split_roi.alloc(std::max<uint64_t>(n_split, 1u) * 4u));
+    a.buckets = w.buckets.as<uint2>();
+    a.bucket_cap = (uint32_t)std::max<uint64_t>(n_items, 1u);
+    a.split_roi = w.split_roi.as<uint32_t>();
+    a.g_cap = (uint32_t)n_split;
+    a.split_vox = a.tile_vox = q.tile_vox;
+    a.aux_values = q.aux_values;
+    a.enqueue = 1;
+    return NYX_OK;
+}
+
+// Label tables, ROI discovery and the ROI descriptors (device), with the tile
+// queue if one is asked for.  want_rois: the descriptors are wanted on the
+// host too (fetch_rois).
+nyx_status discover(nyx_ctx *ctx, const nyx_image *imgs, int32_t n, Work &w, hipStream_t st, bool want_rois,
+                    const TileQueue *tiles = nullptr) {
     w.h_imgs.resize(n);
     uint32_t chunk = 0;
     uint64_t tv = 0;
-    std::vector<uint64_t> vbase(n);
+    // one upload: image descriptors, first voxels, and the cleared label maxima
+    std::vector<uint64_t> up((sizeof(ImgDesc) * n + 12u * n + 7u) / 8u, 0u);
+    uint64_t *vbase = up.data() + sizeof(ImgDesc) / 8u * n;
+    static_assert(sizeof(ImgDesc) % 8u == 0, "ImgDesc is followed by 64-bit words");
     for (int i = 0; i < n; ++i) {
         ImgDesc &d = w.h_imgs[i];
         memset(&d, 0, sizeof d);
@@ -334,18 +441,20 @@ nyx_status discover(nyx_ctx *ctx, const nyx_image *imgs, int32_t n, Work &w, hip
     }
     w.total_chunks = chunk;
     w.total_vox = tv;
-    HIPC(ctx, w.imgs.alloc(sizeof(ImgDesc) * n));
-    HIPC(ctx, hipMemcpyAsync(w.imgs.p, w.h_imgs.data(), sizeof(ImgDesc) * n, hipMemcpyHostToDevice, st));
-    HIPC(ctx, w.vox_base.alloc(sizeof(uint64_t) * n));
-    HIPC(ctx, hipMemcpyAsync(w.vox_base.p, vbase.data(), sizeof(uint64_t) * n, hipMemcpyHostToDevice, st));
+    memcpy(up.data(), w.h_imgs.data(), sizeof(ImgDesc) * n);
+    HIPC(ctx, w.imgs.alloc(up.size() * 8u));
+    HIPC(ctx, copy_up(ctx, w.imgs.p, up.data(), up.size() * 8u, 0, st));
+    w.vox_base = reinterpret_cast<uint64_t *>(w.imgs.as<ImgDesc>() + n);
+    uint32_t *const dmax = reinterpret_cast<uint32_t *>(w.vox_base + n);
     // largest label per image sizes the label tables
-    DevBuf dmax;
-    dmax.arena = w.imgs.arena;
-    HIPC(ctx, dmax.alloc(sizeof(uint32_t) * n));
-    std::vector<uint32_t> zeros(n, 0u), hmax(n);
-    HIPC(ctx, hipMemcpyAsync(dmax.p, zeros.data(), sizeof(uint32_t) * n, hipMemcpyHostToDevice, st));
-    HIPC(ctx, launch_max_label(w.imgs.as<ImgDesc>(), n, dmax.as<uint32_t>(), st));
-    HIPC(ctx, hipMemcpyAsync(hmax.data(), dmax.p, sizeof(uint32_t) * n, hipMemcpyDeviceToHost, st));
+    std::vector<uint32_t> big;
+    uint32_t *hmax = reinterpret_cast<uint32_t *>(ctx->pin + kPinUp);
+    if (sizeof(uint32_t) * n > kPinDown) {
+        big.resize(n);
+        hmax = big.data();
+    }
+    HIPC(ctx, launch_max_label(w.imgs.as<ImgDesc>(), n, tv, dmax, st));
+    HIPC(ctx, hipMemcpyAsync(hmax, dmax, sizeof(uint32_t) * n, hipMemcpyDeviceToHost, st));
     HIPC(ctx, hipStreamSynchronize(st));
     uint64_t total = 0;
     for (int i = 0; i < n; ++i) total += (uint64_t)hmax[i] + 1u;
@@ -372,7 +481,7 @@ nyx_status discover(nyx_ctx *ctx, const nyx_image *imgs, int32_t n, Work &w, hip
         total += (uint64_t)w.h_imgs[i].max_label + 1u;
     }
     w.tab_total = (uint32_t)total;
-    HIPC(ctx, hipMemcpyAsync(w.imgs.p, w.h_imgs.data(), sizeof(ImgDesc) * n, hipMemcpyHostToDevice, st));
+    HIPC(ctx, copy_up(ctx, w.imgs.p, w.h_imgs.data(), sizeof(ImgDesc) * n, 0, st));
     for (auto &b : w.tab) HIPC(ctx, b.alloc(sizeof(uint32_t) * (size_t)total));
     w.n_blocks = (w.tab_total + 1023u) / 1024u;
     w.n_counters = C_BLOCKS + w.n_blocks;
@@ -397,36 +506,55 @@ nyx_status discover(nyx_ctx *ctx, const nyx_image *imgs, int32_t n, Work &w, hip
     a.counters = w.counters.as<uint32_t>();
     HIPC(ctx, launch_reset(a, w.n_counters, st));
     HIPC(ctx, launch_scan(a, st));
-    // ROI count from the per-block counts
-    StepArgs a0 = a;
-    if (w.n_blocks) {
-        // count kernel only (compaction with zero ROI capacity writes nothing)
-        a0.roi_cap = 0;
-        a0.enqueue = 0;
-        HIPC(ctx, launch_compact(a0, 0u, 0u, st));
+    // The descriptors, in room for every label where that is little; else
+    // the ROIs are counted first (a compaction with no ROI capacity writes
+    // nothing) and the compaction repeated with room for them.
+    const size_t roi_room = sizeof(RoiDesc) * (size_t)w.tab_total;
+    const bool one_pass = w.tab_total <= kOnePassLabels && (!w.rois.arena || w.rois.arena->spill || w.rois.arena->fits(roi_room));
+    const uint32_t *hc = reinterpret_cast<const uint32_t *>(ctx->pin + kPinUp);
+    constexpr size_t kHead = 16u * sizeof(uint32_t);
+    const uint32_t spec = want_rois && one_pass ? (uint32_t)std::min<size_t>(w.tab_total, (kPinDown - kHead) / sizeof(RoiDesc)) : 0u;
+    nyx_status s = NYX_OK;
+    for (int pass = one_pass ? 1 : 0; pass < 2; ++pass) {
+        const uint32_t cap = pass == 0 ? 0u : (one_pass ? w.tab_total : w.n_rois);
+        if (pass == 1) {
+            if (tiles && (s = setup_tiles(ctx, w, cap, *tiles)) != NYX_OK) return s;
+            HIPC(ctx, w.rois.alloc(sizeof(RoiDesc) * std::max<uint32_t>(cap, 1u)));
+            a.rois = w.rois.as<RoiDesc>();
+        }
+        a.roi_cap = cap;
+        if (pass == 1 && !one_pass) HIPC(ctx, launch_reset_counters(a, w.n_counters, st));
+        HIPC(ctx, launch_compact(a, 0u, 0xFFFFFFFFu, st));
+        HIPC(ctx, hipMemcpyAsync(ctx->pin + kPinUp, w.counters.p, kHead, hipMemcpyDeviceToHost, st));
+        if (spec && pass == 1)
+            HIPC(ctx, hipMemcpyAsync(ctx->pin + kPinUp + kHead, w.rois.p, sizeof(RoiDesc) * spec, hipMemcpyDeviceToHost, st));
+        HIPC(ctx, hipStreamSynchronize(st));
+        if (hc[C_ERR] & E_LABEL_RANGE) return fail(ctx, NYX_ERR_INTERNAL, "label range check failed during discovery");
+        w.n_rois = hc[C_NROIS];
     }
-    std::vector<uint32_t> hc(w.n_counters);
-    HIPC(ctx, hipMemcpyAsync(hc.data(), w.counters.p, sizeof(uint32_t) * w.n_counters, hipMemcpyDeviceToHost, st));
-    HIPC(ctx, hipStreamSynchronize(st));
-    if (hc[C_ERR] & E_LABEL_RANGE) return fail(ctx, NYX_ERR_INTERNAL, "label range check failed during discovery");
-    w.n_rois = hc[C_NROIS];
-    HIPC(ctx, w.rois.alloc(sizeof(RoiDesc) * std::max<uint32_t>(w.n_rois, 1u)));
-    a.rois = w.rois.as<RoiDesc>();
+    if (hc[C_ERR]) return fail(ctx, NYX_ERR_INTERNAL, "discovery failed (error bits %u)", hc[C_ERR]);
+    if (w.n_rois <= spec) {
+        const RoiDesc *h = reinterpret_cast<const RoiDesc *>(ctx->pin + kPinUp + kHead);
+        w.h_rois.assign(h, h + w.n_rois);
+        w.have_rois = true;
+    }
+    w.rois.shrink(sizeof(RoiDesc) * std::max<uint32_t>(w.n_rois, 1u));
     a.roi_cap = w.n_rois;
+    w.n_split = std::min(hc[C_NSPLIT], a.g_cap);
+    w.n_aux = hc[C_AUX];
+    if (tiles) a.g_cap = w.n_split;
     return NYX_OK;
 }
 
-// Re-runs the compaction to fill the ROI descriptors and fetches them.
+// The ROI descriptors on the host.
 nyx_status fetch_rois(nyx_ctx *ctx, Work &w, hipStream_t st) {
-    StepArgs a = w.args;
-    a.enqueue = 0;
-    HIPC(ctx, launch_reset(a, w.n_counters, st));
-    HIPC(ctx, launch_scan(a, st));
-    HIPC(ctx, launch_compact(a, 0u, 0u, st));
+    if (w.have_rois) return NYX_OK;
     w.h_rois.resize(w.n_rois);
-    if (w.n_rois)
+    if (w.n_rois) {
         HIPC(ctx, hipMemcpyAsync(w.h_rois.data(), w.rois.p, sizeof(RoiDesc) * w.n_rois, hipMemcpyDeviceToHost, st));
-    HIPC(ctx, hipStreamSynchronize(st));
+        HIPC(ctx, hipStreamSynchronize(st));
+    }
+    w.have_rois = true;
     return NYX_OK;
 }
 
@@ -818,28 +946,6 @@ nyx_status setup_step(nyx_ctx *ctx, Work &w, const Config &cfg, const nyx_offset
     return NYX_OK;
 }
 
-// Work queue of a family whose items are tiles of about tile_vox voxels: the
-// compaction cuts every ROI above tile_vox into fewer than 2 ceil(n / tile_vox)
-// tiles (tiles_for), so the image's voxels bound the entries and the split
-// ROIs, which get one slot of slot_bytes each.
-nyx_status setup_tiles(nyx_ctx *ctx, Work &w, StepArgs &a, uint32_t tile_vox, uint64_t slot_bytes, DevBuf &slots,
-                       uint32_t *items) {
-    const uint64_t n_split = std::min<uint64_t>(w.n_rois, w.total_vox / tile_vox);
-    const uint64_t n_items = w.n_rois + 4u * (w.total_vox / tile_vox);
-    if (n_items >= (1ull << 31)) return fail(ctx, NYX_ERR_UNSUPPORTED, "too many work items");
-    HIPC(ctx, w.buckets.alloc((size_t)kClasses * std::max<uint64_t>(n_items, 1u) * sizeof(uint2)));
-    HIPC(ctx, w.split_roi.alloc(std::max<uint64_t>(n_split, 1u) * 4u));
-    HIPC(ctx, slots.alloc(n_split * slot_bytes));
-    a.buckets = w.buckets.as<uint2>();
-    a.bucket_cap = (uint32_t)std::max<uint64_t>(n_items, 1u);
-    a.split_roi = w.split_roi.as<uint32_t>();
-    a.g_cap = (uint32_t)n_split;
-    a.split_vox = a.tile_vox = tile_vox;
-    a.enqueue = 1;
-    *items = (uint32_t)n_items;
-    return NYX_OK;
-}
-
 nyx_status set_outputs(nyx_ctx *ctx, StepArgs &a, nyx_roi_table *rois, void *table, uint32_t table_rows) {
     a.table = table;
     a.table_rows = table_rows;
@@ -854,11 +960,17 @@ nyx_status set_outputs(nyx_ctx *ctx, StepArgs &a, nyx_roi_table *rois, void *tab
 }
 
 // The full step on a stream.  per_roi: one accumulation launch per ROI.
-nyx_status enqueue_step(nyx_plan *p, hipStream_t st, bool per_roi) {
+// scanned: the label statistics are those of the discovery just made on this
+// stream (one-shot calls), so the images are not scanned again.
+nyx_status enqueue_step(nyx_plan *p, hipStream_t st, bool per_roi, bool scanned = false) {
     nyx_ctx *ctx = p->ctx;
     const StepArgs &a = p->w.args;
-    HIPC(ctx, launch_reset(a, p->w.n_counters, st));
-    HIPC(ctx, launch_scan(a, st));
+    if (scanned) {
+        HIPC(ctx, launch_reset_counters(a, p->w.n_counters, st));
+    } else {
+        HIPC(ctx, launch_reset(a, p->w.n_counters, st));
+        HIPC(ctx, launch_scan(a, st));
+    }
     HIPC(ctx, launch_compact(a, 0u, 0xFFFFFFFFu, st));
     HIPC(ctx, launch_zero_split(a, st));
     if (!per_roi) {
@@ -873,8 +985,8 @@ nyx_status enqueue_step(nyx_plan *p, hipStream_t st, bool per_roi) {
 }
 
 nyx_status check_counters(nyx_ctx *ctx, Work &w, hipStream_t st) {
-    uint32_t h[8];
-    HIPC(ctx, hipMemcpyAsync(h, w.counters.p, sizeof h, hipMemcpyDeviceToHost, st));
+    const uint32_t *h = reinterpret_cast<const uint32_t *>(ctx->pin + kPinUp);
+    HIPC(ctx, hipMemcpyAsync(ctx->pin + kPinUp, w.counters.p, 8u * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     HIPC(ctx, hipStreamSynchronize(st));
     uint32_t e = h[C_ERR];
     if (e & E_LABEL_RANGE) return fail(ctx, NYX_ERR_CAPACITY, "a label exceeds the planned label range");
@@ -960,7 +1072,14 @@ nyx_status nyx_create(nyx_ctx **out, int device_ordinal) {
     c->device = device_ordinal;
     c->n_cu = prop.multiProcessorCount;
     c->scratch = scr;
+    void *pin = nullptr;
+    if (hipHostMalloc(&pin, kPinBytes, hipHostMallocDefault) != hipSuccess) {
+        delete c;
+        return NYX_ERR_DEVICE;
+    }
+    c->pin = static_cast<uint8_t *>(pin);
     if (hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking) != hipSuccess) {
+        (void)hipHostFree(c->pin);
         delete c;
         return NYX_ERR_DEVICE;
     }
@@ -971,6 +1090,8 @@ nyx_status nyx_create(nyx_ctx **out, int device_ordinal) {
 void nyx_destroy(nyx_ctx *ctx) {
     if (!ctx) return;
     if (ctx->capture_stream) (void)hipStreamDestroy(ctx->capture_stream);
+    if (ctx->pool.base) (void)hipFree(ctx->pool.base);
+    if (ctx->pin) (void)hipHostFree(ctx->pin);
     delete ctx;
 }
 
@@ -1006,22 +1127,20 @@ nyx_status nyx_bin_rois(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_images, i
     if (n_bins < 2 || n_bins > 65535) return fail(ctx, NYX_ERR_INVALID, "n_bins must be in [2, 65535]");
     hipStream_t st = (hipStream_t)stream;
     HIPC(ctx, hipSetDevice(ctx->device));
+    OneShot call(ctx, st);
     Work w;
-    s = discover(ctx, imgs, n_images, w, st);
-    if (s != NYX_OK) return s;
+    w.use_arena(&ctx->pool);
+    if ((s = discover(ctx, imgs, n_images, w, st, false)) != NYX_OK) return s;
     if (rois->n_rois_host) *rois->n_rois_host = w.n_rois;
     if (rois->capacity < (int64_t)w.n_rois)
         return fail(ctx, NYX_ERR_CAPACITY, "ROI table capacity %lld < %u ROIs", (long long)rois->capacity, w.n_rois);
     StepArgs a = w.args;
     a.ng = n_bins;
-    a.enqueue = 0;
     set_outputs(ctx, a, rois, nullptr, 0);
-    HIPC(ctx, launch_reset(a, w.n_counters, st));
-    HIPC(ctx, launch_scan(a, st));
-    HIPC(ctx, launch_compact(a, 0u, 0u, st));
-    if (bins_out) HIPC(ctx, launch_bin_image(a, bins_out, w.total_vox, w.vox_base.as<uint64_t>(), st));
+    HIPC(ctx, launch_roi_out(a, st));
+    if (bins_out) HIPC(ctx, launch_bin_image(a, bins_out, w.total_vox, w.vox_base, st));
     HIPC(ctx, hipStreamSynchronize(st));
-    return NYX_OK;
+    return call.end(NYX_OK);
 }
 
 nyx_status nyx_glcm_accumulate(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_images, const nyx_roi_table *rois,
@@ -1038,15 +1157,17 @@ nyx_status nyx_glcm_accumulate(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_im
     const bool nonsym = symmetric == 0;
     hipStream_t st = (hipStream_t)stream;
     HIPC(ctx, hipSetDevice(ctx->device));
+    OneShot call(ctx, st);
     Work w;
-    if ((s = discover(ctx, imgs, n_images, w, st)) != NYX_OK) return s;
+    w.use_arena(&ctx->pool);
+    if ((s = discover(ctx, imgs, n_images, w, st, true)) != NYX_OK) return s;
     if (rois && rois->n_rois_host && *rois->n_rois_host != (int64_t)w.n_rois)
         return fail(ctx, NYX_ERR_INVALID, "ROI table has %lld rows, images have %u ROIs",
                     (long long)*rois->n_rois_host, w.n_rois);
     if (bins) {
         uint64_t off = 0;
         for (auto &d : w.h_imgs) { d.B = bins + off; off += d.nvox; }
-        HIPC(ctx, hipMemcpyAsync(w.imgs.p, w.h_imgs.data(), sizeof(ImgDesc) * n_images, hipMemcpyHostToDevice, st));
+        HIPC(ctx, copy_up(ctx, w.imgs.p, w.h_imgs.data(), sizeof(ImgDesc) * n_images, 0, st));
     }
     if ((s = fetch_rois(ctx, w, st)) != NYX_OK) return s;
     const uint32_t ng = (uint32_t)n_bins;
@@ -1067,29 +1188,33 @@ nyx_status nyx_glcm_accumulate(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_im
     }
     const uint32_t grid = (uint32_t)ctx->n_cu * (uint32_t)std::max(occ, 1) * 2u;
     DevBuf dcount, doff;
+    dcount.arena = doff.arena = &ctx->pool;
     HIPC(ctx, dcount.alloc((size_t)batch * K * 8u));
     HIPC(ctx, doff.alloc((size_t)batch * K * 8u));
     std::vector<uint64_t> hcount((size_t)batch * K), hoff((size_t)batch * K);
     uint64_t nnz_total = 0;
+    // Phase 0 counts the cells, phase 1 writes them; the matrices of a single
+    // batch are still there in phase 1, those of several are made again.
+    const bool single = batch >= w.n_rois;
     for (int phase = 0; phase < 2; ++phase) {
         uint64_t written = 0;
         for (uint32_t lo = 0; lo < w.n_rois; lo += batch) {
             uint32_t hi = std::min(w.n_rois, lo + batch);
             uint32_t ns = hi - lo;
-            HIPC(ctx, launch_reset(a, w.n_counters, st));
-            HIPC(ctx, launch_scan(a, st));
-            HIPC(ctx, launch_compact(a, lo, hi, st));
-            HIPC(ctx, launch_zero_split(a, st));
-            HIPC(ctx, launch_batch(a, grid, cfg.block, kNone, st));
-            HIPC(ctx, launch_band(a, (uint32_t)ctx->n_cu, st));
-            HIPC(ctx, launch_coo_count(a, ns, dcount.as<uint64_t>(), st));
-            HIPC(ctx, hipMemcpyAsync(hcount.data(), dcount.p, (size_t)ns * K * 8u, hipMemcpyDeviceToHost, st));
-            HIPC(ctx, hipStreamSynchronize(st));
-            if ((s = check_counters(ctx, w, st)) != NYX_OK) return s;
+            if (phase == 0 || !single) {
+                HIPC(ctx, launch_reset_counters(a, w.n_counters, st));
+                HIPC(ctx, launch_compact(a, lo, hi, st));
+                HIPC(ctx, launch_zero_split(a, st));
+                HIPC(ctx, launch_batch(a, grid, cfg.block, kNone, st));
+                HIPC(ctx, launch_band(a, (uint32_t)ctx->n_cu, st));
+                HIPC(ctx, launch_coo_count(a, ns, dcount.as<uint64_t>(), st));
+                HIPC(ctx, hipMemcpyAsync(hcount.data(), dcount.p, (size_t)ns * K * 8u, hipMemcpyDeviceToHost, st));
+                if ((s = check_counters(ctx, w, st)) != NYX_OK) return s;   // (synchronises)
+            }
             uint64_t acc = written;
             for (size_t i = 0; i < (size_t)ns * K; ++i) { hoff[i] = acc; acc += hcount[i]; }
             if (phase == 1) {
-                HIPC(ctx, hipMemcpyAsync(doff.p, hoff.data(), (size_t)ns * K * 8u, hipMemcpyHostToDevice, st));
+                HIPC(ctx, copy_up(ctx, doff.p, hoff.data(), (size_t)ns * K * 8u, 0, st));
                 HIPC(ctx, launch_coo_emit(a, ns, doff.as<uint64_t>(), out->key, out->count, st));
                 HIPC(ctx, hipStreamSynchronize(st));
             }
@@ -1108,7 +1233,7 @@ nyx_status nyx_glcm_accumulate(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_im
             if (nnz_total && (!out->key || !out->count)) return fail(ctx, NYX_ERR_INVALID, "COO arrays are NULL");
         }
     }
-    return NYX_OK;
+    return call.end(NYX_OK);
 }
 
 int32_t nyx_intensity_feature_count(void) { return kNumIntensityFeat; }
@@ -1128,8 +1253,13 @@ nyx_status nyx_intensity_features(nyx_ctx *ctx, const nyx_image *imgs, int32_t n
     if (prec != NYX_FP32 && prec != NYX_FP64) return fail(ctx, NYX_ERR_INVALID, "bad precision");
     hipStream_t st = (hipStream_t)stream;
     HIPC(ctx, hipSetDevice(ctx->device));
+    uint64_t vox = 0;
+    for (int i = 0; i < n_images; ++i) vox += (uint64_t)(imgs[i].nz * imgs[i].ny * imgs[i].nx);
+    const TileQueue tq{intensity_tile_vox(vox, (uint32_t)ctx->n_cu), 1};
+    OneShot call(ctx, st);
     Work w;
-    if ((s = discover(ctx, imgs, n_images, w, st)) != NYX_OK) return s;
+    w.use_arena(&ctx->pool);
+    if ((s = discover(ctx, imgs, n_images, w, st, false, &tq)) != NYX_OK) return s;
     const int64_t n = w.n_rois;
     if (rois && rois->n_rois_host) *rois->n_rois_host = n;
     if (rois && rois->capacity < n)
@@ -1140,17 +1270,14 @@ nyx_status nyx_intensity_features(nyx_ctx *ctx, const nyx_image *imgs, int32_t n
     StepArgs a = w.args;
     a.ng = n_bins;
     DevBuf slots, sums;
-    uint32_t items = 0;
-    if ((s = setup_tiles(ctx, w, a, intensity_tile_vox(w.total_vox), intensity_slot_bytes(), slots, &items)) != NYX_OK)
-        return s;
+    slots.arena = sums.arena = &ctx->pool;
+    HIPC(ctx, slots.alloc(intensity_slot_bytes(w.n_split, w.n_aux)));
     HIPC(ctx, sums.alloc(intensity_sums_bytes(w.n_rois)));
     set_outputs(ctx, a, rois, nullptr, 0);
-    HIPC(ctx, launch_reset(a, w.n_counters, st));
-    HIPC(ctx, launch_scan(a, st));
-    HIPC(ctx, launch_compact(a, 0u, 0xFFFFFFFFu, st));
-    HIPC(ctx, launch_intensity(a, items, (uint32_t)ctx->n_cu, prec == NYX_FP64, slots.p, sums.p, table,
+    HIPC(ctx, launch_roi_out(a, st));
+    HIPC(ctx, launch_intensity(a, a.bucket_cap, (uint32_t)ctx->n_cu, prec == NYX_FP64, slots.p, sums.p, table,
                                (uint32_t)std::min<int64_t>(table_capacity_rows, 0xFFFFFFFFll), st));
-    return check_counters(ctx, w, st);
+    return call.end(check_counters(ctx, w, st));
 }
 
 int32_t nyx_neighbourhood_feature_count(void) { return kNumNeighbourFeat; }
@@ -1175,8 +1302,13 @@ nyx_status nyx_neighbourhood_features(nyx_ctx *ctx, const nyx_image *imgs, int32
                     any_volume ? "3D" : "2D");
     hipStream_t st = (hipStream_t)stream;
     HIPC(ctx, hipSetDevice(ctx->device));
+    uint64_t vox = 0;
+    for (int i = 0; i < n_images; ++i) vox += (uint64_t)(imgs[i].nz * imgs[i].ny * imgs[i].nx);
+    const TileQueue tq{neighbourhood_tile_vox(vox, (uint32_t)ctx->n_cu, (uint32_t)n_bins, any_volume), 0};
+    OneShot call(ctx, st);
     Work w;
-    if ((s = discover(ctx, imgs, n_images, w, st)) != NYX_OK) return s;
+    w.use_arena(&ctx->pool);
+    if ((s = discover(ctx, imgs, n_images, w, st, false, &tq)) != NYX_OK) return s;
     const int64_t n = w.n_rois;
     if (rois && rois->n_rois_host) *rois->n_rois_host = n;
     if (rois && rois->capacity < n)
@@ -1187,18 +1319,14 @@ nyx_status nyx_neighbourhood_features(nyx_ctx *ctx, const nyx_image *imgs, int32
     StepArgs a = w.args;
     a.ng = n_bins;
     DevBuf gtab;
-    uint32_t items = 0;
-    if ((s = setup_tiles(ctx, w, a, neighbourhood_tile_vox(w.total_vox, (uint32_t)ctx->n_cu, (uint32_t)n_bins, any_volume),
-                         neighbourhood_slot_bytes((uint32_t)n_bins, any_volume), gtab, &items)) != NYX_OK)
-        return s;
+    gtab.arena = &ctx->pool;
+    HIPC(ctx, gtab.alloc((size_t)w.n_split * neighbourhood_slot_bytes((uint32_t)n_bins, any_volume)));
     set_outputs(ctx, a, rois, nullptr, 0);
-    HIPC(ctx, launch_reset(a, w.n_counters, st));
-    HIPC(ctx, launch_scan(a, st));
-    HIPC(ctx, launch_compact(a, 0u, 0xFFFFFFFFu, st));
-    HIPC(ctx, launch_neighbourhood(a, items, (uint32_t)ctx->n_cu, prec == NYX_FP64, (uint32_t)alpha, any_volume,
+    HIPC(ctx, launch_roi_out(a, st));
+    HIPC(ctx, launch_neighbourhood(a, a.bucket_cap, (uint32_t)ctx->n_cu, prec == NYX_FP64, (uint32_t)alpha, any_volume,
                                    gtab.as<uint32_t>(), table,
                                    (uint32_t)std::min<int64_t>(table_capacity_rows, 0xFFFFFFFFll), st));
-    return check_counters(ctx, w, st);
+    return call.end(check_counters(ctx, w, st));
 }
 
 nyx_status nyx_glcm_features(nyx_ctx *ctx, const nyx_glcm *glcm, const nyx_roi_table *rois, nyx_precision prec,
@@ -1224,7 +1352,9 @@ nyx_status nyx_glcm_features(nyx_ctx *ctx, const nyx_glcm *glcm, const nyx_roi_t
     const uint32_t n_rois = (uint32_t)glcm->n_rois;
     const int K = glcm->n_offsets;
     if (n_rois == 0) return NYX_OK;
+    OneShot call(ctx, st);
     DevBuf seg, scratch, scratch_y, counters;
+    seg.arena = scratch.arena = scratch_y.arena = counters.arena = &ctx->pool;
     HIPC(ctx, seg.alloc(((size_t)n_rois * K + 1) * 8u));
     HIPC(ctx, scratch.alloc((size_t)n_rois * K * sizeof(DirSums)));
     HIPC(ctx, scratch_y.alloc((size_t)n_rois * K * sizeof(DirSumsY)));
@@ -1242,12 +1372,12 @@ nyx_status nyx_glcm_features(nyx_ctx *ctx, const nyx_glcm *glcm, const nyx_roi_t
     a.nonsym = glcm->symmetric == 0;
     HIPC(ctx, launch_coo_features(a, glcm->key, glcm->count, nnz, n_rois, seg.as<uint64_t>(), scratch.as<DirSums>(),
                                   scratch_y.as<DirSumsY>(), st));
-    uint32_t herr = 0;
-    HIPC(ctx, hipMemcpyAsync(&herr, counters.as<uint32_t>() + C_ERR, 4, hipMemcpyDeviceToHost, st));
+    HIPC(ctx, hipMemcpyAsync(ctx->pin + kPinUp, counters.as<uint32_t>() + C_ERR, 4, hipMemcpyDeviceToHost, st));
     HIPC(ctx, hipStreamSynchronize(st));
+    const uint32_t herr = *reinterpret_cast<const uint32_t *>(ctx->pin + kPinUp);
     if (herr & E_COO_RANGE) return fail(ctx, NYX_ERR_INVALID, "COO entry outside its matrix");
     if (herr & E_TABLE_CAP) return fail(ctx, NYX_ERR_CAPACITY, "feature table too small");
-    return NYX_OK;
+    return call.end(NYX_OK);
 }
 
 }  // extern "C"
@@ -1275,7 +1405,7 @@ nyx_status plan_init(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_images, cons
     p->K = opts->n_offsets;
     p->ng = opts->n_bins;
     p->prec = opts->precision;
-    if ((s = discover(ctx, imgs, n_images, p->w, st)) != NYX_OK) return s;
+    if ((s = discover(ctx, imgs, n_images, p->w, st, true)) != NYX_OK) return s;
     if ((s = fetch_rois(ctx, p->w, st)) != NYX_OK) return s;
     const bool merged = opts->aggregate == NYX_AGG_MERGED;
     // the default plan: one copy (or the forced count) at the load-balance tile size
@@ -1296,6 +1426,25 @@ nyx_status plan_init(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_images, cons
     return NYX_OK;
 }
 
+// One eager step of a configured plan, after the capacity checks of the
+// caller's buffers; waits for the stream.
+nyx_status extract_once(nyx_plan *p, nyx_roi_table *rois, void *table, int64_t table_capacity_rows, hipStream_t st,
+                        bool scanned) {
+    nyx_ctx *ctx = p->ctx;
+    const int64_t n = p->w.n_rois;
+    if (rois && rois->n_rois_host) *rois->n_rois_host = n;
+    if (table_capacity_rows < n)
+        return fail(ctx, NYX_ERR_CAPACITY, "table capacity %lld < %lld rows", (long long)table_capacity_rows, (long long)n);
+    if (rois && rois->capacity < n)
+        return fail(ctx, NYX_ERR_CAPACITY, "ROI table capacity %lld < %lld", (long long)rois->capacity, (long long)n);
+    if (n > 0 && !table) return fail(ctx, NYX_ERR_INVALID, "table is NULL");
+    set_outputs(ctx, p->w.args, rois, table, (uint32_t)n);
+    nyx_status s = enqueue_step(p, st, false, scanned);
+    if (s == NYX_OK) return check_counters(ctx, p->w, st);
+    (void)hipStreamSynchronize(st);
+    return s;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1305,6 +1454,10 @@ nyx_status nyx_plan_create(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_images
     if (!ctx) return NYX_ERR_INVALID;
     if (!out || !opts) return fail(ctx, NYX_ERR_INVALID, "NULL argument");
     *out = nullptr;
+    // The images may have been written on any stream: the plan's own stream
+    // reads them from here on.
+    HIPC(ctx, hipSetDevice(ctx->device));
+    HIPC(ctx, hipDeviceSynchronize());
     hipStream_t st = ctx->capture_stream;
     std::unique_ptr<nyx_plan> p(new nyx_plan());
     std::vector<Config> cands;
@@ -1482,25 +1635,27 @@ void nyx_plan_destroy(nyx_plan *p) {
 nyx_status nyx_extract_batch(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_images, const nyx_extract_opts *opts,
                              nyx_roi_table *rois, void *table, int64_t table_capacity_rows, nyx_stream stream) {
     if (!ctx) return NYX_ERR_INVALID;
-    nyx_plan *p = nullptr;
-    int64_t n = 0;
-    nyx_status s = nyx_plan_create(ctx, imgs, n_images, opts, &p, &n);
+    if (!opts) return fail(ctx, NYX_ERR_INVALID, "NULL argument");
+    hipStream_t st = (hipStream_t)stream;
+    if (opts->autotune) {
+        // timing the candidates runs the step many times: a plan of its own
+        nyx_plan *p = nullptr;
+        int64_t n = 0;
+        nyx_status s = nyx_plan_create(ctx, imgs, n_images, opts, &p, &n);
+        if (s != NYX_OK) return s;
+        s = extract_once(p, rois, table, table_capacity_rows, st, false);
+        nyx_plan_destroy(p);
+        return s;
+    }
+    OneShot call(ctx, st);
+    nyx_plan p;
+    p.w.use_arena(&ctx->pool);
+    std::vector<Config> cands;
+    Config cfg;
+    nyx_status s = plan_init(ctx, imgs, n_images, opts, &p, st, cands, cfg);
+    if (s == NYX_OK) s = configure(&p, cfg, opts);
     if (s != NYX_OK) return s;
-    if (rois && rois->n_rois_host) *rois->n_rois_host = n;
-    if (table_capacity_rows < n) {
-        nyx_plan_destroy(p);
-        return fail(ctx, NYX_ERR_CAPACITY, "table capacity %lld < %lld rows", (long long)table_capacity_rows, (long long)n);
-    }
-    if (rois && rois->capacity < n) {
-        nyx_plan_destroy(p);
-        return fail(ctx, NYX_ERR_CAPACITY, "ROI table capacity %lld < %lld", (long long)rois->capacity, (long long)n);
-    }
-    set_outputs(ctx, p->w.args, rois, table, (uint32_t)n);
-    s = enqueue_step(p, (hipStream_t)stream, false);
-    if (s == NYX_OK) s = check_counters(ctx, p->w, (hipStream_t)stream);
-    else (void)hipStreamSynchronize((hipStream_t)stream);
-    nyx_plan_destroy(p);
-    return s;
+    return call.end(extract_once(&p, rois, table, table_capacity_rows, st, true));
 }
 
 nyx_status nyx_extract_batch_noalloc(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_images,
@@ -1527,18 +1682,7 @@ nyx_status nyx_extract_batch_noalloc(nyx_ctx *ctx, const nyx_image *imgs, int32_
                         ar.wanted);
         return s;
     }
-    const int64_t n = p.w.n_rois;
-    if (rois && rois->n_rois_host) *rois->n_rois_host = n;
-    if (table_capacity_rows < n)
-        return fail(ctx, NYX_ERR_CAPACITY, "table capacity %lld < %lld rows", (long long)table_capacity_rows, (long long)n);
-    if (rois && rois->capacity < n)
-        return fail(ctx, NYX_ERR_CAPACITY, "ROI table capacity %lld < %lld", (long long)rois->capacity, (long long)n);
-    if (n > 0 && !table) return fail(ctx, NYX_ERR_INVALID, "table is NULL");
-    set_outputs(ctx, p.w.args, rois, table, (uint32_t)n);
-    s = enqueue_step(&p, st, false);
-    if (s == NYX_OK) s = check_counters(ctx, p.w, st);
-    else (void)hipStreamSynchronize(st);
-    return s;
+    return extract_once(&p, rois, table, table_capacity_rows, st, true);
 }
 
 }  // extern "C"

@@ -27,6 +27,7 @@ enum Counter : int {
     C_NITEMS = 4,   // work items enqueued
     C_NBAND = 5,    // split ROIs accumulated by the banded kernel
     C_BAND_TICKET = 6,  // work tickets of the banded kernel
+    C_AUX = 7,      // extra storage of the split ROIs, in blocks of 64 counters (aux_values)
     C_CLASS = 8,    // kClasses counters: work-group items per size class
     C_TICKETS = 128,  // kTicketLanes ticket counters of the persistent kernel, kTicketStride apart
     C_BLOCKS = 128 + 32 * 32, // per-block ROI counts of the compaction (variable length)
@@ -75,7 +76,7 @@ struct RoiDesc {
     uint32_t vmin, vmax, gslot, rows;   // rows = bbox rows (z * y extent)
     int32_t x0, y0, z0, x1, y1, z1;
     uint32_t tcols;                      // column blocks per tile row (n_tiles = row blocks * tcols)
-    uint32_t pad1;
+    uint32_t aux;                        // split ROI: first block of its extra storage (aux_values)
 };
 
 // Layout of the persistent kernel's dynamic LDS (byte offsets).
@@ -183,6 +184,7 @@ struct StepArgs {
     uint32_t tile_vox;          // target voxels per tile of a split ROI
     int32_t force_split;        // 1: every ROI goes through the global matrices
     int32_t enqueue;            // 0: compaction builds the ROI table only
+    int32_t aux_values;         // 1: a split ROI gets a counter per value of its range (RoiDesc::aux)
     int32_t fp64;               // feature table element type
     void *table;
     uint32_t table_rows;

@@ -142,6 +142,19 @@ def _stream(stream):
     return c_void_p(int(stream))
 
 
+def _filled(stream):
+    """`stream` as _stream gives it, behind the current stream's work: the
+    wrappers fill the output tensors there before the library writes them."""
+    h = _stream(stream)
+    cur = torch.cuda.current_stream()
+    if (h.value or 0) != cur.cuda_stream:
+        if isinstance(stream, torch.cuda.Stream):
+            stream.wait_stream(cur)
+        else:
+            cur.synchronize()
+    return h
+
+
 def _images(images):
     """images: sequence of (intensity, labels) CUDA tensors of shape (nz, ny, nx)
     or (ny, nx), 2-byte and 4-byte integer dtypes, C-contiguous."""
@@ -192,6 +205,34 @@ def _dev():
     return torch.device("cuda", torch.cuda.current_device())
 
 
+# ROI rows a one-shot call makes room for before it knows the count: one per
+# 256 voxels, within a bound on the memory of the tables.  The usual call then
+# makes one pass over the images; one with more ROIs is told their number and
+# makes a second.
+_GUESS_VOXELS, _GUESS_BYTES, _GUESS_MIN = 256, 32 << 20, 64
+
+
+def _guess_rows(images, row_bytes: int) -> int:
+    vox = sum(int(I.numel()) for I, _ in images)
+    return max(_GUESS_MIN, min(vox // _GUESS_VOXELS, _GUESS_BYTES // (row_bytes + 48)))
+
+
+def _with_room(images, row_bytes, capacity, ctx, attempt):
+    """attempt(capacity) -> (status, n_rois, result) with the caller's capacity, or with a guessed
+    one and, where that is too small, with the count the first attempt reported."""
+    rows = _guess_rows(images, row_bytes) if capacity is None else int(capacity)
+    status, n, result = attempt(rows)
+    if status == NYX_ERR_CAPACITY and capacity is None and n > rows:
+        status, n, result = attempt(n)
+    _check(status, ctx)
+    return result
+
+
+def _rows(t, n: int):
+    """The first n rows; copied out where the tensor holds much more (its memory is then freed)."""
+    return t[:n] if t.shape[0] <= 2 * n + 256 else t[:n].clone()
+
+
 # ------------------------------------------------------------------ objects
 class Ctx:
     def __init__(self, handle):
@@ -226,6 +267,15 @@ class RoiTable:
     @property
     def n_rois(self) -> int:
         return int(self.n.value)
+
+    def _trim(self):
+        """Rows beyond the ROIs found leave the table (one row stays in an empty one)."""
+        n = max(self.n_rois, 1)
+        if n < self.label.shape[0]:
+            for name in ("label", "image", "n_vox", "vmin", "vmax", "bbox"):
+                t = getattr(self, name)
+                setattr(self, name, _rows(t, n))
+            self.capacity = self.n_rois
 
 
 class Glcm:
@@ -285,22 +335,26 @@ def nyx_bin_rois(ctx: Ctx, images, n_bins: int, want_bins: bool = False, stream=
     """ROI table (and optionally the per-voxel level image, flattened over the images)."""
     imgs = _images(images)
     dev = _dev()
-    if capacity is None:
-        probe = RoiTable(0, dev)
-        st = probe.struct()
-        status = lib().nyx_bin_rois(ctx.handle, imgs, len(images), int(n_bins), byref(st), None, _stream(stream))
-        if status not in (NYX_OK, NYX_ERR_CAPACITY):
-            _check(status, ctx)
-        capacity = probe.n_rois
-    rois = RoiTable(capacity, dev)
     bins = None
     if want_bins:
         total = sum(int(I.numel()) for I, _ in images)
         bins = torch.zeros(max(total, 1), dtype=torch.int16, device=dev)
-    st = rois.struct()
-    _check(lib().nyx_bin_rois(ctx.handle, imgs, len(images), int(n_bins), byref(st),
-                              bins.data_ptr() if bins is not None else None, _stream(stream)), ctx)
+
+    def attempt(rows):
+        rois = RoiTable(rows, dev)
+        st = rois.struct()
+        status = lib().nyx_bin_rois(ctx.handle, imgs, len(images), int(n_bins), byref(st),
+                                    bins.data_ptr() if bins is not None else None, _filled(stream))
+        return status, rois.n_rois, rois
+    rois = _with_room(images, 0, capacity, ctx, attempt)
+    if capacity is None:
+        rois._trim()
     return rois, bins
+
+
+# Bytes of key and count arrays nyx_glcm_accumulate makes room for before it
+# knows how many cells are nonzero.
+_GUESS_CELL_BYTES = 64 << 20
 
 
 def nyx_glcm_accumulate(ctx: Ctx, images, rois: RoiTable, n_bins: int, offsets, bins=None, stream=None,
@@ -308,21 +362,26 @@ def nyx_glcm_accumulate(ctx: Ctx, images, rois: RoiTable, n_bins: int, offsets, 
     imgs = _images(images)
     offs, K = _offsets(offsets)
     dev = _dev()
-    nnz = c_int64(0)
-    out = nyx_glcm(None, None, 0, ctypes.pointer(nnz), 0, 0, 1, 0)
     rs = rois.struct() if rois is not None else None
     bptr = bins.data_ptr() if bins is not None else None
-    status = lib().nyx_glcm_accumulate(ctx.handle, imgs, len(images), byref(rs) if rs is not None else None, bptr,
-                                       offs, K, 1 if symmetric else 0, int(n_bins), byref(out), _stream(stream))
-    if status not in (NYX_OK, NYX_ERR_CAPACITY):
-        _check(status, ctx)
-    n = int(nnz.value)
-    keys = torch.zeros(max(n, 1), dtype=torch.int64, device=dev)
-    counts = torch.zeros(max(n, 1), dtype=torch.int64, device=dev)
-    out = nyx_glcm(keys.data_ptr(), counts.data_ptr(), n, ctypes.pointer(nnz), 0, 0, 1, 0)
-    _check(lib().nyx_glcm_accumulate(ctx.handle, imgs, len(images), byref(rs) if rs is not None else None, bptr,
-                                     offs, K, 1 if symmetric else 0, int(n_bins), byref(out), _stream(stream)), ctx)
-    return Glcm(keys[:n], counts[:n], n, int(n_bins), K, int(out.n_rois), symmetric)
+    nnz = c_int64(0)
+    # no more cells than voxel pairs, nor (with the ROI count) than matrix cells
+    cap = K * sum(int(I.numel()) for I, _ in images)
+    if rois is not None:
+        cap = min(cap, rois.n_rois * K * (n_bins * (n_bins + 1) // 2 if symmetric else n_bins * n_bins))
+    cap = max(min(cap, _GUESS_CELL_BYTES // 16), 0)
+    while True:
+        keys = torch.empty(max(cap, 1), dtype=torch.int64, device=dev)
+        counts = torch.empty(max(cap, 1), dtype=torch.int64, device=dev)
+        out = nyx_glcm(keys.data_ptr(), counts.data_ptr(), cap, ctypes.pointer(nnz), 0, 0, 1, 0)
+        status = lib().nyx_glcm_accumulate(ctx.handle, imgs, len(images), byref(rs) if rs is not None else None, bptr,
+                                           offs, K, 1 if symmetric else 0, int(n_bins), byref(out), _filled(stream))
+        n = int(nnz.value)
+        if status != NYX_ERR_CAPACITY or n <= cap:
+            break
+        cap = n
+    _check(status, ctx)
+    return Glcm(_rows(keys, n), _rows(counts, n), n, int(n_bins), K, int(out.n_rois), symmetric)
 
 
 def nyx_glcm_features(ctx: Ctx, glcm: Glcm, precision: int = NYX_FP32, stream=None, capacity=None,
@@ -334,7 +393,7 @@ def nyx_glcm_features(ctx: Ctx, glcm: Glcm, precision: int = NYX_FP32, stream=No
     g = glcm.struct(nnz)
     rs = rois.struct() if rois is not None else None
     _check(lib().nyx_glcm_features(ctx.handle, byref(g), byref(rs) if rs is not None else None, int(precision),
-                                   table.data_ptr(), rows, _stream(stream)), ctx)
+                                   table.data_ptr(), rows, _filled(stream)), ctx)
     return table[:glcm.n_rois]
 
 
@@ -347,25 +406,30 @@ def nyx_intensity_feature_name(f: int):
     return None if s is None else s.decode()
 
 
+def _family(ctx, images, width, precision, capacity, call):
+    """One call of a 37-column family: call(rois struct, table pointer, rows) -> status."""
+    dtype = torch.float64 if precision == NYX_FP64 else torch.float32
+    dev = _dev()
+
+    def attempt(rows):
+        rois = RoiTable(rows, dev)
+        table = torch.full((max(rows, 1), width), float("nan"), dtype=dtype, device=dev)
+        st = rois.struct()
+        return call(st, table.data_ptr(), rows), rois.n_rois, (rois, table)
+    rois, table = _with_room(images, width * dtype.itemsize, capacity, ctx, attempt)
+    if capacity is None:
+        rois._trim()
+        table = _rows(table, max(rois.n_rois, 1))
+    return rois, table[:rois.n_rois]
+
+
 def nyx_intensity_features(ctx: Ctx, images, n_bins: int, precision: int = NYX_FP32, stream=None, capacity=None):
     """First-order intensity features: returns (RoiTable, table (n, 37))."""
     imgs = _images(images)
-    dev = _dev()
-    if capacity is None:
-        probe = RoiTable(0, dev)
-        st = probe.struct()
-        status = lib().nyx_intensity_features(ctx.handle, imgs, len(images), int(n_bins), int(precision), byref(st),
-                                              None, 0, _stream(stream))
-        if status not in (NYX_OK, NYX_ERR_CAPACITY):
-            _check(status, ctx)
-        capacity = probe.n_rois
-    rois = RoiTable(capacity, dev)
-    dtype = torch.float64 if precision == NYX_FP64 else torch.float32
-    table = torch.full((max(capacity, 1), nyx_intensity_feature_count()), float("nan"), dtype=dtype, device=dev)
-    st = rois.struct()
-    _check(lib().nyx_intensity_features(ctx.handle, imgs, len(images), int(n_bins), int(precision), byref(st),
-                                        table.data_ptr(), int(capacity), _stream(stream)), ctx)
-    return rois, table[:rois.n_rois]
+    return _family(ctx, images, nyx_intensity_feature_count(), precision, capacity,
+                   lambda st, table, rows: lib().nyx_intensity_features(
+                       ctx.handle, imgs, len(images), int(n_bins), int(precision), byref(st), table, rows,
+                       _filled(stream)))
 
 
 def nyx_neighbourhood_feature_count() -> int:
@@ -381,22 +445,10 @@ def nyx_neighbourhood_features(ctx: Ctx, images, n_bins: int, alpha: int = 0, pr
                                stream=None, capacity=None):
     """NGLDM, NGTDM and GLDM features: returns (RoiTable, table (n, 37))."""
     imgs = _images(images)
-    dev = _dev()
-    if capacity is None:
-        probe = RoiTable(0, dev)
-        st = probe.struct()
-        status = lib().nyx_neighbourhood_features(ctx.handle, imgs, len(images), int(n_bins), int(alpha),
-                                                  int(precision), byref(st), None, 0, _stream(stream))
-        if status not in (NYX_OK, NYX_ERR_CAPACITY):
-            _check(status, ctx)
-        capacity = probe.n_rois
-    rois = RoiTable(capacity, dev)
-    dtype = torch.float64 if precision == NYX_FP64 else torch.float32
-    table = torch.full((max(capacity, 1), nyx_neighbourhood_feature_count()), float("nan"), dtype=dtype, device=dev)
-    st = rois.struct()
-    _check(lib().nyx_neighbourhood_features(ctx.handle, imgs, len(images), int(n_bins), int(alpha), int(precision),
-                                            byref(st), table.data_ptr(), int(capacity), _stream(stream)), ctx)
-    return rois, table[:rois.n_rois]
+    return _family(ctx, images, nyx_neighbourhood_feature_count(), precision, capacity,
+                   lambda st, table, rows: lib().nyx_neighbourhood_features(
+                       ctx.handle, imgs, len(images), int(n_bins), int(alpha), int(precision), byref(st), table, rows,
+                       _filled(stream)))
 
 
 def nyx_extract_batch(ctx: Ctx, images, n_bins: int, offsets, precision: int = NYX_FP32, stream=None,
@@ -407,20 +459,20 @@ def nyx_extract_batch(ctx: Ctx, images, n_bins: int, offsets, precision: int = N
     imgs = _images(images)
     opts, keep = _opts(n_bins, offsets, precision, mode=mode, copies=copies, aggregate=aggregate, symmetric=symmetric)
     dev = _dev()
-    if capacity is None:
-        probe = RoiTable(0, dev)
-        st = probe.struct()
-        status = lib().nyx_extract_batch(ctx.handle, imgs, len(images), byref(opts), byref(st), None, 0,
-                                         _stream(stream))
-        if status not in (NYX_OK, NYX_ERR_CAPACITY):
-            _check(status, ctx)
-        capacity = probe.n_rois
-    rois = RoiTable(capacity, dev)
     dtype = torch.float64 if precision == NYX_FP64 else torch.float32
-    table = torch.zeros((max(capacity, 1), table_blocks(opts.n_offsets, aggregate), 30), dtype=dtype, device=dev)
-    st = rois.struct()
-    _check(lib().nyx_extract_batch(ctx.handle, imgs, len(images), byref(opts), byref(st), table.data_ptr(),
-                                   int(capacity), _stream(stream)), ctx)
+    blocks = table_blocks(opts.n_offsets, aggregate)
+
+    def attempt(rows):
+        rois = RoiTable(rows, dev)
+        table = torch.zeros((max(rows, 1), blocks, 30), dtype=dtype, device=dev)
+        st = rois.struct()
+        status = lib().nyx_extract_batch(ctx.handle, imgs, len(images), byref(opts), byref(st), table.data_ptr(), rows,
+                                         _filled(stream))
+        return status, rois.n_rois, (rois, table)
+    rois, table = _with_room(images, blocks * 30 * dtype.itemsize, capacity, ctx, attempt)
+    if capacity is None:
+        rois._trim()
+        table = _rows(table, max(rois.n_rois, 1))
     return rois, table[:rois.n_rois]
 
 

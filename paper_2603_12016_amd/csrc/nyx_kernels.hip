@@ -548,7 +548,7 @@ struct ItemDesc {
 };
 static_assert(sizeof(ItemDesc) <= kItemBytes, "staged descriptor exceeds its LDS slot");
 
-__device__ void stage_item(const StepArgs &a, uint32_t roi, uint32_t tile, ItemDesc *dst) {
+__device__ __forceinline__ void stage_item(const StepArgs &a, uint32_t roi, uint32_t tile, ItemDesc *dst) {
     ItemDesc it;
     it.roi = kNone;
     if (roi < a.roi_cap) {
@@ -678,6 +678,13 @@ __device__ __forceinline__ void add_pair(const StepArgs &a, uint8_t *smem, uint3
     }
 }
 
+// On the pair adders of k_batch (and forced on stage_item and the
+// accumulations): one left out of line takes the address of the kernel's
+// arguments, and every use of them then goes through a copy in scratch memory
+// (the list mode did: 484 -> 427 us at 256 levels on 2000 cells, 1201 -> 1000
+// us at 128 levels and 8 offsets on 4400).
+#define NYX_INLINE __attribute__((always_inline))
+
 constexpr uint32_t kStagedMinRows = 4;   // fewer rows per ring chunk: gather instead
 constexpr uint32_t kStageBatch = 8;      // voxels staged per lane and round
 constexpr int kStagedDirs = 13;          // neighbour levels read per group
@@ -712,7 +719,7 @@ __device__ __forceinline__ uint32_t staged_reach(const StepArgs &a, int d0, int 
 // per pass instead of once per offset that reaches it.  Levels fit a byte
 // (ng <= 255).
 template <class Add>
-__device__ void accumulate_staged(const StepArgs &a, const RoiDesc &rd, const ItemCtx &c, uint32_t ra, uint32_t rb,
+__device__ __forceinline__ void accumulate_staged(const StepArgs &a, const RoiDesc &rd, const ItemCtx &c, uint32_t ra, uint32_t rb,
                                   int d0, int d1, uint8_t *ring, uint32_t ring_rows, uint32_t reach, Add &&add) {
     const uint32_t W = (uint32_t)(rd.x1 - rd.x0 + 1), H = (uint32_t)(rd.y1 - rd.y0 + 1), rows = rd.rows;
     const uint32_t C = ring_rows - reach;
@@ -841,7 +848,7 @@ __device__ void accumulate_staged(const StepArgs &a, const RoiDesc &rd, const It
 constexpr int kGatherDirs = 8;
 
 template <class Add, class Off = RowOff>
-__device__ void accumulate_rows(const StepArgs &a, const RoiDesc &rd, const ItemCtx &c, uint32_t ra, uint32_t rb,
+__device__ __forceinline__ void accumulate_rows(const StepArgs &a, const RoiDesc &rd, const ItemCtx &c, uint32_t ra, uint32_t rb,
                                 uint32_t ca, uint32_t cb, int d0, int d1, uint32_t t0, uint32_t ts, Add &&add,
                                 Off off = Off{}) {
     const uint32_t W = cb - ca, H = (uint32_t)(rd.y1 - rd.y0 + 1);
@@ -922,7 +929,7 @@ __device__ __forceinline__ uint32_t lane_next(uint32_t v) {
 // BINS: levels from a caller-supplied bin image (else from intensity); ro:
 // the triangle row offsets of the levels.
 template <bool BINS, class RO, class Add>
-__device__ void accumulate_sweep2d(const RoiDesc &rd, const ItemCtx &c, uint32_t ra, uint32_t rb, uint32_t ca,
+__device__ __forceinline__ void accumulate_sweep2d(const RoiDesc &rd, const ItemCtx &c, uint32_t ra, uint32_t rb, uint32_t ca,
                                    uint32_t cb, int h, int v, int d45, int d135, int w, int nw, RO ro, Add &&add) {
     // a voxel's level, 0 outside the ROI: computed for every lane and then
     // selected by label (no branch per voxel)
@@ -1024,6 +1031,130 @@ __device__ void accumulate_sweep2d(const RoiDesc &rd, const ItemCtx &c, uint32_t
     }
 }
 
+// 3D distance-1 accumulation by row sweep.  A unit is a strip of columns x
+// kSweep3Rows rows of one plane; a wavefront takes 1, 2 or 4 units at a time
+// on groups of 64, 32 or 16 lanes (the fewest strip steps for the width; the
+// first and last lane of a group only supply neighbours).  The unit's rows
+// of its plane and of the next one are loaded in one batch, levels formed
+// once per row, left and right neighbours come by DPP wave shifts and the
+// rows above and below from the lane's own window, so a voxel's 13 pairs
+// cost 2.4 loads, no LDS reads and no barrier.  Bound by VALU issue (some
+// 140 operations a voxel, most of them the 13 cell indices) and the LDS
+// atomics' conflicts; 500 ellipsoids of a 512 x 512 x 256 volume at 64 levels:
+// 1094 us through the staged ring (two LDS reads' latency a pair at eight
+// wavefronts on a CU, two barriers a chunk), 413 us so.
+// slots: 1 + the local direction slot of forward neighbour class c (class3d)
+// in bits 4 c .. 4 c + 3, 0 where it is not in this pass.
+constexpr int kSweep3Rows = 8;
+
+__device__ __forceinline__ uint32_t lane_prev(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x138, 0xF, 0xF, true);  // wave_shr1; lane 0 reads 0
+}
+
+// Levels of one row at the lane's column and its neighbours (0: outside the
+// ROI), with their triangle row offsets.
+struct Row3 {
+    uint32_t l[3], t[3];
+    __device__ __forceinline__ void set(uint32_t v) {
+        l[1] = v;
+        t[1] = row_off(v);
+        l[0] = lane_prev(l[1]); t[0] = lane_prev(t[1]);
+        l[2] = lane_next(l[1]); t[2] = lane_next(t[1]);
+    }
+};
+
+template <class Add>
+__device__ __forceinline__ void accumulate_sweep3d(const RoiDesc &rd, const ItemCtx &c, uint32_t ra, uint32_t rb, uint32_t ca,
+                                   uint32_t cb, uint64_t slots, uint32_t w, uint32_t nw, Add &&add) {
+    const uint32_t Wb = (uint32_t)(rd.x1 - rd.x0 + 1), H = (uint32_t)(rd.y1 - rd.y0 + 1),
+                   Dz = (uint32_t)(rd.z1 - rd.z0 + 1);
+    const uint32_t nx = (uint32_t)c.nx, plane = (uint32_t)c.ny * nx;
+    const uint32_t v00 = (uint32_t)rd.z0 * plane + (uint32_t)rd.y0 * nx + (uint32_t)rd.x0;
+    const uint32_t W = cb - ca;
+    uint32_t lg = 0, best = ((W + 61u) / 62u) << 2;
+    for (uint32_t q = 1; q <= 2u; ++q) {
+        const uint32_t wo = (64u >> q) - 2u, steps = ((W + wo - 1u) / wo) << (2u - q);
+        if (steps < best) { best = steps; lg = q; }
+    }
+    const uint32_t Wl = 64u >> lg, Wo = Wl - 2u, S = 1u << lg;
+    const uint32_t ln = (uint32_t)lane(), sub = ln >> (6u - lg), col = ln & (Wl - 1u);
+    const uint32_t nstrip = (W + Wo - 1u) / Wo, nch = (H + (uint32_t)kSweep3Rows - 1u) / (uint32_t)kSweep3Rows;
+    const uint32_t z_lo = ra / H, z_n = (rb - 1u) / H - z_lo + 1u;
+    const uint32_t units = nstrip * nch * z_n;
+    const bool up = (slots >> 16) != 0ull;   // any pair into the next plane
+    const auto has = [&](int k) { return (slots >> (4 * k) & 15u) != 0ull; };
+    const auto dir = [&](int k) { return (uint32_t)(slots >> (4 * k) & 15u) - 1u; };
+    for (uint32_t u0 = w * S; u0 < units; u0 += nw * S) {
+        const uint32_t u = u0 + sub;
+        uint32_t strip = 0u, z = z_lo;
+        int32_t y0 = 0, lo = 0, hi = 0;   // owned rows [lo, hi) of the unit's rows [y0, y0 + kSweep3Rows)
+        if (u < units) {
+            const uint32_t q = u / nstrip, zq = q / nch;
+            strip = u - q * nstrip;
+            z = z_lo + zq;
+            y0 = (int32_t)((q - zq * nch) * (uint32_t)kSweep3Rows);
+            lo = max(y0, (int32_t)ra - (int32_t)(z * H));
+            hi = min(min(y0 + kSweep3Rows, (int32_t)H), (int32_t)rb - (int32_t)(z * H));
+        }
+        if (__ballot(lo < hi) == 0ull) continue;
+        const int32_t x = (int32_t)(ca + Wo * strip + col) - 1;     // bbox column of the lane
+        const bool xin = lo < hi && x >= 0 && x < (int32_t)Wb;
+        const bool owner = col >= 1u && col <= Wo && x < (int32_t)cb;
+        // rows y0 .. y0 + kSweep3Rows of the plane, y0 - 1 .. y0 + kSweep3Rows of the next
+        uint32_t lab0[kSweep3Rows + 1], val0[kSweep3Rows + 1], lab1[kSweep3Rows + 2], val1[kSweep3Rows + 2];
+        const bool next = xin && up && z + 1u < Dz;
+        const uint32_t vz = v00 + z * plane + (uint32_t)x;
+#pragma unroll
+        for (int j = 0; j < kSweep3Rows + 2; ++j) {
+            const int32_t y = y0 + j - 1;
+            const bool yin = y >= 0 && y < (int32_t)H && y <= hi;
+            if (j > 0) {
+                lab0[j - 1] = 0u;
+                val0[j - 1] = 0u;
+                if (xin && yin && y >= lo) {
+                    lab0[j - 1] = ldg(c.L, vz + (uint32_t)y * nx);
+                    val0[j - 1] = ldg(c.I, vz + (uint32_t)y * nx);
+                }
+            }
+            lab1[j] = 0u;
+            val1[j] = 0u;
+            if (next && yin && y >= lo - 1) {
+                lab1[j] = ldg(c.L, vz + plane + (uint32_t)y * nx);
+                val1[j] = ldg(c.I, vz + plane + (uint32_t)y * nx);
+            }
+        }
+        const auto level = [&](uint32_t lab, uint32_t raw) -> uint32_t {
+            const uint32_t b = fbn_level_rd(raw, c.vmin, c.rcp, c.ng);
+            return lab == c.label ? b : 0u;
+        };
+        Row3 cur, below, n[3];   // rows y, y + 1 of the plane; y - 1, y, y + 1 of the next (by j mod 3)
+        below.set(level(lab0[0], val0[0]));
+        n[0].set(level(lab1[0], val1[0]));
+        n[1].set(level(lab1[1], val1[1]));
+#pragma unroll
+        for (int j = 0; j < kSweep3Rows; ++j) {
+            cur = below;
+            below.set(level(lab0[j + 1], val0[j + 1]));
+            n[(j + 2) % 3].set(level(lab1[j + 2], val1[j + 2]));
+            const int32_t y = y0 + j;
+            if (owner && cur.l[1] && y >= lo && y < hi) {
+                const uint32_t a = cur.l[1], ta = cur.t[1];
+                if (has(0) && cur.l[2]) add(dir(0), a, ta, cur.l[2], cur.t[2]);
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    if (has(1 + k) && below.l[k]) add(dir(1 + k), a, ta, below.l[k], below.t[k]);
+#pragma unroll
+                for (int r = 0; r < 3; ++r)
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        const Row3 &m = n[(j + r) % 3];
+                        if (has(4 + 3 * r + k) && m.l[k]) add(dir(4 + 3 * r + k), a, ta, m.l[k], m.t[k]);
+                    }
+            }
+        }
+    }
+}
+
 // One direction of a finished item: features (unsplit ROI) or a 64-bit
 // atomic merge into the ROI's global matrix (tile of a split ROI).
 template <class Acc, bool NS, class Src>
@@ -1053,9 +1184,11 @@ __device__ __forceinline__ void dir_or_flush(const StepArgs &a, const WaveGrp &g
 // separate instantiation so the symmetric kernel carries none of its code
 // (and none of its registers).  BS: threads per work-group, 256, or 512 for
 // layouts whose LDS leaves room for one work-group per CU only (eight waves
-// instead of four then share the CU's latency).
-template <int MODE, class OutT, bool NS, int BS>
-__global__ __launch_bounds__(BS, ((BS == 256 && sizeof(OutT) == 4) ? 5 : 1)) void k_batch(StepArgs a,
+// instead of four then share the CU's latency).  VOL: the 3D row sweep, with
+// neither the 2D sweep nor the staged ring; at most 128 VGPRs, so that two
+// work-groups of 512 threads fit a CU.
+template <int MODE, class OutT, bool NS, int BS, bool VOL>
+__global__ __launch_bounds__(BS, VOL ? 4 : ((BS == 256 && sizeof(OutT) == 4) ? 5 : 1)) void k_batch(StepArgs a,
                                                                                       uint32_t direct_roi) {
     extern __shared__ __align__(16) uint8_t smem[];
     typedef typename std::conditional<sizeof(OutT) == 8, double, float>::type Acc;
@@ -1138,15 +1271,27 @@ __global__ __launch_bounds__(BS, ((BS == 256 && sizeof(OutT) == 4) ? 5 : 1)) voi
                     // ordered pairs (level at v, level at v + d) by gather, into squares
                     if (MODE != 0 && ra < rb && ca < cb) {
                         const bool merged = MODE >= 2 && a.merged;
-                        auto add = [&](uint32_t dl, uint32_t la, uint32_t ta, uint32_t lb, uint32_t tb) {
+                        auto add = [&](uint32_t dl, uint32_t la, uint32_t ta, uint32_t lb, uint32_t tb) NYX_INLINE {
                             add_pair<MODE, true>(a, smem, merged ? 0u : dl, la, ta, lb, tb);
                         };
                         accumulate_rows(a, rd, c, ra, rb, ca, cb, d0, d1, threadIdx.x, blockDim.x, add, SqOff{ng});
                     }
+                } else if constexpr (VOL) {
+                    // (a caller-supplied bin image takes the gather)
+                    if (ra < rb && ca < cb) {
+                        const bool merged = MODE >= 2 && a.merged;
+                        auto add = [&](uint32_t dl, uint32_t la, uint32_t ta, uint32_t lb, uint32_t tb) NYX_INLINE {
+                            add_pair<MODE>(a, smem, merged ? 0u : dl, la, ta, lb, tb);
+                        };
+                        if (!c.B && pass < kMaxSweepPasses)
+                            accumulate_sweep3d(rd, c, ra, rb, ca, cb, a.sweep3[pass], (uint32_t)w, (uint32_t)nw, add);
+                        else
+                            accumulate_rows(a, rd, c, ra, rb, ca, cb, d0, d1, threadIdx.x, blockDim.x, add);
+                    }
                 } else if (ra < rb && ca < cb) {
                     // merged matrices: every offset counts into the one triangle
                     const bool merged = MODE >= 2 && a.merged;
-                    auto add = [&](uint32_t dl, uint32_t la, uint32_t ta, uint32_t lb, uint32_t tb) {
+                    auto add = [&](uint32_t dl, uint32_t la, uint32_t ta, uint32_t lb, uint32_t tb) NYX_INLINE {
                         add_pair<MODE>(a, smem, merged ? 0u : dl, la, ta, lb, tb);
                     };
                     const uint32_t W = (uint32_t)(rd.x1 - rd.x0 + 1), H = (uint32_t)(rd.y1 - rd.y0 + 1);
@@ -1734,16 +1879,16 @@ hipError_t launch_bin_image(const StepArgs &a, uint16_t *bins, uint64_t total_vo
     return hipSuccess;
 }
 
-template <int MODE, class OutT, bool NS, int BS>
+template <int MODE, class OutT, bool NS, int BS, bool VOL>
 static hipError_t launch_batch_b(const StepArgs &a, uint32_t grid, uint32_t direct_roi, hipStream_t st) {
     static bool attr_done = false;
     if (!attr_done) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_batch<MODE, OutT, NS, BS>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_batch<MODE, OutT, NS, BS, VOL>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
         attr_done = true;
     }
-    hipLaunchKernelGGL((k_batch<MODE, OutT, NS, BS>), dim3(grid), dim3(BS), a.lds.bytes, st, a, direct_roi);
+    hipLaunchKernelGGL((k_batch<MODE, OutT, NS, BS, VOL>), dim3(grid), dim3(BS), a.lds.bytes, st, a, direct_roi);
     NYX_CHECK_LAUNCH();
     return hipSuccess;
 }
@@ -1752,9 +1897,13 @@ static hipError_t launch_batch_b(const StepArgs &a, uint32_t grid, uint32_t dire
 template <int MODE, class OutT, bool NS>
 static hipError_t launch_batch_t(const StepArgs &a, uint32_t grid, uint32_t block, uint32_t direct_roi,
                                  hipStream_t st) {
-    if (block == 512u) return launch_batch_b<MODE, OutT, NS, 512>(a, grid, direct_roi, st);
-    if (block != 256u) return hipErrorInvalidConfiguration;
-    return launch_batch_b<MODE, OutT, NS, 256>(a, grid, direct_roi, st);
+    if (block != 256u && block != 512u) return hipErrorInvalidConfiguration;
+    if constexpr (!NS)
+        if (a.sweep3_ok)
+            return block == 512u ? launch_batch_b<MODE, OutT, NS, 512, true>(a, grid, direct_roi, st)
+                                 : launch_batch_b<MODE, OutT, NS, 256, true>(a, grid, direct_roi, st);
+    return block == 512u ? launch_batch_b<MODE, OutT, NS, 512, false>(a, grid, direct_roi, st)
+                         : launch_batch_b<MODE, OutT, NS, 256, false>(a, grid, direct_roi, st);
 }
 
 template <int MODE, bool NS>
@@ -1779,34 +1928,38 @@ hipError_t launch_batch(const StepArgs &a, uint32_t grid, uint32_t block, uint32
     }
 }
 
-template <int MODE, bool NS>
+template <int MODE, bool NS, bool VOL>
 static const void *batch_kernel_m(int fp64, uint32_t block) {
     if (block == 512u)
-        return fp64 ? reinterpret_cast<const void *>(&k_batch<MODE, double, NS, 512>)
-                    : reinterpret_cast<const void *>(&k_batch<MODE, float, NS, 512>);
-    return fp64 ? reinterpret_cast<const void *>(&k_batch<MODE, double, NS, 256>)
-                : reinterpret_cast<const void *>(&k_batch<MODE, float, NS, 256>);
+        return fp64 ? reinterpret_cast<const void *>(&k_batch<MODE, double, NS, 512, VOL>)
+                    : reinterpret_cast<const void *>(&k_batch<MODE, float, NS, 512, VOL>);
+    return fp64 ? reinterpret_cast<const void *>(&k_batch<MODE, double, NS, 256, VOL>)
+                : reinterpret_cast<const void *>(&k_batch<MODE, float, NS, 256, VOL>);
 }
 
-static const void *batch_kernel(int mode, int fp64, int ns, uint32_t block) {
+template <int MODE>
+static const void *batch_kernel_k(int fp64, int ns, int vol, uint32_t block) {
+    if constexpr (MODE != 0)
+        if (ns) return batch_kernel_m<MODE, true, false>(fp64, block);
+    return vol ? batch_kernel_m<MODE, false, true>(fp64, block) : batch_kernel_m<MODE, false, false>(fp64, block);
+}
+
+static const void *batch_kernel(int mode, int fp64, int ns, int vol, uint32_t block) {
     switch (mode) {
-        case 0: return batch_kernel_m<0, false>(fp64, block);
-        case 1: return ns ? batch_kernel_m<1, true>(fp64, block) : batch_kernel_m<1, false>(fp64, block);
-        case 2: return ns ? batch_kernel_m<2, true>(fp64, block) : batch_kernel_m<2, false>(fp64, block);
-        default: return ns ? batch_kernel_m<3, true>(fp64, block) : batch_kernel_m<3, false>(fp64, block);
+        case 0: return batch_kernel_k<0>(fp64, ns, vol, block);
+        case 1: return batch_kernel_k<1>(fp64, ns, vol, block);
+        case 2: return batch_kernel_k<2>(fp64, ns, vol, block);
+        default: return batch_kernel_k<3>(fp64, ns, vol, block);
     }
 }
 
-hipError_t batch_occupancy(int mode, int fp64, int ns, uint32_t block, uint32_t lds_bytes, int *blocks_per_cu) {
+hipError_t batch_occupancy(int mode, int fp64, int ns, int vol, uint32_t block, uint32_t lds_bytes,
+                           int *blocks_per_cu) {
     if (block != 256u && block != 512u) return hipErrorInvalidConfiguration;
-    const void *f = batch_kernel(mode, fp64, ns, block);
+    const void *f = batch_kernel(mode, fp64, ns, vol, block);
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, f, (int)block, (size_t)lds_bytes);
-}
-
-hipError_t get_batch_attributes(int mode, int fp64, int ns, uint32_t block, hipFuncAttributes *attr) {
-    return hipFuncGetAttributes(attr, batch_kernel(mode, fp64, ns, block));
 }
 
 static hipError_t set_feature_kernel_attrs() {

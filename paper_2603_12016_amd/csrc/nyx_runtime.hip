@@ -805,17 +805,6 @@ Config default_config(const std::vector<Config> &cands, const Work &w, uint32_t 
     return best ? *best : cands.front();
 }
 
-// A configuration whose LDS leaves room for one 256-thread work-group per CU
-// runs with 512 threads instead when its layout (a scan buffer and a set of
-// marginals per reducing wave) still fits: eight waves then share the CU's
-// latency instead of four.
-Config widen_block(const Config &c, uint32_t ng, int K) {
-    if (c.block != 256u || groups_per_cu(make_layout(c, ng, K, false).bytes) != 1u) return c;
-    Config w = c;
-    w.block = 512u;
-    return make_layout(w, ng, K, false).bytes <= kLdsBudget ? w : c;
-}
-
 nyx_status choose_config(nyx_ctx *ctx, const Work &w, uint32_t ng, int K, int force_split, uint32_t block,
                          Config &cfg, bool nonsym = false) {
     std::vector<Config> c = candidate_configs(ctx, w, ng, K, force_split, block, false, 1u, 1.f, nonsym);
@@ -868,8 +857,51 @@ bool sweep_table(const std::vector<ImgDesc> &imgs, const nyx_offset *off, int K,
     return true;
 }
 
+// 3D row-sweep eligibility: every offset of each pass a distance-1 offset,
+// each of the 13 neighbour classes at most once per pass.
+bool sweep3_table(const nyx_offset *off, int K, uint32_t kp, uint64_t *sweep, int max_passes) {
+    memset(sweep, 0, sizeof(uint64_t) * max_passes);
+    int pass = 0;
+    for (int d0 = 0; d0 < K; d0 += (int)kp, ++pass) {
+        if (pass >= max_passes) return false;
+        for (int d = d0; d < std::min(K, d0 + (int)kp); ++d) {
+            const nyx_offset &o = off[d];
+            if (abs(o.dz) > 1 || abs(o.dy) > 1 || abs(o.dx) > 1) return false;
+            const int at = 4 * class3d(o.dz, o.dy, o.dx);
+            if (sweep[pass] >> at & 15u) return false;   // the same class twice in a pass
+            sweep[pass] |= (uint64_t)(d - d0 + 1) << at;
+        }
+    }
+    return true;
+}
+
 void set_sweep(StepArgs &a, const std::vector<ImgDesc> &imgs, const nyx_offset *off, int K, uint32_t kp) {
     a.sweep_ok = sweep_table(imgs, off, K, kp, a.sweep, kMaxSweepPasses) ? 1 : 0;
+    a.sweep3_ok = !a.sweep_ok && sweep3_table(off, K, kp, a.sweep3, kMaxSweepPasses) ? 1 : 0;
+}
+
+// A configuration whose LDS leaves room for one 256-thread work-group per CU
+// runs with 512 threads instead when its layout (a scan buffer and a set of
+// marginals per reducing wave) still fits: eight waves then share the CU's
+// latency instead of four.  The 3D row sweep (vol) has no barrier inside its
+// accumulation, so it takes 512 threads wherever they leave the number of
+// work-groups on a CU alone, up to the two its registers allow (500 ellipsoids
+// at 64 levels and 13 offsets: batch kernel 669 us with 256, 413 with 512).
+Config widen_block(const Config &c, uint32_t ng, int K, bool vol) {
+    if (c.block != 256u) return c;
+    const uint32_t groups = groups_per_cu(make_layout(c, ng, K, false).bytes);
+    if (groups > (vol ? 2u : 1u)) return c;
+    Config w = c;
+    w.block = 512u;
+    const uint32_t bytes = make_layout(w, ng, K, false).bytes;
+    return bytes <= kLdsBudget && groups_per_cu(bytes) == groups ? w : c;
+}
+
+// Whether the 3D row sweep accumulates a configuration's passes.
+bool takes_sweep3(const Work &w, const Config &c, const nyx_offset *off, int K) {
+    StepArgs t;
+    set_sweep(t, w.h_imgs, off, K, c.kp);
+    return !c.nonsym && t.sweep3_ok;
 }
 
 // Allocates queue, split matrices and fills the step arguments.
@@ -940,9 +972,9 @@ nyx_status setup_step(nyx_ctx *ctx, Work &w, const Config &cfg, const nyx_offset
     a.enqueue = 1;
     a.fp64 = fp64;
     // ordered counts take the gather accumulation (no sweep, no staged ring)
-    if (cfg.nonsym) a.sweep_ok = 0;
+    if (cfg.nonsym) a.sweep_ok = a.sweep3_ok = 0;
     else set_sweep(a, w.h_imgs, off, K, cfg.kp);
-    a.lds = make_layout(cfg, ng, K, !a.sweep_ok);
+    a.lds = make_layout(cfg, ng, K, !a.sweep_ok && !a.sweep3_ok);
     return NYX_OK;
 }
 
@@ -1028,7 +1060,8 @@ nyx_status configure(nyx_plan *p, const Config &cfg, const nyx_extract_opts *opt
                     kLdsBudget);
     p->block = cfg.block;
     int occ = 0;
-    HIPC(ctx, batch_occupancy(cfg.mode, p->prec == NYX_FP64, cfg.nonsym, cfg.block, p->w.args.lds.bytes, &occ));
+    HIPC(ctx, batch_occupancy(cfg.mode, p->prec == NYX_FP64, cfg.nonsym, p->w.args.sweep3_ok, cfg.block,
+                              p->w.args.lds.bytes, &occ));
     p->grid = (uint32_t)ctx->n_cu * (uint32_t)std::max(occ, 1);
     uint64_t items;
     uint32_t n_split;
@@ -1180,13 +1213,7 @@ nyx_status nyx_glcm_accumulate(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_im
     if ((s = setup_step(ctx, w, cfg, offsets, K, ng, 0, batch, 0, nullptr)) != NYX_OK) return s;
     StepArgs &a = w.args;
     set_outputs(ctx, a, nullptr, nullptr, 0);
-    int occ = 0;
-    {
-        hipFuncAttributes fa;
-        HIPC(ctx, get_batch_attributes(a.lds.mode, 0, a.nonsym, cfg.block, &fa));
-        occ = 1;
-    }
-    const uint32_t grid = (uint32_t)ctx->n_cu * (uint32_t)std::max(occ, 1) * 2u;
+    const uint32_t grid = (uint32_t)ctx->n_cu * 2u;
     DevBuf dcount, doff;
     dcount.arena = doff.arena = &ctx->pool;
     HIPC(ctx, dcount.alloc((size_t)batch * K * 8u));
@@ -1422,7 +1449,7 @@ nyx_status plan_init(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_images, cons
             if (c.mode == opts->accum_mode) { cfg = c; found = true; break; }
         if (!found) return fail(ctx, NYX_ERR_UNSUPPORTED, "accumulation mode %d does not fit this workload", opts->accum_mode);
     }
-    cfg = widen_block(cfg, (uint32_t)p->ng, p->K);
+    cfg = widen_block(cfg, (uint32_t)p->ng, p->K, takes_sweep3(p->w, cfg, opts->offsets_host, p->K));
     return NYX_OK;
 }
 
@@ -1480,7 +1507,8 @@ nyx_status nyx_plan_create(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_images
         // and the work-group size: 512 threads where 256 leave one group per CU
         const size_t n256 = cands.size();
         for (size_t i = 0; i < n256; ++i) {
-            const Config c = widen_block(cands[i], (uint32_t)p->ng, p->K);
+            const Config c = widen_block(cands[i], (uint32_t)p->ng, p->K,
+                                         takes_sweep3(p->w, cands[i], opts->offsets_host, p->K));
             if (c.block != cands[i].block) cands.push_back(c);
         }
     }

@@ -198,7 +198,19 @@ struct StepArgs {
     // of the H, V, D45, D135 neighbour classes (-1 = absent)
     int32_t sweep_ok;
     int8_t sweep[kMaxSweepPasses][4];
+    // 3D distance-1 row sweep: per pass, 1 + the local direction slot of each
+    // of the 13 forward neighbours (class3d) in four bits each, 0 = absent
+    int32_t sweep3_ok;
+    uint64_t sweep3[kMaxSweepPasses];
 };
+
+// Class 0..12 of a distance-1 offset up to sign: with the sign that points
+// forward in raster order, dz 9 + dy 3 + dx numbers (0, 0, 1) as 1 to
+// (1, 1, 1) as 13.
+inline int class3d(int dz, int dy, int dx) {
+    const int c = dz * 9 + dy * 3 + dx;
+    return (c < 0 ? -c : c) - 1;
+}
 
 // Deterministic split rule shared by host planning and device enqueueing:
 // a ROI above split_vox voxels is cut into about n / tile_vox tiles, first

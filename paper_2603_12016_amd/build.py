@@ -13,7 +13,7 @@ MICRO_SOURCES = ["csrc/nyx_micro.hip"]
 MICRO_LIB = os.path.join(HERE, "libnyx_micro.so")
 
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # no packed-FP32 instructions in generated code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
@@ -27,15 +27,29 @@ def hipcc() -> str:
 
 
 def _compile(sources, lib, verbose):
+    """One hipcc per source, side by side, then the link."""
     tmp = lib + ".tmp%d" % os.getpid()
-    cmd = [hipcc(), *HIPCC_FLAGS, "-I" + os.path.join(HERE, "csrc"), "-I" + os.path.join(ROOT, "include"),
-           "-o", tmp, *[os.path.join(HERE, s) for s in sources]]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
-    os.replace(tmp, lib)
+    include = ["-I" + os.path.join(HERE, "csrc"), "-I" + os.path.join(ROOT, "include")]
+    objects, jobs = [], []
+    try:
+        for s in sources:
+            obj = "%s.%s.o" % (tmp, os.path.basename(s))
+            cmd = [hipcc(), *HIPCC_FLAGS, *include, "-c", "-o", obj, os.path.join(HERE, s)]
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            objects.append(obj)
+            jobs.append(subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))
+        output = [j.communicate()[0] for j in jobs]
+        if any(j.returncode for j in jobs):
+            raise RuntimeError("hipcc failed:\n" + "".join(output))
+        res = subprocess.run([hipcc(), *HIPCC_FLAGS, "-shared", "-o", tmp, *objects], capture_output=True, text=True)
+        if res.returncode != 0:
+            raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
+        os.replace(tmp, lib)
+    finally:
+        for obj in objects:
+            if os.path.exists(obj):
+                os.remove(obj)
     return lib
 
 

@@ -291,6 +291,26 @@ struct SrcDenseList {
     }
 };
 
+// Packed hash table of one direction: n slots of key | count (0: free).
+struct SrcPacked {
+    uint32_t *T;
+    uint32_t n;
+    uint32_t lvl_bits, cnt_bits;
+    template <class Grp, class Fn>
+    __device__ __forceinline__ void for_each(const Grp &g, Fn &&fn) const {
+        const uint32_t lm = (1u << lvl_bits) - 1u, cm = (1u << cnt_bits) - 1u;
+        for (uint32_t e = g.rank(); e < n; e += g.size()) {
+            const uint32_t w = T[e];
+            if (w) fn((w >> cnt_bits) & lm, w >> (cnt_bits + lvl_bits), w & cm);
+        }
+    }
+    template <class Grp>
+    __device__ __forceinline__ void clear(const Grp &g) const {
+        for (uint32_t e = 4u * g.rank(); e < n; e += 4u * g.size())   // (n is a multiple of 4)
+            *reinterpret_cast<uint4 *>(T + e) = make_uint4(0u, 0u, 0u, 0u);
+    }
+};
+
 // LDS hash slots listed per direction.
 struct SrcHashList {
     const uint32_t *list;
@@ -491,8 +511,40 @@ template <> __device__ __forceinline__ double mi_resum_threshold<double>() { ret
 constexpr uint32_t kWideLevels = 256u;
 template <class Src> struct is_tri_scan : std::false_type {};
 template <bool P> struct is_tri_scan<SrcTriScan<P>> : std::true_type {};
-template <uint32_t U, class Fn>
-__device__ __forceinline__ void level_sweep(uint32_t r0, uint32_t gs, uint32_t n, const uint32_t *a, Fn &&fn) {
+// Marginals of one matrix, zeroed u32 LDS words: counters of 32 bits, or of
+// 16 bits two to a word (HALF: every marginal of the item stays below 2^16).
+template <bool HALF> struct Marg;
+template <> struct Marg<false> {
+    uint32_t *w;
+    __device__ __forceinline__ explicit Marg(uint32_t *w_) : w(w_) {}
+    __device__ __forceinline__ Marg at(uint32_t i) const { return Marg(w + i); }
+    __device__ __forceinline__ void add(uint32_t i, uint32_t v) const { atomicAdd(&w[i], v); }
+    __device__ __forceinline__ uint32_t operator[](uint32_t i) const { return w[i]; }
+    // zeroes the first n counters
+    template <class Grp> __device__ __forceinline__ void clear(const Grp &g, uint32_t n) const {
+        for (uint32_t i = (uint32_t)g.rank(); i < n; i += (uint32_t)g.size()) w[i] = 0u;
+    }
+};
+template <> struct Marg<true> {
+    uint32_t *w;
+    uint32_t off;            // first counter
+    __device__ __forceinline__ explicit Marg(uint32_t *w_, uint32_t off_ = 0u) : w(w_), off(off_) {}
+    __device__ __forceinline__ Marg at(uint32_t i) const { return Marg(w, off + i); }
+    __device__ __forceinline__ void add(uint32_t i, uint32_t v) const {
+        i += off;
+        atomicAdd(&w[i >> 1], v << ((i & 1u) << 4));
+    }
+    __device__ __forceinline__ uint32_t operator[](uint32_t i) const {
+        return (uint32_t)reinterpret_cast<const uint16_t *>(w)[off + i];
+    }
+    // zeroes the first n counters of the whole set (off 0)
+    template <class Grp> __device__ __forceinline__ void clear(const Grp &g, uint32_t n) const {
+        for (uint32_t i = (uint32_t)g.rank(); i < (n + 1u) >> 1; i += (uint32_t)g.size()) w[i] = 0u;
+    }
+};
+
+template <uint32_t U, class M, class Fn>
+__device__ __forceinline__ void level_sweep(uint32_t r0, uint32_t gs, uint32_t n, const M &a, Fn &&fn) {
     for (uint32_t i0 = r0; i0 < n; i0 += U * gs) {
         uint32_t v[U];
 #pragma unroll
@@ -501,9 +553,8 @@ __device__ __forceinline__ void level_sweep(uint32_t r0, uint32_t gs, uint32_t n
         for (uint32_t u = 0; u < U; ++u) fn(i0 + u * gs, v[u]);
     }
 }
-template <uint32_t U, class Fn>
-__device__ __forceinline__ void level_sweep(uint32_t r0, uint32_t gs, uint32_t n, const uint32_t *a,
-                                            const uint32_t *b, Fn &&fn) {
+template <uint32_t U, class M, class Fn>
+__device__ __forceinline__ void level_sweep(uint32_t r0, uint32_t gs, uint32_t n, const M &a, const M &b, Fn &&fn) {
     for (uint32_t i0 = r0; i0 < n; i0 += U * gs) {
         uint32_t v[U], w[U];
 #pragma unroll
@@ -517,16 +568,16 @@ __device__ __forceinline__ void level_sweep(uint32_t r0, uint32_t gs, uint32_t n
     }
 }
 
-// Reduced sums of one direction.  R, Sp, Sm are zeroed LDS arrays of ng,
-// 2 ng - 1 and ng u32 (row, sum and difference marginals of the symmetric
-// matrix); they are zeroed again on return, and the source is cleared.
+// Reduced sums of one direction.  marg: room for 4 ng - 1 zeroed counters
+// (row, sum and difference marginals of the symmetric matrix: ng, 2 ng - 1
+// and ng); they are zeroed again on return, and the source is cleared.
 // *out (LDS or global) is written by the group.  ISum is the type of the
 // per-lane integer sums: double where every partial and total stays below
 // 2^53 (small work items; required by the batched reduction), uint64_t
 // otherwise.  Returns T (0: direction empty).
-template <class Acc, class ISum, class Grp, class Src>
-__device__ uint64_t dir_sums(const Grp &g, const Src &src, uint32_t *R, uint32_t *Sp, uint32_t *Sm,
-                             uint32_t ng, DirSums *out) {
+template <class Acc, class ISum, class Grp, class Src, bool H>
+__device__ uint64_t dir_sums(const Grp &g, const Src &src, const Marg<H> &marg, uint32_t ng, DirSums *out) {
+    const Marg<H> R = marg, Sp = marg.at(ng), Sm = marg.at(3u * ng - 1u);
     static_assert(!Grp::kBatched || std::is_same<ISum, double>::value, "batched sums are exact doubles");
     const int r0 = g.rank(), gs = g.size();
     // One sweep over the nonzero cells: marginals and cell terms.  A cell
@@ -536,10 +587,10 @@ __device__ uint64_t dir_sums(const Grp &g, const Src &src, uint32_t *R, uint32_t
     uint32_t maxP = 0;
     LaneSum<Acc> plp;
     src.for_each(g, [&](uint32_t lo, uint32_t hi, uint32_t c) {
-        atomicAdd(&R[lo], c);
-        atomicAdd(&R[hi], c);
-        atomicAdd(&Sp[lo + hi], 2u * c);
-        atomicAdd(&Sm[hi - lo], 2u * c);
+        R.add(lo, c);
+        R.add(hi, c);
+        Sp.add(lo + hi, 2u * c);
+        Sm.add(hi - lo, 2u * c);
         const bool diag = lo == hi;
         const uint32_t P = diag ? 2u * c : c;
         const ISum Pm = diag ? (ISum)P : (ISum)(2ull * P);    // P summed over both orders
@@ -625,8 +676,7 @@ __device__ uint64_t dir_sums(const Grp &g, const Src &src, uint32_t *R, uint32_t
     if (T == 0) {
         g.sync();
         if (r0 == 0) out->T = 0;
-        for (uint32_t i = r0; i < ng; i += gs) { R[i] = 0u; Sm[i] = 0u; }
-        for (uint32_t k = r0; k < 2u * ng - 1u; k += gs) Sp[k] = 0u;
+        marg.clear(g, 4u * ng - 1u);
         src.clear(g);
         g.sync();
         return 0;
@@ -701,8 +751,7 @@ __device__ uint64_t dir_sums(const Grp &g, const Src &src, uint32_t *R, uint32_t
     }
     // Clean up for the next direction / item.
     g.sync();
-    for (uint32_t i = r0; i < ng; i += gs) { R[i] = 0u; Sm[i] = 0u; }
-    for (uint32_t k = r0; k < 2u * ng - 1u; k += gs) Sp[k] = 0u;
+    marg.clear(g, 4u * ng - 1u);
     src.clear(g);
     g.sync();
     return T;
@@ -710,23 +759,23 @@ __device__ uint64_t dir_sums(const Grp &g, const Src &src, uint32_t *R, uint32_t
 
 // Reduced sums of one direction of a non-symmetric matrix (ordered counts):
 // the source hands cells (a, b, c) with P(a, b) = c, a the level at v and b
-// the level at v + d.  R and Cm are the row and column marginals (ng u32
-// each), Sp and Sm the sum and difference marginals (2 ng - 1 and ng u32),
-// all zeroed LDS arrays that are zeroed again on return; *out and *outy
-// receive the sums (the column-marginal ones in *outy).  Every total is
+// the level at v + d.  marg: room for 5 ng - 1 zeroed counters (row, column,
+// sum and difference marginals: ng, ng, 2 ng - 1 and ng), zeroed again on
+// return; *out and *outy receive the sums (the column-marginal ones in *outy).  Every total is
 // reduced value by value in exact integers or double.  Returns T.
-template <class Acc, class Grp, class Src>
-__device__ uint64_t dir_sums_ns(const Grp &g, const Src &src, uint32_t *R, uint32_t *Cm, uint32_t *Sp, uint32_t *Sm,
-                                uint32_t ng, DirSums *out, DirSumsY *outy) {
+template <class Acc, class Grp, class Src, bool H>
+__device__ uint64_t dir_sums_ns(const Grp &g, const Src &src, const Marg<H> &marg, uint32_t ng, DirSums *out,
+                                DirSumsY *outy) {
+    const Marg<H> R = marg, Cm = marg.at(ng), Sp = marg.at(2u * ng), Sm = marg.at(4u * ng - 1u);
     const int r0 = g.rank(), gs = g.size();
     uint64_t Tl = 0, sumP2 = 0, S11 = 0;
     uint32_t maxP = 0;
     LaneSum<Acc> plp;
     src.for_each(g, [&](uint32_t a, uint32_t b, uint32_t c) {
-        atomicAdd(&R[a], c);
-        atomicAdd(&Cm[b], c);
-        atomicAdd(&Sp[a + b], c);
-        atomicAdd(&Sm[a > b ? a - b : b - a], c);
+        R.add(a, c);
+        Cm.add(b, c);
+        Sp.add(a + b, c);
+        Sm.add(a > b ? a - b : b - a, c);
         Tl += c;
         sumP2 += (uint64_t)c * c;
         maxP = c > maxP ? c : maxP;
@@ -767,13 +816,37 @@ __device__ uint64_t dir_sums_ns(const Grp &g, const Src &src, uint32_t *R, uint3
         const uint32_t sp = Sp[k];
         if (sp) plps.add((Acc)sp * term_log2<Acc>((Acc)sp));
     }
-    const uint64_t T = g.sum(Tl);
-    const uint64_t S1t = g.sum(S1), S2t = g.sum(S2), S1yt = g.sum(S1y), S2yt = g.sum(S2y), Sm1t = g.sum(Sm1);
-    const uint64_t S11t = g.sum(S11), sumP2t = g.sum(sumP2);
-    const double plp_t = g.sum(comp_value(plp)), rlr_t = g.sum(comp_value(rlr)), clc_t = g.sum(comp_value(clc));
-    const double slp_t = g.sum(comp_value(slp)), plps_t = g.sum(comp_value(plps));
-    const double hom1_t = g.sum(comp_value(hom1)), hom2_t = g.sum(comp_value(hom2));
-    const double idmn_t = g.sum(comp_value(idmn)), idn_t = g.sum(comp_value(idn)), iv_t = g.sum(comp_value(iv));
+    // Group totals: batched groups (items of at most 2^20 voxels, so every
+    // integer total is an exact double) reduce the fifteen shared slots and
+    // the three column-marginal sums in two batches; the others value by value.
+    uint64_t T, S1t, S1yt;
+    double slot = 0.0, rest = 0.0, plp_t, rlr_t, clc_t;
+    uint64_t tot_u[8];
+    double tot_d[7];
+    if constexpr (Grp::kBatched) {
+        double v[kSumSlots] = {(double)Tl, (double)S1, (double)S2, (double)Sm1, (double)S11, (double)sumP2,
+                               comp_value(plp), comp_value(rlr), comp_value(slp), comp_value(plps),
+                               comp_value(hom1), comp_value(hom2), comp_value(idmn), comp_value(idn),
+                               comp_value(iv), comp_value(clc)};
+        slot = g.reduce_slots(v);
+        rest = g.reduce_pair((double)S1y, (double)S2y);
+        T = (uint64_t)g.bcast(slot, 0);
+        S1t = (uint64_t)g.bcast(slot, 1);
+        S1yt = (uint64_t)g.bcast(rest, 0);
+        plp_t = g.bcast(slot, 6);
+        rlr_t = g.bcast(slot, 7);
+        clc_t = g.bcast(slot, 15);
+    } else {
+        tot_u[0] = g.sum(Tl); tot_u[1] = g.sum(S1); tot_u[2] = g.sum(S2); tot_u[3] = g.sum(Sm1);
+        tot_u[4] = g.sum(S11); tot_u[5] = g.sum(sumP2); tot_u[6] = g.sum(S1y); tot_u[7] = g.sum(S2y);
+        plp_t = g.sum(comp_value(plp)); rlr_t = g.sum(comp_value(rlr)); clc_t = g.sum(comp_value(clc));
+        tot_d[0] = g.sum(comp_value(slp)); tot_d[1] = g.sum(comp_value(plps)); tot_d[2] = g.sum(comp_value(hom1));
+        tot_d[3] = g.sum(comp_value(hom2)); tot_d[4] = g.sum(comp_value(idmn)); tot_d[5] = g.sum(comp_value(idn));
+        tot_d[6] = g.sum(comp_value(iv));
+        T = tot_u[0];
+        S1t = tot_u[1];
+        S1yt = tot_u[6];
+    }
     const uint32_t maxPt = g.max(maxP);
     double CSHADE = 0.0, CPROM = 0.0, MI = __builtin_nan("");
     if (T) {
@@ -791,8 +864,14 @@ __device__ uint64_t dir_sums_ns(const Grp &g, const Src &src, uint32_t *R, uint3
                 cp += d3 * d * p;
             }
         }
-        CSHADE = g.sum(cs);
-        CPROM = g.sum(cp);
+        if constexpr (Grp::kBatched) {
+            const double pr = g.reduce_pair(cs, cp);
+            CSHADE = g.bcast(pr, 0);
+            CPROM = g.bcast(pr, 8);
+        } else {
+            CSHADE = g.sum(cs);
+            CPROM = g.sum(cp);
+        }
         // mutual information HX + HY - HXY, re-summed cell by cell when the
         // closed form would lose the digits the information measures need
         const double mi_cf = (double)__log2f((float)Td) - (rlr_t + clc_t - plp_t) * invT;
@@ -808,20 +887,26 @@ __device__ uint64_t dir_sums_ns(const Grp &g, const Src &src, uint32_t *R, uint3
             MI = g.sum(comp_value(m));
         }
     }
+    if constexpr (Grp::kBatched) {
+        if (r0 < kSumSlots - 1)
+            reinterpret_cast<uint64_t *>(out)[r0] = r0 < 6 ? (uint64_t)slot : __builtin_bit_cast(uint64_t, slot);
+        const double S2yt = g.bcast(rest, 8);
+        if (r0 == 0) { outy->S1y = S1yt; outy->S2y = (uint64_t)S2yt; outy->clc = clc_t; outy->spare = 0.0; }
+    } else if (r0 == 0) {
+        out->T = T; out->S1 = S1t; out->S2 = tot_u[2]; out->Sm1 = tot_u[3]; out->S11 = tot_u[4]; out->sumP2 = tot_u[5];
+        out->plp = plp_t; out->rlr = rlr_t; out->slp = tot_d[0]; out->plps = tot_d[1];
+        out->hom1 = tot_d[2]; out->hom2 = tot_d[3]; out->idmn = tot_d[4]; out->idn = tot_d[5]; out->iv = tot_d[6];
+        outy->S1y = S1yt; outy->S2y = tot_u[7]; outy->clc = clc_t; outy->spare = 0.0;
+    }
     if (r0 == 0) {
-        out->T = T; out->S1 = S1t; out->S2 = S2t; out->Sm1 = Sm1t; out->S11 = S11t; out->sumP2 = sumP2t;
-        out->plp = plp_t; out->rlr = rlr_t; out->slp = slp_t; out->plps = plps_t;
-        out->hom1 = hom1_t; out->hom2 = hom2_t; out->idmn = idmn_t; out->idn = idn_t; out->iv = iv_t;
         out->spare = 0.0;
         out->maxP = maxPt;
         out->CSHADE = CSHADE;
         out->CPROM = CPROM;
         out->MI = MI;
-        outy->S1y = S1yt; outy->S2y = S2yt; outy->clc = clc_t; outy->spare = 0.0;
     }
     g.sync();
-    for (uint32_t i = r0; i < ng; i += gs) { R[i] = 0u; Cm[i] = 0u; Sm[i] = 0u; }
-    for (uint32_t k = r0; k < 2u * ng - 1u; k += gs) Sp[k] = 0u;
+    marg.clear(g, 5u * ng - 1u);
     src.clear(g);
     g.sync();
     return T;

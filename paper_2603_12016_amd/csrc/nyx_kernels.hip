@@ -425,7 +425,7 @@ __global__ __launch_bounds__(1024) void k_compact_write(StepArgs a, uint32_t roi
     a.rois[row] = rd;
     if (take && !band && (rd.gslot != kNone || nt == 1u)) {
         enq = true;
-        cls = size_class((rd.n + nt - 1u) / nt);
+        cls = size_class(item_bound(rd.n, rd.rows, (uint32_t)(rd.x1 - rd.x0 + 1), tl));
         local = atomicAdd(&cls_cnt[cls], nt);
     }
     write_roi(a, row, rd);
@@ -615,10 +615,10 @@ __device__ __forceinline__ uint32_t half_index(uint32_t i) {
 // Add one level pair (1-based la, lb, with their row offsets ta, tb) to
 // local direction dl: unordered into the triangle (SQ false), or ordered
 // (la at v, lb at v + d) into the square of ordered counts (SQ true; ta from
-// SqOff, hash keys keep the order).
+// SqOff, hash keys keep the order).  slots: packed table slots of the item.
 template <int MODE, bool SQ = false>
 __device__ __forceinline__ void add_pair(const StepArgs &a, uint8_t *smem, uint32_t dl, uint32_t la, uint32_t ta,
-                                         uint32_t lb, uint32_t tb) {
+                                         uint32_t lb, uint32_t tb, uint32_t slots = 0u) {
     const LdsLayout &Ly = a.lds;
     uint32_t lo = (SQ || la < lb ? la : lb) - 1u, hi = (SQ || la < lb ? lb : la) - 1u;
     uint32_t *LCNT = reinterpret_cast<uint32_t *>(smem + Ly.lcnt_off);
@@ -652,6 +652,47 @@ __device__ __forceinline__ void add_pair(const StepArgs &a, uint8_t *smem, uint3
                 if (pos < Ly.list_cap) LST[pos] = lo | (hi << 16);
                 else atomicOr(&a.counters[C_ERR], (uint32_t)E_LIST_CAP);
             }
+        }
+    } else if (MODE == 4) {
+        // Packed table of direction dl: one word per slot, key above count, 0
+        // free, in buckets of four that one 16-byte read shows: a slot that
+        // holds the key takes a plain add, else the first free one is claimed
+        // by compare-and-swap, else the next bucket is probed.  (Slot by slot,
+        // a wavefront waited for its longest of 64 probe chains.)  Bound by
+        // the two LDS round trips a pair and the 16 waves a CU's tables leave:
+        // 2000 cells at 256 levels 470 us as a list of first touches in dense
+        // triangles, 212 here; a 1024-level image (67 M voxels in 10000 small
+        // regions and one band) 600 in 64-bit slots, 330 here.
+        uint32_t *T = reinterpret_cast<uint32_t *>(smem + Ly.u_off) + __umul24(dl, Ly.hash_cap);
+        const uint32_t key = (hi << Ly.lvl_bits) | lo, base = key << Ly.cnt_bits, buckets = slots >> 2;
+        uint32_t b = packed_bucket(key, buckets);
+        for (uint32_t probe = 0;;) {
+            typedef uint32_t Bucket __attribute__((ext_vector_type(4)));
+            const Bucket v = *(const volatile __attribute__((address_space(3))) Bucket *)(T + 4u * b);
+            // an occupied slot holds the key where it differs from `base` in the count alone
+            const uint32_t cm = 1u << Ly.cnt_bits;
+            const bool m0 = v.x - base - 1u < cm - 1u, m1 = v.y - base - 1u < cm - 1u, m2 = v.z - base - 1u < cm - 1u,
+                       m3 = v.w - base - 1u < cm - 1u;
+            uint32_t j = m0 ? 0u : (m1 ? 1u : (m2 ? 2u : 3u));
+            if (m0 | m1 | m2 | m3) {
+                __hip_atomic_fetch_add(&T[4u * b + j], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                break;
+            }
+            if (v.x == 0u || v.y == 0u || v.z == 0u || v.w == 0u) {
+                j = v.x == 0u ? 0u : (v.y == 0u ? 1u : (v.z == 0u ? 2u : 3u));
+                const uint32_t old = atomicCAS(&T[4u * b + j], 0u, base + 1u);
+                if (old == 0u) break;
+                if (old - base - 1u < cm - 1u) {
+                    __hip_atomic_fetch_add(&T[4u * b + j], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    break;
+                }
+                continue;   // another key took the slot: the bucket again
+            }
+            if (++probe == buckets) {   // (more pairs than the item's bound: a plan run on other images)
+                atomicOr(&a.counters[C_ERR], (uint32_t)E_HASH_FULL);
+                break;
+            }
+            if (++b == buckets) b = 0u;
         }
     } else {
         uint32_t *HK = reinterpret_cast<uint32_t *>(smem + Ly.hkey_off);
@@ -1157,7 +1198,7 @@ __device__ __forceinline__ void accumulate_sweep3d(const RoiDesc &rd, const Item
 
 // One direction of a finished item: features (unsplit ROI) or a 64-bit
 // atomic merge into the ROI's global matrix (tile of a split ROI).
-template <class Acc, bool NS, class Src>
+template <class Acc, bool NS, bool H = false, class Src>
 __device__ __forceinline__ void dir_or_flush(const StepArgs &a, const WaveGrp &g, const Src &s, bool split,
                                              const RoiDesc &rd, uint32_t roi, int d, uint32_t *MARG, uint32_t ng) {
     if (split) {
@@ -1171,9 +1212,9 @@ __device__ __forceinline__ void dir_or_flush(const StepArgs &a, const WaveGrp &g
     } else if constexpr (NS) {
         // marginals: row, column, sum, difference
         const uint64_t at = (uint64_t)roi * a.K_out + d;
-        dir_sums_ns<Acc>(g, s, MARG, MARG + ng, MARG + 2u * ng, MARG + 4u * ng - 1u, ng, a.dsums + at, a.dsums_y + at);
+        dir_sums_ns<Acc>(g, s, Marg<H>(MARG), ng, a.dsums + at, a.dsums_y + at);
     } else {
-        dir_sums<Acc, double>(g, s, MARG, MARG + ng, MARG + 3u * ng - 1u, ng, a.dsums + (uint64_t)roi * a.K_out + d);
+        dir_sums<Acc, double>(g, s, Marg<H>(MARG), ng, a.dsums + (uint64_t)roi * a.K_out + d);
     }
 }
 
@@ -1203,13 +1244,15 @@ __global__ __launch_bounds__(BS, VOL ? 4 : ((BS == 256 && sizeof(OutT) == 4) ? 5
     const int K = a.K;
     const uint32_t ng = (uint32_t)a.ng;
     constexpr bool ns = NS;   // ordered counts: squares, gather accumulation, four marginals
-    const uint32_t marg_words = (ns ? 5u : 4u) * ng;
+    constexpr bool half = MODE == 4;   // marginals of 16 bits (items are small)
+    const uint32_t marg_words = half ? ((ns ? 5u : 4u) * ng + 1u) >> 1 : (ns ? 5u : 4u) * ng;
     uint32_t *MARG = reinterpret_cast<uint32_t *>(smem + Ly.marg_off) + w * marg_words;
 
     // LDS starts clean and every item leaves it clean.
     if (MODE != 1) {
         uint32_t *U = reinterpret_cast<uint32_t *>(smem + Ly.u_off);
-        for (uint32_t i = threadIdx.x; i < Ly.n_tri * Ly.copies * Ly.tri_pad; i += blockDim.x) U[i] = 0u;
+        const uint32_t words = MODE == 4 ? Ly.n_tri * Ly.hash_cap : Ly.n_tri * Ly.copies * Ly.tri_pad;
+        for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) U[i] = 0u;
     } else {
         uint32_t *HK = reinterpret_cast<uint32_t *>(smem + Ly.hkey_off);
         uint32_t *HC = reinterpret_cast<uint32_t *>(smem + Ly.hcnt_off);
@@ -1222,7 +1265,7 @@ __global__ __launch_bounds__(BS, VOL ? 4 : ((BS == 256 && sizeof(OutT) == 4) ? 5
     if ((MODE == 2 || MODE == 3) && !NS)
         for (uint32_t x = threadIdx.x; x <= ng; x += blockDim.x)
             reinterpret_cast<uint32_t *>(smem + Ly.ro_off)[x] = x ? row_off(x) : 0u;
-    if (direct_roi == kNone) ticket_load(MISC, a.counters + C_CLASS, a.bucket_cap, threadIdx.x);
+    if (direct_roi == kNone) ticket_load(MISC, a.counters + C_CLASS, a.bucket_cap, threadIdx.x, a.cls_lo, a.cls_hi);
     __syncthreads();
     if (threadIdx.x == 0 && direct_roi == kNone) ticket_prefix(MISC);
     __syncthreads();
@@ -1239,7 +1282,7 @@ __global__ __launch_bounds__(BS, VOL ? 4 : ((BS == 256 && sizeof(OutT) == 4) ? 5
             } else {
                 // (every lane has a work-group: a grid below kTicketLanes uses fewer)
                 const uint32_t lanes = min(kTicketLanes, gridDim.x), tl = blockIdx.x % lanes;
-                n = ticket_claim(MISC, &a.counters[C_TICKETS + tl * kTicketStride], tl, lanes, a.buckets,
+                n = ticket_claim(MISC, &a.counters[a.tickets + tl * kTicketStride], tl, lanes, a.buckets,
                                  a.bucket_cap);
             }
             MISC[32] = n;
@@ -1263,25 +1306,58 @@ __global__ __launch_bounds__(BS, VOL ? 4 : ((BS == 256 && sizeof(OutT) == 4) ? 5
             c.label = rd.label; c.vmin = rd.vmin; c.ng = ng;
             c.rcp = it.rcp;
             c.err = &a.counters[C_ERR];
-            const uint32_t ra = it.ra, rb = it.rb, ca = it.ca, cb = it.cb;
             const bool split = rd.gslot != kNone;
+            uint32_t ra = it.ra, rb = it.rb, ca = it.ca, cb = it.cb;
+            // packed hash: a tile that may hold more voxels than a table (of
+            // a plan whose images now hold other regions) is counted and
+            // flushed in parts
+            uint32_t part_rows = rb - ra, part_cols = cb - ca;
+            if constexpr (MODE == 4) {
+                const uint32_t most = split ? min(rd.n, part_rows * part_cols) : rd.n;
+                if (most > Ly.item_max) {
+                    if (!split) {
+                        if (threadIdx.x == 0) atomicOr(&a.counters[C_ERR], (uint32_t)E_HASH_FULL);
+                        continue;
+                    }
+                    part_cols = min(part_cols, Ly.item_max);
+                    part_rows = max(1u, Ly.item_max / part_cols);
+                }
+            }
+            for (bool more = true; more;) {
+            uint32_t slots = 0u;   // packed hash: those this part uses (pairs of a direction are at most its voxels)
+            if constexpr (MODE == 4) {
+                rb = min(it.rb, ra + part_rows);
+                cb = min(it.cb, ca + part_cols);
+                slots = packed_slots(split ? min(rd.n, (rb - ra) * (cb - ca)) : rd.n, Ly.hash_cap);
+            }
             for (int d0 = 0, pass = 0; d0 < K; d0 += (int)Ly.kp, ++pass) {
                 const int d1 = min(K, d0 + (int)Ly.kp);
                 if constexpr (NS) {
-                    // ordered pairs (level at v, level at v + d) by gather, into squares
+                    // ordered pairs (level at v, level at v + d), into squares
                     if (MODE != 0 && ra < rb && ca < cb) {
-                        const bool merged = MODE >= 2 && a.merged;
+                        const bool merged = (MODE == 2 || MODE == 3) && a.merged;
                         auto add = [&](uint32_t dl, uint32_t la, uint32_t ta, uint32_t lb, uint32_t tb) NYX_INLINE {
-                            add_pair<MODE, true>(a, smem, merged ? 0u : dl, la, ta, lb, tb);
+                            add_pair<MODE, true>(a, smem, merged ? 0u : dl, la, ta, lb, tb, slots);
                         };
-                        accumulate_rows(a, rd, c, ra, rb, ca, cb, d0, d1, threadIdx.x, blockDim.x, add, SqOff{ng});
+                        if (a.sweep_ok && pass < kMaxSweepPasses && !c.B) {
+                            // the row sweep hands out a pair in its class's own direction
+                            const uint32_t flip = a.sweep_flip[pass];
+                            const int8_t *sw = a.sweep[pass];
+                            auto turn = [&](uint32_t dl, uint32_t la, uint32_t ta, uint32_t lb, uint32_t tb) NYX_INLINE {
+                                if (flip >> dl & 1u) add(dl, lb, tb, la, ta);
+                                else add(dl, la, ta, lb, tb);
+                            };
+                            accumulate_sweep2d<false>(rd, c, ra, rb, ca, cb, sw[0], sw[1], sw[2], sw[3], w, nw,
+                                                      SqOff{ng}, turn);
+                        } else
+                            accumulate_rows(a, rd, c, ra, rb, ca, cb, d0, d1, threadIdx.x, blockDim.x, add, SqOff{ng});
                     }
                 } else if constexpr (VOL) {
                     // (a caller-supplied bin image takes the gather)
                     if (ra < rb && ca < cb) {
-                        const bool merged = MODE >= 2 && a.merged;
+                        const bool merged = (MODE == 2 || MODE == 3) && a.merged;
                         auto add = [&](uint32_t dl, uint32_t la, uint32_t ta, uint32_t lb, uint32_t tb) NYX_INLINE {
-                            add_pair<MODE>(a, smem, merged ? 0u : dl, la, ta, lb, tb);
+                            add_pair<MODE>(a, smem, merged ? 0u : dl, la, ta, lb, tb, slots);
                         };
                         if (!c.B && pass < kMaxSweepPasses)
                             accumulate_sweep3d(rd, c, ra, rb, ca, cb, a.sweep3[pass], (uint32_t)w, (uint32_t)nw, add);
@@ -1290,9 +1366,9 @@ __global__ __launch_bounds__(BS, VOL ? 4 : ((BS == 256 && sizeof(OutT) == 4) ? 5
                     }
                 } else if (ra < rb && ca < cb) {
                     // merged matrices: every offset counts into the one triangle
-                    const bool merged = MODE >= 2 && a.merged;
+                    const bool merged = (MODE == 2 || MODE == 3) && a.merged;
                     auto add = [&](uint32_t dl, uint32_t la, uint32_t ta, uint32_t lb, uint32_t tb) NYX_INLINE {
-                        add_pair<MODE>(a, smem, merged ? 0u : dl, la, ta, lb, tb);
+                        add_pair<MODE>(a, smem, merged ? 0u : dl, la, ta, lb, tb, slots);
                     };
                     const uint32_t W = (uint32_t)(rd.x1 - rd.x0 + 1), H = (uint32_t)(rd.y1 - rd.y0 + 1);
                     const uint32_t ring_rows = Ly.ring_bytes / W;
@@ -1315,19 +1391,23 @@ __global__ __launch_bounds__(BS, VOL ? 4 : ((BS == 256 && sizeof(OutT) == 4) ? 5
                         accumulate_rows(a, rd, c, ra, rb, ca, cb, d0, d1, threadIdx.x, blockDim.x, add);
                 }
                 __syncthreads();
-                const int n_mat = (MODE >= 2 && a.merged) ? 1 : d1 - d0;
+                const int n_mat = ((MODE == 2 || MODE == 3) && a.merged) ? 1 : d1 - d0;
                 for (int dl = w; dl < n_mat; dl += nw) {
                     uint32_t *Ud = reinterpret_cast<uint32_t *>(smem + Ly.u_off) + dl * Ly.copies * Ly.tri_pad;
-                    const uint32_t n = min(LCNT[dl], Ly.list_cap);
+                    const uint32_t n = MODE == 4 ? 0u : min(LCNT[dl], Ly.list_cap);
                     const uint32_t *lst = LST + dl * Ly.list_cap;
                     WaveGrp g;
-                    if (MODE == 2 || MODE == 3) {
+                    if constexpr (MODE == 4) {
+                        SrcPacked s{reinterpret_cast<uint32_t *>(smem + Ly.u_off) + dl * Ly.hash_cap, slots,
+                                    Ly.lvl_bits, Ly.cnt_bits};
+                        dir_or_flush<Acc, NS, true>(a, g, s, split, rd, roi, d0 + dl, MARG, ng);
+                    } else if constexpr (MODE == 2 || MODE == 3) {
                         SrcTriScan<MODE == 3> s{Ud, ns ? ng * ng : (ng * (ng + 1u)) >> 1,
                                                 reinterpret_cast<uint16_t *>(BUF) +
                                                     (uint32_t)w * scan_buf_entries(SrcTriScan<MODE == 3>::kPerRead),
                                                 Ly.copies, Ly.tri_pad, ns ? ng : 0u};
                         dir_or_flush<Acc, NS>(a, g, s, split, rd, roi, a.merged ? 0 : d0 + dl, MARG, ng);
-                    } else if (MODE == 0) {
+                    } else if constexpr (MODE == 0) {
                         SrcDenseList s{lst, n, Ud};
                         dir_or_flush<Acc, NS>(a, g, s, split, rd, roi, d0 + dl, MARG, ng);
                     } else {
@@ -1335,9 +1415,16 @@ __global__ __launch_bounds__(BS, VOL ? 4 : ((BS == 256 && sizeof(OutT) == 4) ? 5
                                       reinterpret_cast<uint32_t *>(smem + Ly.hcnt_off)};
                         dir_or_flush<Acc, NS>(a, g, s, split, rd, roi, d0 + dl, MARG, ng);
                     }
-                    if (lane() == 0) LCNT[dl] = 0u;
+                    if (MODE != 4 && lane() == 0) LCNT[dl] = 0u;
                 }
                 __syncthreads();
+            }
+            more = false;
+            if constexpr (MODE == 4) {
+                ca = cb;
+                if (ca >= it.cb) { ca = it.ca; ra = rb; }
+                more = ra < it.rb;
+            }
             }
         }
         __syncthreads();
@@ -1465,9 +1552,9 @@ __global__ __launch_bounds__(1024) void k_split_features(StepArgs a) {
     SrcSquare s{a.G + ((uint64_t)slot * K + d) * (uint64_t)ng * ng, ng, a.nonsym != 0};
     const uint64_t at = (uint64_t)roi * K + d;
     if (a.nonsym)
-        dir_sums_ns<Acc>(g, s, R, R + ng, R + 2u * ng, R + 4u * ng - 1u, ng, a.dsums + at, a.dsums_y + at);
+        dir_sums_ns<Acc>(g, s, Marg<false>(R), ng, a.dsums + at, a.dsums_y + at);
     else
-        dir_sums<Acc, uint64_t>(g, s, R, R + ng, R + 3u * ng - 1u, ng, a.dsums + at);
+        dir_sums<Acc, uint64_t>(g, s, Marg<false>(R), ng, a.dsums + at);
 }
 
 // Split ROIs with symmetric matrices, first pass: one work-group per (slot,
@@ -1776,9 +1863,9 @@ __global__ __launch_bounds__(512) void k_coo_features(StepArgs a, const uint64_t
     SrcCoo src{keys + seg[s], vals + seg[s], (uint32_t)(seg[s + 1] - seg[s]),
                ((uint64_t)(s / K) << 38) | ((uint64_t)(s % K) << 32), ng, &a.counters[C_ERR], a.nonsym != 0};
     if (a.nonsym)
-        dir_sums_ns<Acc>(g, src, R, R + ng, R + 2u * ng, R + 4u * ng - 1u, ng, sums + s, sums_y + s);
+        dir_sums_ns<Acc>(g, src, Marg<false>(R), ng, sums + s, sums_y + s);
     else
-        dir_sums<Acc, uint64_t>(g, src, R, R + ng, R + 3u * ng - 1u, ng, sums + s);
+        dir_sums<Acc, uint64_t>(g, src, Marg<false>(R), ng, sums + s);
 }
 
 // ================================================================== launchers
@@ -1921,6 +2008,8 @@ hipError_t launch_batch(const StepArgs &a, uint32_t grid, uint32_t block, uint32
         case 0: return launch_batch_m<0, false>(a, grid, block, direct_roi, st);
         case 1: return ns ? launch_batch_m<1, true>(a, grid, block, direct_roi, st)
                           : launch_batch_m<1, false>(a, grid, block, direct_roi, st);
+        case 4: return ns ? launch_batch_m<4, true>(a, grid, block, direct_roi, st)
+                          : launch_batch_m<4, false>(a, grid, block, direct_roi, st);
         case 2: return ns ? launch_batch_m<2, true>(a, grid, block, direct_roi, st)
                           : launch_batch_m<2, false>(a, grid, block, direct_roi, st);
         default: return ns ? launch_batch_m<3, true>(a, grid, block, direct_roi, st)
@@ -1948,6 +2037,7 @@ static const void *batch_kernel(int mode, int fp64, int ns, int vol, uint32_t bl
     switch (mode) {
         case 0: return batch_kernel_k<0>(fp64, ns, vol, block);
         case 1: return batch_kernel_k<1>(fp64, ns, vol, block);
+        case 4: return batch_kernel_k<4>(fp64, ns, vol, block);
         case 2: return batch_kernel_k<2>(fp64, ns, vol, block);
         default: return batch_kernel_k<3>(fp64, ns, vol, block);
     }

@@ -223,6 +223,9 @@ struct nyx_plan {
     int K = 0, ng = 0;
     nyx_precision prec = NYX_FP32;
     uint32_t grid = 0, block = 256;
+    // second launch of the batch kernel (packed hash): the size classes below small_cls
+    uint32_t small_cls = 0, small_kp = 0, small_grid = 0;
+    LdsLayout small_lds{};
     std::vector<uint32_t> roi_tiles;   // per-ROI tile count for the per-ROI path
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -559,7 +562,7 @@ nyx_status fetch_rois(nyx_ctx *ctx, Work &w, hipStream_t st) {
 }
 
 struct Config {
-    int mode = 0;            // 0 dense + list, 1 hash, 2 dense + scan, 3 packed dense + scan
+    int mode = 0;            // 0 dense + list, 1 hash, 2 dense + scan, 3 packed dense + scan, 4 packed hash
     uint32_t kp = 1;
     uint32_t block = 256;
     uint32_t split_vox = 0, tile_vox = 0;
@@ -569,6 +572,8 @@ struct Config {
     uint32_t copies = 1;     // privatised copies of each dense triangle (scan modes)
     float tile_scale = 1.f;  // split ROIs above tile_scale x the load-balance share
     int nonsym = 0;          // ordered counts: full squares (dense modes 2 and 3, or the hash)
+    uint32_t small_cls = 0;  // packed hash: items of size classes below this take a launch of their own
+    uint32_t small_kp = 0, small_cap = 0;   // with this many directions per pass and slots per direction
     uint32_t band_vox = 0;   // ROIs above this go to the banded kernel (0: none)
     uint32_t band_w = 0;     // band width (power of two)
 };
@@ -579,7 +584,7 @@ struct Config {
 void set_band(Config &c, uint32_t ng) {
     c.band_vox = 0u;
     c.band_w = 0u;
-    if (c.mode != 1 || c.nonsym) return;
+    if ((c.mode != 1 && c.mode != 4) || c.nonsym) return;
     uint32_t w = 1u;
     while (w * 2u <= ng && (uint64_t)ng * (w * 2u) * 4u <= kBandLds) w *= 2u;
     if (w < kBandMinW) return;
@@ -590,7 +595,8 @@ void set_band(Config &c, uint32_t ng) {
 const char *mode_name(int m) {
     switch (m) {
         case 0: return "dense-list";
-        case 1: return "hash";
+        case 1:
+        case 4: return "hash";
         case 2: return "dense-scan";
         default: return "dense16-scan";
     }
@@ -612,7 +618,25 @@ uint32_t u_words(int mode, uint32_t ng, bool nonsym = false) {
 
 // Marginal words per reducing wave: row, sum and difference marginals, plus
 // the column marginal of an ordered matrix.
-uint32_t marg_words(uint32_t ng, bool nonsym) { return (nonsym ? 5u : 4u) * ng; }
+// (16-bit counters in the packed hash mode, whose items are small).
+uint32_t marg_words(uint32_t ng, bool nonsym, int mode = 0) {
+    const uint32_t n = (nonsym ? 5u : 4u) * ng;
+    return mode == 4 ? (n + 1u) / 2u : n;
+}
+
+// Bits of a 0-based level.
+uint32_t level_bits(uint32_t ng) {
+    uint32_t b = 1u;
+    while ((1u << b) < ng) ++b;
+    return b;
+}
+
+// Most voxels of a packed-hash item: the counts left in a slot's word, and
+// marginals (at most four times the pairs of a direction) of 16 bits.
+uint32_t packed_item_max(uint32_t ng) {
+    const uint32_t lb = level_bits(ng);
+    return lb > 12u ? 0u : std::min((1u << (32u - 2u * lb)) - 1u, 16383u);
+}
 
 // ring: reserve an LDS level ring for the staged accumulation, sized to the
 // LDS the work-group can take without lowering its occupancy.
@@ -632,7 +656,13 @@ LdsLayout make_layout(const Config &c, uint32_t ng, int K, bool ring) {
         off += (bytes + 15u) & ~15u;
         return o;
     };
-    if (c.mode != 1) {
+    if (c.mode == 4) {
+        L.n_tri = c.kp;
+        L.lvl_bits = level_bits(ng);
+        L.cnt_bits = 32u - 2u * L.lvl_bits;
+        L.item_max = std::min(packed_item_max(ng), packed_voxels(c.hash_cap));
+        L.u_off = take(L.n_tri * c.hash_cap * 4u);
+    } else if (c.mode != 1) {
         L.n_tri = c.merged ? 1u : c.kp;   // merged: one triangle for all offsets
         L.u_off = take(L.n_tri * L.copies * L.tri_pad * 4u);
     } else {
@@ -643,7 +673,7 @@ LdsLayout make_layout(const Config &c, uint32_t ng, int K, bool ring) {
     L.lcnt_off = take(c.kp * 4u);
     L.buf_off = take((c.mode == 2 || c.mode == 3) ? L.nwaves * scan_buf_entries(scan_cells(c.mode)) * 2u : 0u);
     L.marg_sets = std::min(L.nwaves, c.merged ? 1u : c.kp);   // one set per wave that reduces a matrix
-    L.marg_off = take(L.marg_sets * marg_words(ng, c.nonsym != 0) * 4u);
+    L.marg_off = take(L.marg_sets * marg_words(ng, c.nonsym != 0, c.mode) * 4u);
     L.misc_off = take(128u * 4u);
     if ((c.mode == 2 || c.mode == 3) && !c.nonsym) L.ro_off = take((ng + 1u) * 4u);
     L.item_off = take((uint32_t)kTicketChunk * kItemBytes);
@@ -661,16 +691,18 @@ LdsLayout make_layout(const Config &c, uint32_t ng, int K, bool ring) {
     return L;
 }
 
+// Work-groups of the persistent kernel per CU for a given LDS footprint.
+uint32_t groups_per_cu(uint64_t lds_bytes) {
+    return (uint32_t)std::min<uint64_t>(kMaxGroupsPerCu, kLdsBudget / std::max<uint64_t>(lds_bytes, 1u));
+}
+
 // Largest voxel count any work item can hold under a split rule.
 uint64_t max_item_vox(const std::vector<RoiDesc> &rois, uint32_t split_vox, uint32_t tile_vox) {
     uint64_t m = 0;
     for (const RoiDesc &r : rois) {
         uint32_t W = (uint32_t)(r.x1 - r.x0 + 1);
         Tiling t = tiles_for(r.n, r.rows, W, split_vox, tile_vox);
-        if (t.row_blocks * t.col_blocks == 1u) { m = std::max<uint64_t>(m, r.n); continue; }
-        uint32_t rpt = (r.rows + t.row_blocks - 1u) / t.row_blocks;
-        uint32_t cpt = (W + t.col_blocks - 1u) / t.col_blocks;
-        m = std::max<uint64_t>(m, std::min<uint64_t>((uint64_t)rpt * cpt, r.n));
+        m = std::max<uint64_t>(m, item_bound(r.n, r.rows, W, t));
     }
     return m;
 }
@@ -678,9 +710,77 @@ uint64_t max_item_vox(const std::vector<RoiDesc> &rois, uint32_t split_vox, uint
 // Feasible LDS configurations for this workload, one per accumulation mode,
 // each with as many directions per pass as fit.  Dense triangles first; the
 // hash table only when no dense triangle fits.
-// Work-groups of the persistent kernel per CU for a given LDS footprint.
-uint32_t groups_per_cu(uint64_t lds_bytes) {
-    return (uint32_t)std::min<uint64_t>(kMaxGroupsPerCu, kLdsBudget / std::max<uint64_t>(lds_bytes, 1u));
+// Packed hash tables, one per direction of a pass, for items much smaller
+// than their triangle.  The main launch takes any item up to the split size;
+// items of the smaller size classes take a second one whose tables (and so
+// whose LDS) are sized for them, with every work-group slot that frees: the
+// class boundary is the one with the least work per slot, counting an item
+// as its voxels plus the fixed part of its reductions (about 500 voxels'
+// worth at 256 levels).  mode 0 (not 4) when nothing fits.
+Config packed_config(const nyx_ctx *ctx, const Work &w, uint32_t ng, int K, int force_split, uint32_t block,
+                     uint32_t lb, bool nonsym, float tile_scale) {
+    Config best;
+    const uint32_t n_max = packed_item_max(ng);
+    // The largest split that fits (a split ROI costs a merge in global
+    // memory), then the most directions per pass: every pass repeats the
+    // sweep and the fixed part of the reductions (2000 cells at 256 levels:
+    // four directions in one 512-thread group per CU beat one in five groups).
+    for (uint32_t kp = (uint32_t)K; kp >= 1u; kp = kp == 1u ? 0u : (kp + 1u) / 2u) {
+        for (uint32_t split = std::min(lb, n_max);; split /= 2u) {
+            const uint64_t mi = max_item_vox(w.h_rois, split, split);
+            if (mi <= n_max) {
+                Config c;
+                c.mode = 4; c.kp = kp; c.block = block; c.split_vox = c.tile_vox = split;
+                // (room for a whole item of the split size, whatever the planned images hold)
+                c.hash_cap = packed_slots((uint32_t)std::max<uint64_t>(mi, split), ~0u);
+                c.force_split = force_split; c.nonsym = nonsym ? 1 : 0; c.tile_scale = tile_scale;
+                if (make_layout(c, ng, K, false).bytes <= kLdsBudget) {
+                    if (best.mode != 4 || split > best.split_vox) best = c;
+                    break;
+                }
+            }
+            if (split < 1024u) break;
+        }
+    }
+    if (best.mode != 4) return best;
+    set_band(best, ng);
+    if (!force_split) {
+        // voxels and items by size class, as the device will bucket them
+        double vox[kClasses] = {}, num[kClasses] = {};
+        for (const RoiDesc &r : w.h_rois) {
+            if (best.band_vox && r.n > best.band_vox) continue;   // (no batch items)
+            const Tiling t = tiles_for(r.n, r.rows, (uint32_t)(r.x1 - r.x0 + 1), best.split_vox, best.tile_vox);
+            const uint32_t cl = size_class(item_bound(r.n, r.rows, (uint32_t)(r.x1 - r.x0 + 1), t));
+            vox[cl] += r.n;
+            num[cl] += (double)t.row_blocks * t.col_blocks;
+        }
+        const double fixed = 500.0 * (1.0 + ng / 256.0);
+        const auto work = [&](uint32_t lo, uint32_t hi) {
+            double s = 0.0;
+            for (uint32_t cl = lo; cl < hi; ++cl) s += vox[cl] + fixed * num[cl];
+            return s;
+        };
+        const double g_main = groups_per_cu(make_layout(best, ng, K, false).bytes);
+        double score = work(0u, kClasses) / g_main * 0.8;   // (a second launch has to be worth its cost)
+        for (uint32_t cls = 6u; cls <= 11u; ++cls) {
+            for (uint32_t kp = (uint32_t)K; kp >= 1u; kp = kp == 1u ? 0u : (kp + 1u) / 2u) {
+                Config s = best;
+                s.kp = kp;
+                s.hash_cap = packed_slots((1u << cls) - 1u, ~0u);
+                const uint32_t bytes = make_layout(s, ng, K, false).bytes;
+                if (bytes > kLdsBudget || s.hash_cap >= best.hash_cap) continue;
+                const double passes = ((double)K + kp - 1) / kp / (((double)K + best.kp - 1) / best.kp);
+                const double t = work(0u, cls) * passes / groups_per_cu(bytes) + work(cls, kClasses) / g_main;
+                if (t < score) {
+                    score = t;
+                    best.small_cls = cls;
+                    best.small_kp = kp;
+                    best.small_cap = s.hash_cap;
+                }
+            }
+        }
+    }
+    return best;
 }
 
 // merged: every offset counts into one LDS triangle in one pass, so only the
@@ -751,6 +851,10 @@ std::vector<Config> candidate_configs(const nyx_ctx *ctx, const Work &w, uint32_
         }
     }
     out.insert(out.end(), later.begin(), later.end());
+    if (!merged && copies == 1u && packed_item_max(ng) > 0u) {
+        const Config c = packed_config(ctx, w, ng, K, force_split, block, lb, nonsym, tile_scale);
+        if (c.mode == 4) out.push_back(c);
+    }
     if (!out.empty() || fixed >= kLdsBudget || merged || copies > 1u) return out;
     // hash mode: items small enough that kp directions of pairs fill at most
     // half the table
@@ -781,15 +885,32 @@ std::vector<Config> candidate_configs(const nyx_ctx *ctx, const Work &w, uint32_
     return out;
 }
 
-// Default choice without timing: an ordered scan of the triangle costs
-// O(Ng^2) per direction and item, a returning-atomic list costs O(pairs);
-// scan while the triangle is small next to the average item.
+// Default choice without timing.  An ordered scan of the triangle costs
+// O(Ng^2) per direction and item and its LDS holds few work-groups, but its
+// atomics return nothing; the packed hash costs O(pairs) and LDS in
+// proportion to the item, with two LDS round trips a pair.  The line lies at
+// a triangle of 16 times the average item.  Batch kernel, scan and hash, in
+// us, on one 2048 x 2048 image: 2000 cells of 100-5000 voxels (1250 on
+// average) 41 and 155 at 64 levels, 144 and 192 at 128 (6.6 times), 448 and
+// 212 at 256 (26 times); 8000 of 30-600 (190) 90 and 138 at 64 levels (11
+// times), 188 and 146 at 100 (27 times), 1384 and 188 at 256.  (The list of
+// the returning-atomic mode lost to one of them everywhere: 81, 181, 332 on
+// the first and 118, 269, 774 us on the second; it stays for callers that ask
+// for it and where neither fits.)
 Config default_config(const std::vector<Config> &cands, const Work &w, uint32_t ng, int K) {
     uint64_t total_vox = 0;
     for (const RoiDesc &r : w.h_rois) total_vox += r.n;
     const uint64_t avg = w.h_rois.empty() ? 1u : std::max<uint64_t>(1u, total_vox / w.h_rois.size());
     const uint64_t tri = (uint64_t)ng * (ng + 1u) / 2u;
-    const bool prefer_scan = tri <= 8u * avg;
+    bool any_scan = false, any_hash = false;
+    for (const Config &c : cands) {
+        any_scan |= c.mode == 2 || c.mode == 3;
+        any_hash |= c.mode == 4;
+    }
+    if (any_hash && (tri > 16u * avg || !any_scan))
+        for (const Config &c : cands)
+            if (c.mode == 4) return c;
+    const bool prefer_scan = any_scan && (any_hash || tri <= 8u * avg);
     // among the candidates of the preferred kind: fewest passes over the
     // voxels per work-group slot (passes / work-groups per CU); ties keep the
     // earlier candidate (more directions per pass)
@@ -811,6 +932,14 @@ nyx_status choose_config(nyx_ctx *ctx, const Work &w, uint32_t ng, int K, int fo
     if (c.empty()) return fail(ctx, NYX_ERR_UNSUPPORTED, "no LDS configuration fits n_bins=%u with %d offsets", ng, K);
     cfg = default_config(c, w, ng, K);
     return NYX_OK;
+}
+
+// Whether a candidate is what a forced accumulation mode names: the dense
+// modes 0, 2 and 3 by number; the hash table, packed or not, where no dense
+// triangle fits.
+bool is_mode(const Config &c, int mode, const std::vector<Config> &cands) {
+    if (mode != 1) return c.mode == mode && mode != 4;
+    return (c.mode == 1 || c.mode == 4) && (cands.front().mode == 1 || cands.front().mode == 4);
 }
 
 // Item and split-slot counts implied by a configuration.
@@ -835,8 +964,9 @@ void count_items(const std::vector<RoiDesc> &rois, const Config &c, uint64_t *it
 // Row-sweep eligibility: all images 2D and every offset of each pass one of
 // the four distance-1 in-plane classes, each class at most once per pass.
 bool sweep_table(const std::vector<ImgDesc> &imgs, const nyx_offset *off, int K, uint32_t kp,
-                 int8_t (*sweep)[4], int max_passes) {
+                 int8_t (*sweep)[4], uint32_t *flip, int max_passes) {
     memset(sweep, -1, sizeof(int8_t[4]) * max_passes);
+    memset(flip, 0, sizeof(uint32_t) * max_passes);
     for (const ImgDesc &d : imgs)
         if (d.nz != 1) return false;
     int pass = 0;
@@ -852,6 +982,9 @@ bool sweep_table(const std::vector<ImgDesc> &imgs, const nyx_offset *off, int K,
             else cls = 3;                        // (-1, -1) or (+1, +1)
             if (sweep[pass][cls] >= 0) return false; // the same class twice in a pass
             sweep[pass][cls] = (int8_t)(d - d0);
+            // the sweep's own directions: (0, 1), (-1, 0), (-1, 1) and (1, 1)
+            const bool own = cls == 0 ? o.dx > 0 : (cls == 3 ? o.dy > 0 : o.dy < 0);
+            if (!own) flip[pass] |= 1u << (d - d0);
         }
     }
     return true;
@@ -876,7 +1009,7 @@ bool sweep3_table(const nyx_offset *off, int K, uint32_t kp, uint64_t *sweep, in
 }
 
 void set_sweep(StepArgs &a, const std::vector<ImgDesc> &imgs, const nyx_offset *off, int K, uint32_t kp) {
-    a.sweep_ok = sweep_table(imgs, off, K, kp, a.sweep, kMaxSweepPasses) ? 1 : 0;
+    a.sweep_ok = sweep_table(imgs, off, K, kp, a.sweep, a.sweep_flip, kMaxSweepPasses) ? 1 : 0;
     a.sweep3_ok = !a.sweep_ok && sweep3_table(off, K, kp, a.sweep3, kMaxSweepPasses) ? 1 : 0;
 }
 
@@ -970,10 +1103,14 @@ nyx_status setup_step(nyx_ctx *ctx, Work &w, const Config &cfg, const nyx_offset
     a.tile_vox = cfg.tile_vox;
     a.force_split = cfg.force_split;
     a.enqueue = 1;
+    a.cls_lo = 0u;
+    a.cls_hi = kClasses;
+    a.tickets = C_TICKETS;
     a.fp64 = fp64;
-    // ordered counts take the gather accumulation (no sweep, no staged ring)
-    if (cfg.nonsym) a.sweep_ok = a.sweep3_ok = 0;
-    else set_sweep(a, w.h_imgs, off, K, cfg.kp);
+    // (ordered counts in volumes and at other distances take the gather: the
+    // 3D sweep and the staged ring fold a direction and its reverse together)
+    set_sweep(a, w.h_imgs, off, K, cfg.kp);
+    if (cfg.nonsym) a.sweep3_ok = 0;
     a.lds = make_layout(cfg, ng, K, !a.sweep_ok && !a.sweep3_ok);
     return NYX_OK;
 }
@@ -991,6 +1128,24 @@ nyx_status set_outputs(nyx_ctx *ctx, StepArgs &a, nyx_roi_table *rois, void *tab
     return NYX_OK;
 }
 
+// The batch kernel over the queue: one launch, or one for the larger size
+// classes and one, with a layout of its own, for the smaller.
+hipError_t launch_batches(const nyx_plan *p, hipStream_t st) {
+    StepArgs a = p->w.args;
+    if (p->small_cls) a.cls_lo = p->small_cls;
+    hipError_t e = launch_batch(a, p->grid, p->block, kNone, st);
+    if (e != hipSuccess || !p->small_cls) return e;
+    a.cls_lo = 0u;
+    a.cls_hi = p->small_cls;
+    a.tickets = C_TICKETS2;
+    a.lds = p->small_lds;
+    nyx_offset off[kMaxOffsets];
+    for (int k = 0; k < a.K; ++k) off[k] = nyx_offset{a.off[k][0], a.off[k][1], a.off[k][2]};
+    set_sweep(a, p->w.h_imgs, off, a.K, p->small_kp);
+    if (a.nonsym) a.sweep3_ok = 0;
+    return launch_batch(a, p->small_grid, 256u, kNone, st);
+}
+
 // The full step on a stream.  per_roi: one accumulation launch per ROI.
 // scanned: the label statistics are those of the discovery just made on this
 // stream (one-shot calls), so the images are not scanned again.
@@ -1006,7 +1161,7 @@ nyx_status enqueue_step(nyx_plan *p, hipStream_t st, bool per_roi, bool scanned 
     HIPC(ctx, launch_compact(a, 0u, 0xFFFFFFFFu, st));
     HIPC(ctx, launch_zero_split(a, st));
     if (!per_roi) {
-        HIPC(ctx, launch_batch(a, p->grid, p->block, kNone, st));
+        HIPC(ctx, launch_batches(p, st));
     } else {
         for (uint32_t r = 0; r < p->w.n_rois; ++r) HIPC(ctx, launch_batch(a, p->roi_tiles[r], p->block, r, st));
     }
@@ -1039,10 +1194,12 @@ std::string describe(const Config &c, const nyx_plan *p, uint64_t items, uint32_
     char buf[640];
     snprintf(buf, sizeof buf,
              "mode=%s kp=%u copies=%u symmetric=%d block=%u grid=%u lds=%uB split_vox=%u tile_vox=%u tile_scale=%g "
-             "list_cap=%u hash_cap=%u band_vox=%u band_w=%u band_voxels=%llu rois=%u items=%llu split_rois=%u ng=%d K=%d "
+             "list_cap=%u hash_cap=%u small_cls=%u small_kp=%u small_cap=%u small_grid=%u small_lds=%uB band_vox=%u band_w=%u band_voxels=%llu rois=%u items=%llu split_rois=%u ng=%d K=%d "
              "tuned_ms=%.4f",
              mode_name(c.mode), c.kp, p->w.args.lds.copies, c.nonsym ? 0 : 1, c.block, p->grid, p->w.args.lds.bytes, c.split_vox,
-             c.tile_vox, (double)c.tile_scale, c.list_cap, c.hash_cap, c.band_vox, c.band_w,
+             c.tile_vox, (double)c.tile_scale, c.list_cap, c.hash_cap, p->small_cls, p->small_cls ? c.small_kp : 0u,
+             p->small_cls ? c.small_cap : 0u, p->small_cls ? p->small_grid : 0u, p->small_cls ? p->small_lds.bytes : 0u,
+             c.band_vox, c.band_w,
              (unsigned long long)band_voxels, p->w.n_rois,
              (unsigned long long)items,
              n_split, p->ng, p->K, (double)p->tuned_ms);
@@ -1063,6 +1220,19 @@ nyx_status configure(nyx_plan *p, const Config &cfg, const nyx_extract_opts *opt
     HIPC(ctx, batch_occupancy(cfg.mode, p->prec == NYX_FP64, cfg.nonsym, p->w.args.sweep3_ok, cfg.block,
                               p->w.args.lds.bytes, &occ));
     p->grid = (uint32_t)ctx->n_cu * (uint32_t)std::max(occ, 1);
+    p->small_cls = cfg.mode == 4 ? cfg.small_cls : 0u;
+    if (p->small_cls) {
+        Config s = cfg;
+        s.block = 256u;
+        s.kp = p->small_kp = cfg.small_kp;
+        s.hash_cap = cfg.small_cap;
+        StepArgs t = p->w.args;
+        set_sweep(t, p->w.h_imgs, opts->offsets_host, p->K, s.kp);
+        if (cfg.nonsym) t.sweep3_ok = 0;
+        p->small_lds = make_layout(s, (uint32_t)p->ng, p->K, !t.sweep_ok && !t.sweep3_ok);
+        HIPC(ctx, batch_occupancy(cfg.mode, p->prec == NYX_FP64, cfg.nonsym, t.sweep3_ok, 256u, p->small_lds.bytes, &occ));
+        p->small_grid = (uint32_t)ctx->n_cu * (uint32_t)std::max(occ, 1);
+    }
     uint64_t items;
     uint32_t n_split;
     count_items(p->w.h_rois, cfg, &items, &n_split, &p->roi_tiles);
@@ -1446,7 +1616,7 @@ nyx_status plan_init(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_images, cons
     if (opts->accum_mode >= 0) {
         bool found = false;
         for (const Config &c : cands)
-            if (c.mode == opts->accum_mode) { cfg = c; found = true; break; }
+            if (is_mode(c, opts->accum_mode, cands)) { cfg = c; found = true; break; }
         if (!found) return fail(ctx, NYX_ERR_UNSUPPORTED, "accumulation mode %d does not fit this workload", opts->accum_mode);
     }
     cfg = widen_block(cfg, (uint32_t)p->ng, p->K, takes_sweep3(p->w, cfg, opts->offsets_host, p->K));
@@ -1522,7 +1692,7 @@ nyx_status nyx_plan_create(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_images
         for (auto &e : ev) HIPC(ctx, hipEventCreate(&e));
         float best = 1e30f;
         for (const Config &c : cands) {
-            if (opts->accum_mode >= 0 && c.mode != opts->accum_mode) continue;
+            if (opts->accum_mode >= 0 && !is_mode(c, opts->accum_mode, cands)) continue;
             if ((s = configure(p.get(), c, opts)) != NYX_OK) continue;
             set_outputs(ctx, p->w.args, nullptr, tmp.p, p->w.n_rois);
             if ((s = enqueue_step(p.get(), st, false)) != NYX_OK) break;
@@ -1626,7 +1796,7 @@ nyx_status nyx_plan_profile(nyx_plan *p, void *table, float *ms_host, nyx_stream
     if (he == hipSuccess) he = hipEventRecord(ev[3], st);
     if (he == hipSuccess) he = launch_zero_split(a, st);
     if (he == hipSuccess) he = hipEventRecord(ev[4], st);
-    if (he == hipSuccess) he = launch_batch(a, p->grid, p->block, kNone, st);
+    if (he == hipSuccess) he = launch_batches(p, st);
     if (he == hipSuccess) he = hipEventRecord(ev[5], st);
     if (he == hipSuccess) he = launch_band(a, (uint32_t)ctx->n_cu, st);
     if (he == hipSuccess) he = hipEventRecord(ev[6], st);

@@ -14,8 +14,9 @@ constexpr int kNumNeighbourFeat = 37;   // NGLDM, NGTDM and GLDM features per RO
 constexpr int kMaxOffsets = 64;
 constexpr int kClasses = 32;           // work-item size classes (log2 of voxels)
 constexpr uint32_t kNone = 0xFFFFFFFFu;
-constexpr int kTicketChunk = 8;        // most queue entries taken per work ticket
-constexpr uint32_t kTicketVox = 8192u; // voxels a ticket of small items aims at
+constexpr uint32_t kTicketShift = 3u;  // most queue entries taken per work ticket: 2^3
+constexpr int kTicketChunk = 1 << kTicketShift;
+constexpr int kTicketVoxShift = 13;    // voxels a ticket of small items aims at: 2^13
 constexpr uint32_t kItemBytes = 128u;  // LDS bytes of one staged work-item descriptor
 constexpr int kMaxSweepPasses = 16;    // passes with a precomputed 2D sweep map
 
@@ -30,13 +31,15 @@ enum Counter : int {
     C_AUX = 7,      // extra storage of the split ROIs, in blocks of 64 counters (aux_values)
     C_CLASS = 8,    // kClasses counters: work-group items per size class
     C_TICKETS = 128,  // kTicketLanes ticket counters of the persistent kernel, kTicketStride apart
-    C_BLOCKS = 128 + 32 * 32, // per-block ROI counts of the compaction (variable length)
+    C_TICKETS2 = 128 + 32 * 32,     // the same for the second launch of a step (small items)
+    C_BLOCKS = 128 + 2 * 32 * 32, // per-block ROI counts of the compaction (variable length)
 };
 // Work-group w draws tickets w mod kTicketLanes, +kTicketLanes, ... from
 // its own counter: the claims spread over kTicketLanes memory lines instead
 // of serialising on one.
 constexpr uint32_t kTicketLanes = 32, kTicketStride = 32;
-static_assert(C_TICKETS + kTicketLanes * kTicketStride <= C_BLOCKS, "ticket counters overlap");
+static_assert(C_TICKETS + kTicketLanes * kTicketStride <= C_TICKETS2 &&
+              C_TICKETS2 + kTicketLanes * kTicketStride <= C_BLOCKS, "ticket counters overlap");
 
 enum ErrBit : uint32_t {
     E_LABEL_RANGE = 1u,   // a label exceeds the planned label-table capacity
@@ -126,11 +129,13 @@ __host__ __device__ constexpr uint32_t scan_buf_entries(uint32_t cells_per_read)
 }
 
 struct LdsLayout {
-    uint32_t mode;        // 0 = dense triangles, 1 = hash table
+    uint32_t mode;        // 0, 2, 3 = dense triangles, 1 = hash table, 4 = packed hash tables
     uint32_t kp;          // directions accumulated per pass
     uint32_t tri_pad;     // u32 words per dense triangle (dense mode)
     uint32_t list_cap;    // entries per direction list
-    uint32_t hash_cap;    // slots (power of two, hash mode)
+    uint32_t hash_cap;    // slots: power of two (hash mode), or per direction (packed hash)
+    uint32_t lvl_bits, cnt_bits;   // packed hash: a slot is hi level | lo level | count
+    uint32_t item_max;    // packed hash: most voxels a table takes (room and cnt_bits)
     uint32_t u_off, list_off, lcnt_off, marg_off, feat_off, sums_off, misc_off, hkey_off, hcnt_off, buf_off;
     uint32_t item_off;    // staged descriptors of the current ticket (work-group kernel)
     uint32_t ring_off, ring_bytes;   // level ring of the staged accumulation (0 bytes: none)
@@ -196,8 +201,11 @@ struct StepArgs {
     LdsLayout lds;
     // 2D distance-1 row-sweep accumulation: per pass, the local direction slot
     // of the H, V, D45, D135 neighbour classes (-1 = absent)
+    uint32_t cls_lo, cls_hi;    // size classes [cls_lo, cls_hi) of this launch of the batch kernel
+    uint32_t tickets;           // its ticket counters (C_TICKETS or C_TICKETS2)
     int32_t sweep_ok;
     int8_t sweep[kMaxSweepPasses][4];
+    uint32_t sweep_flip[kMaxSweepPasses];   // ordered counts: bit dl where direction dl runs against its class
     // 3D distance-1 row sweep: per pass, 1 + the local direction slot of each
     // of the 13 forward neighbours (class3d) in four bits each, 0 = absent
     int32_t sweep3_ok;
@@ -231,6 +239,48 @@ inline Tiling tiles_for(uint32_t n, uint32_t rows, uint32_t width, uint32_t spli
     return t;
 }
 
+// Most voxels one item of a ROI of n voxels can hold: its own n, or a tile's
+// share of the box.  Items are put into the size class of this bound.
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline uint32_t item_bound(uint32_t n, uint32_t rows, uint32_t width, Tiling t) {
+    if (t.row_blocks * t.col_blocks <= 1u) return n;
+    const uint64_t area = (uint64_t)((rows + t.row_blocks - 1u) / t.row_blocks) *
+                          ((width + t.col_blocks - 1u) / t.col_blocks);
+    return area < n ? (uint32_t)area : n;
+}
+
+// Slots of the packed hash table an item of at most nb voxels uses, of cap:
+// three for two pairs of a direction (a voxel owns one pair per direction),
+// in buckets of four.
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline uint32_t packed_slots(uint32_t nb, uint32_t cap) {
+    const uint32_t s = (nb + (nb >> 1) + 11u) & ~3u;
+    return s < cap ? s : cap;
+}
+
+// Most voxels of an item that packed_slots(., cap) doesn't cut short: the
+// largest n with n + n / 2 + 8 <= cap.
+inline uint32_t packed_voxels(uint32_t cap) { return cap < 8u ? 0u : (2u * (cap - 8u) + 1u) / 3u; }
+
+// First bucket a key (at most 24 bits) probes in a packed table of `buckets`
+// (below 2^15): the upper half of the low 32 bits of key * C, scaled to the
+// table.  The 24-bit multiply returns int: its product is unsigned again
+// before it is shifted.
+__host__ __device__
+inline uint32_t packed_bucket(uint32_t key, uint32_t buckets) {
+#ifdef __HIP_DEVICE_COMPILE__
+    const uint32_t p = (uint32_t)__umul24(key, 0x9E3779u);
+    return (uint32_t)__umul24(p >> 16, buckets) >> 16;
+#else
+    const uint32_t p = (uint32_t)((uint64_t)(key & 0xFFFFFFu) * 0x9E3779u);
+    return ((p >> 16) * buckets) >> 16;
+#endif
+}
+
 // Bounds of tile `tile` of a ROI: bbox rows [ra, rb) and columns [ca, cb).
 #ifdef __HIPCC__
 __host__ __device__
@@ -250,23 +300,43 @@ inline void tile_bounds(uint32_t rows, uint32_t width, uint32_t n_tiles, uint32_
 }
 
 // Work tickets.  The queue is the concatenation of the size-class buckets,
-// largest class first; a ticket hands out up to ticket_chunk(cl) consecutive
+// largest class first; a ticket hands out 2^ticket_shift(cl) consecutive
 // entries of one class (several small items per ticket, one item per ticket
-// from the classes whose items alone keep a work-group busy).
+// from the classes whose items alone keep a work-group busy), at most 2^most.
+// (Powers of two: with general quotients the batch kernel of the 16-bit
+// triangles spilled registers, 2252 -> 2275 us on a 64-image plate.)
 #ifdef __HIPCC__
 __host__ __device__
 #endif
-inline uint32_t ticket_chunk(int cl) {
-    const uint32_t c = kTicketVox >> cl;
-    return c < 1u ? 1u : (c > (uint32_t)kTicketChunk ? (uint32_t)kTicketChunk : c);
+inline uint32_t ticket_shift(int cl, uint32_t most) {
+    const uint32_t s = cl < kTicketVoxShift ? (uint32_t)(kTicketVoxShift - cl) : 0u;
+    return s < most ? s : most;
+}
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline uint32_t ticket_chunk(int cl, uint32_t most = kTicketShift) { return 1u << ticket_shift(cl, most); }
+
+// Shift of the most entries per ticket for `items` entries and `groups`
+// work-groups: a quarter of a group's share, rounded down to a power of two,
+// so that few items still spread over all groups.  (Eight a ticket always
+// kept 10 work-groups busy with an image of 80 regions: 101 us, now 28;
+// 2000 cells of 100-5000 voxels 117, now 43.)
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline uint32_t ticket_most(uint32_t items, uint32_t groups) {
+    uint32_t s = 0u;
+    while (s < kTicketShift && (items >> (s + 3u)) >= groups) ++s;
+    return s;
 }
 
 #ifdef __HIPCC__
 __host__ __device__
 #endif
-inline uint32_t class_tickets(uint32_t entries, int cl) {
-    const uint32_t ch = ticket_chunk(cl);
-    return (entries + ch - 1u) / ch;
+inline uint32_t class_tickets(uint32_t entries, int cl, uint32_t most = kTicketShift) {
+    const uint32_t s = ticket_shift(cl, most);
+    return (entries + (1u << s) - 1u) >> s;
 }
 
 // first[cl] = tickets of all larger classes (entries[cl]: queue entries of
@@ -274,11 +344,11 @@ inline uint32_t class_tickets(uint32_t entries, int cl) {
 #ifdef __HIPCC__
 __host__ __device__
 #endif
-inline uint32_t ticket_offsets(const uint32_t *entries, uint32_t *first) {
+inline uint32_t ticket_offsets(const uint32_t *entries, uint32_t *first, uint32_t most = kTicketShift) {
     uint32_t acc = 0;
     for (int cl = kClasses - 1; cl >= 0; --cl) {
         first[cl] = acc;
-        acc += class_tickets(entries[cl], cl);
+        acc += class_tickets(entries[cl], cl, most);
     }
     return acc;
 }
@@ -289,13 +359,13 @@ inline uint32_t ticket_offsets(const uint32_t *entries, uint32_t *first) {
 __host__ __device__
 #endif
 inline void ticket_range(uint32_t t, const uint32_t *entries, const uint32_t *first, int *cl_out, uint32_t *e0,
-                         uint32_t *e1) {
+                         uint32_t *e1, uint32_t most = kTicketShift) {
     int cl = kClasses - 1;
-    while (cl > 0 && t >= first[cl] + class_tickets(entries[cl], cl)) --cl;
-    const uint32_t ch = ticket_chunk(cl);
+    while (cl > 0 && t >= first[cl] + class_tickets(entries[cl], cl, most)) --cl;
+    const uint32_t s = ticket_shift(cl, most);
     *cl_out = cl;
-    *e0 = (t - first[cl]) * ch;
-    const uint32_t end = *e0 + ch;
+    *e0 = (t - first[cl]) << s;
+    const uint32_t end = *e0 + (1u << s);
     *e1 = end < entries[cl] ? end : entries[cl];
 }
 

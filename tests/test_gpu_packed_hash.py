@@ -1,0 +1,133 @@
+"""The packed hash of many levels, the tickets and the ordered row sweep on the
+GPU: regions from one voxel to several tiles, plans at the edges of the key and
+count fields (level counts at powers of two, the largest it takes, and one
+beyond), planes and volumes, symmetric and ordered, against the features of the
+exact counts; and a plan whose images change under it to regions that its
+tables cannot take whole."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+FLAT = [(0, 0, 1), (0, 1, 0), (0, 1, 1), (0, 1, -1)]
+TURNED = [(0, 0, -1), (0, 1, -1), (0, 1, 0), (0, -1, -1)]
+FAR = [(0, 0, -1), (0, 1, -1), (0, 1, 2), (0, 3, 0)]
+DEEP = [(0, 0, 1), (0, 1, 0), (1, 0, 0), (1, 1, -1), (-1, 1, 1)]
+CLUSHADE, CLUPROM = 3, 2
+UNIT = [6, 8, 12, 16, 17, 23, 26]     # CORR, the entropies and the information measures: error against 1
+
+
+def _plane(rng, ny, nx, pieces):
+    """Regions of given (rows, columns) side by side, with holes and ragged edges."""
+    I = rng.integers(0, 60000, (1, ny, nx)).astype(np.uint16)
+    L = np.zeros((1, ny, nx), np.uint32)
+    y = x = tall = 0
+    for k, (h, w) in enumerate(pieces):
+        if x + w > nx:
+            y, x, tall = y + tall, 0, 0
+        assert y + h <= ny and x + w <= nx
+        part = L[0, y:y + h, x:x + w]
+        part[rng.random((h, w)) < 0.93] = k + 1
+        part[0, 0] = k + 1
+        x, tall = x + w, max(tall, h)
+    return I, L
+
+
+def _images(kind):
+    rng = np.random.default_rng(len(kind))
+    if kind == "volume":
+        I = rng.integers(0, 5000, (12, 40, 70)).astype(np.uint16)
+        L = np.ones((12, 40, 70), np.uint32)
+        L[:3, :9, :9] = 2
+        L[11, 39, 69] = 3
+        return [(I, L), _plane(rng, 20, 40, [(3, 5), (20, 11)])]
+    small = [(1, 1), (1, 2), (2, 2), (5, 7), (8, 8), (9, 15), (16, 16), (17, 40), (40, 17)]
+    if kind == "cells":
+        return [_plane(rng, 60, 300, small), _plane(rng, 40, 100, [(1, 64), (30, 30)])]
+    # a region of two tiles, one of one row wider than a tile, one near the split
+    return [_plane(rng, 250, 5000, small + [(100, 80), (64, 64), (1, 4800), (110, 200)])]
+
+
+def _device(pairs):
+    import torch
+    return [(torch.from_numpy(i.view(np.int16)).cuda(), torch.from_numpy(l.view(np.int32)).cuda()) for i, l in pairs]
+
+
+def _same(got, want, fp64):
+    """Against the column's largest value (FP64 1e-9, FP32 1e-5); at least 1 for
+    the unit-scale features, and the bound CLUPROM^(3/4) of the cluster shade's
+    terms for the shade, as its signed terms cancel."""
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    g, w = got.reshape(-1, 30).astype(np.float64), want.reshape(-1, 30)
+    top = np.nanmax(np.abs(w), axis=0)
+    top[UNIT] = np.maximum(top[UNIT], 1.0)
+    top[CLUSHADE] = max(top[CLUSHADE], top[CLUPROM] ** 0.75)
+    err = np.nan_to_num(np.abs(g - w)) / np.maximum(top, 1e-30)
+    assert err.max() <= (1e-9 if fp64 else 1e-5), np.unravel_index(err.argmax(), err.shape)
+
+
+def _want(nyx, ctx, images, bins, offs, symmetric):
+    rois, _ = nyx.nyx_bin_rois(ctx, images, bins)
+    counts = nyx.nyx_glcm_accumulate(ctx, images, rois, bins, offs, symmetric=symmetric)
+    return nyx.nyx_glcm_features(ctx, counts, nyx.NYX_FP64).cpu().numpy()
+
+
+CASES = [(k, b, o, s) for k in ("cells", "large") for b in (64, 128, 256, 512, 1024, 2047) for o, s in
+         ((FLAT, True), (TURNED, False), (FAR, b % 512 > 0))] + [("volume", b, DEEP, True) for b in (129, 700)] + \
+        [("cells", b, FLAT, True) for b in (2048, 4095, 4096)]
+
+
+@pytest.mark.parametrize("fp64", [True, False])
+@pytest.mark.parametrize("kind,bins,offs,symmetric", CASES)
+def test_features_of_the_counts(kind, bins, offs, symmetric, fp64):
+    import torch
+    from paper_2603_12016_amd import nyx
+    print(kind, bins, len(offs), symmetric, fp64, flush=True)
+    prec = nyx.NYX_FP64 if fp64 else 0
+    ctx, images = nyx.nyx_create(0), _device(_images(kind))
+    torch.cuda.synchronize()
+    want = _want(nyx, ctx, images, bins, offs, symmetric)
+    plan = nyx.nyx_plan_create(ctx, images, bins, offs, prec, symmetric=symmetric)
+    print(nyx.nyx_plan_describe(plan), flush=True)
+    table = nyx.new_table(plan, len(offs), prec)
+    for _ in range(3):
+        table.fill_(-7.0)
+        nyx.nyx_plan_execute(plan, table)
+    nyx.nyx_plan_check(plan)
+    _same(table.cpu().numpy(), want, fp64)
+
+
+@pytest.mark.parametrize("bins", [256, 1000])
+def test_plan_on_other_regions(bins):
+    """Small compact regions when the plan is made; then the same labels as long
+    diagonal bands (boxes far larger than the region, tiles of the box larger
+    than a table), and back."""
+    import torch
+    from paper_2603_12016_amd import nyx
+    rng = np.random.default_rng(bins)
+    n = 600
+    I = rng.integers(0, 60000, (1, n, n)).astype(np.uint16)
+    y, x = np.mgrid[0:n, 0:n]
+    first = np.zeros((1, n, n), np.uint32)
+    other = np.zeros((1, n, n), np.uint32)
+    for k in range(6):
+        first[0, 20 * k:20 * k + 15, 7:40] = k + 1
+        other[0][(y + x >= 150 * k + 100) & (y + x < 150 * k + 103)] = k + 1
+    first[0, 300:500, 100:230] = 7       # (one region of several tiles, so that the plan has room for split ones)
+    other[0][(y - x > 380)] = 7
+    first[0, 500, 500] = other[0, 0, 0] = 8
+    ctx, images = nyx.nyx_create(0), _device([(I, first)])
+    torch.cuda.synchronize()
+    plan = nyx.nyx_plan_create(ctx, images, bins, FLAT, nyx.NYX_FP64)
+    print(nyx.nyx_plan_describe(plan), flush=True)
+    table = nyx.new_table(plan, len(FLAT), nyx.NYX_FP64)
+    for labels in (first, other, first):
+        images[0][1].copy_(torch.from_numpy(labels.view(np.int32)))
+        torch.cuda.synchronize()
+        want = _want(nyx, ctx, images, bins, FLAT, True)
+        table.fill_(-7.0)
+        nyx.nyx_plan_execute(plan, table)
+        nyx.nyx_plan_check(plan)
+        _same(table.cpu().numpy(), want, True)

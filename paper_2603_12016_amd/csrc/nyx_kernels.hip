@@ -1432,25 +1432,33 @@ __global__ __launch_bounds__(BS, VOL ? 4 : ((BS == 256 && sizeof(OutT) == 4) ? 5
 }
 
 // ------------------------------------------------------------------ banded ROIs
-// Large split ROIs whose triangle does not fit LDS (many levels): a work item
-// is one (ROI, direction, block of bbox rows); the work-group takes the
-// block's pairs of that direction (by the row sweep for an in-plane
-// distance-1 offset of a 2D image, else by gather) and counts every pair with
-// |i - j| <
-// band_w into an LDS band of ng x band_w 32-bit cells (cell (lo, hi) at
-// lo * band_w + hi - lo), the rare wider pairs straight into the ROI's
+// Large split ROIs of plans with many levels: a work item is one (ROI, set of
+// band_dirs directions, block of bbox rows); the work-group takes the block's
+// pairs of those directions (in-plane distance-1 offsets of a 2D image by one
+// row sweep, others by gather) and counts every pair with |i - j| < band_w
+// into an LDS band of ng x band_w 32-bit cells per direction (cell (lo, hi)
+// at lo * band_w + hi - lo), the rare wider pairs straight into the ROI's
 // global matrix; the band is then added once, cell by nonzero cell, into
 // the global matrix.  Smooth images put nearly every pair near the diagonal,
 // so a block of hundreds of thousands of voxels costs one merge of a few
 // thousand cells instead of one per small tile.  Tickets: one atomic per
-// work item, mapped onto the banded ROIs in list order.
+// work item, mapped onto the banded ROIs in list order.  Bound by the sweep
+// (a level and its LDS atomics per voxel and set) and, where the band is
+// narrow, by the wide pairs.  Region of 60 M voxels, 4 directions, whole step:
+// 1024 levels (one direction of 32 cells at a time) 1100 us with 2^18 voxels
+// an item, 1002 with an item per CU; 512 levels 833 one direction at a time,
+// 690 two; 256 levels 641 two, 600 four.  (16-bit cells, emptied every 2^15
+// voxels so that none overflows, took two directions at 1024 levels: 1313.)
 __global__ __launch_bounds__(1024) void k_band(StepArgs a) {
     extern __shared__ __align__(16) uint8_t smem[];
     uint32_t *band = reinterpret_cast<uint32_t *>(smem);
-    __shared__ uint32_t s_it[5];   // ROI row, direction, block, blocks, found
+    __shared__ uint32_t s_it[5];   // ROI row, first direction, block, blocks, found
     const uint32_t ng = (uint32_t)a.ng, B = a.band_w, lgB = 31u - (uint32_t)__builtin_clz(B);
-    const uint32_t cells = ng * B;
+    const uint32_t cells = ng * B;   // of one direction
+    const uint32_t n_sets = ((uint32_t)a.K + a.band_dirs - 1u) / a.band_dirs;
     const uint32_t nb = min(a.counters[C_NBAND], a.g_cap);
+    if (nb == 0u) return;
+    for (uint32_t i = threadIdx.x; i < a.band_dirs * cells; i += blockDim.x) band[i] = 0u;
     for (;;) {
         if (threadIdx.x == 0) {
             uint32_t t = atomicAdd(&a.counters[C_BAND_TICKET], 1u);
@@ -1460,9 +1468,9 @@ __global__ __launch_bounds__(1024) void k_band(StepArgs a) {
                 if (row >= a.roi_cap) continue;
                 const RoiDesc &rd = a.rois[row];
                 const uint32_t nrb = band_blocks(rd.rows, (uint32_t)(rd.x1 - rd.x0 + 1), a.band_tile);
-                const uint32_t items = nrb * (uint32_t)a.K;
+                const uint32_t items = nrb * n_sets;
                 if (t < items) {
-                    s_it[0] = row; s_it[1] = t / nrb; s_it[2] = t - (t / nrb) * nrb; s_it[3] = nrb; s_it[4] = 1u;
+                    s_it[0] = row; s_it[1] = t / nrb * a.band_dirs; s_it[2] = t - (t / nrb) * nrb; s_it[3] = nrb; s_it[4] = 1u;
                     break;
                 }
                 t -= items;
@@ -1471,7 +1479,7 @@ __global__ __launch_bounds__(1024) void k_band(StepArgs a) {
         __syncthreads();
         if (s_it[4] == 0u) break;
         const uint32_t row = s_it[0], nrb = s_it[3];
-        const int d = (int)s_it[1];
+        const int d0 = (int)s_it[1], d1 = min(a.K, d0 + (int)a.band_dirs);
         const uint32_t blk = s_it[2];
         const RoiDesc rd = a.rois[row];
         __syncthreads();   // every thread has read s_it before thread 0 rewrites it
@@ -1483,8 +1491,6 @@ __global__ __launch_bounds__(1024) void k_band(StepArgs a) {
                    rd.x0 > rd.x1 || rd.y0 > rd.y1 || rd.z0 > rd.z1);
         }
         if (!ok) continue;   // uniform: every thread skips the item
-        for (uint32_t i = threadIdx.x; i < cells; i += blockDim.x) band[i] = 0u;
-        __syncthreads();
         ItemCtx c;
         c.I = im.I; c.L = im.L; c.B = im.B;
         c.nx = im.nx; c.ny = im.ny; c.nz = im.nz;
@@ -1494,36 +1500,54 @@ __global__ __launch_bounds__(1024) void k_band(StepArgs a) {
         const uint32_t W = (uint32_t)(rd.x1 - rd.x0 + 1);
         const uint32_t rpb = (rd.rows + nrb - 1u) / nrb;
         const uint32_t ra = min(blk * rpb, rd.rows), rb = min(ra + rpb, rd.rows);
-        uint64_t *G = a.G + ((uint64_t)rd.gslot * a.K_out + (a.merged ? 0 : d)) * (uint64_t)ng * ng;
-        auto add = [&](uint32_t, uint32_t la, uint32_t, uint32_t lb, uint32_t) {
+        uint64_t *G = a.G + ((uint64_t)rd.gslot * a.K_out + (a.merged ? 0 : d0)) * (uint64_t)ng * ng;
+        const uint64_t step = a.merged ? 0u : (uint64_t)ng * ng;   // to the next direction's matrix
+        auto add = [&](uint32_t dl, uint32_t la, uint32_t, uint32_t lb, uint32_t) NYX_INLINE {
             const uint32_t lo = (la < lb ? la : lb) - 1u, hi = (la < lb ? lb : la) - 1u;
-            if (hi - lo < B)
-                atomicAdd(&band[(lo << lgB) + hi - lo], 1u);
-            else
-                atomicAdd(reinterpret_cast<unsigned long long *>(&G[(uint64_t)lo * ng + hi]), 1ull);
-        };
-        // an in-plane distance-1 offset of a 2D image: the row sweep (each
-        // voxel's level once, neighbours by lane exchange); others: gather
-        const int32_t oz = a.off[d][0], oy = a.off[d][1], ox = a.off[d][2];
-        int cls = -1;
-        if (im.nz == 1 && !c.B && oz == 0 && (oy | ox) != 0 && oy >= -1 && oy <= 1 && ox >= -1 && ox <= 1)
-            cls = oy == 0 ? 0 : (ox == 0 ? 1 : (oy * ox < 0 ? 2 : 3));
-        if (ra < rb) {
-            if (cls >= 0) {
-                const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-                accumulate_sweep2d<false>(rd, c, ra, rb, 0u, W, cls == 0 ? 0 : -1, cls == 1 ? 0 : -1,
-                                          cls == 2 ? 0 : -1, cls == 3 ? 0 : -1, w, (int)(blockDim.x / kWave),
-                                          NoRowOff{}, add);
+            if (hi - lo < B) {
+                atomicAdd(&band[dl * cells + (lo << lgB) + hi - lo], 1u);
             } else {
-                accumulate_rows(a, rd, c, ra, rb, 0u, W, d, d + 1, threadIdx.x, blockDim.x, add);
+                atomicAdd(reinterpret_cast<unsigned long long *>(&G[dl * step + (uint64_t)lo * ng + hi]), 1ull);
+            }
+        };
+        // in-plane distance-1 offsets of a 2D image: one row sweep (each
+        // voxel's level once, neighbours by lane exchange); others: gather
+        int slot[4] = {-1, -1, -1, -1};
+        uint32_t gather = 0u;
+        for (int d = d0; d < d1; ++d) {
+            const int32_t oz = a.off[d][0], oy = a.off[d][1], ox = a.off[d][2];
+            int cls = -1;
+            if (im.nz == 1 && !c.B && oz == 0 && (oy | ox) != 0 && oy >= -1 && oy <= 1 && ox >= -1 && ox <= 1)
+                cls = oy == 0 ? 0 : (ox == 0 ? 1 : (oy * ox < 0 ? 2 : 3));
+            bool taken = false;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (k == cls && slot[k] < 0) { slot[k] = d - d0; taken = true; }
+            if (!taken) gather |= 1u << (d - d0);
+        }
+        if (ra < rb) {
+            if (slot[0] >= 0 || slot[1] >= 0 || slot[2] >= 0 || slot[3] >= 0)
+                accumulate_sweep2d<false>(rd, c, ra, rb, 0u, W, slot[0], slot[1], slot[2], slot[3],
+                                          __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)),
+                                          (int)(blockDim.x / kWave), NoRowOff{}, add);
+            for (uint32_t m = gather; m; m &= m - 1u) {
+                const int dl = __builtin_ctz(m);
+                auto add_one = [&](uint32_t, uint32_t la, uint32_t ta, uint32_t lb, uint32_t tb) NYX_INLINE {
+                    add((uint32_t)dl, la, ta, lb, tb);
+                };
+                accumulate_rows(a, rd, c, ra, rb, 0u, W, d0 + dl, d0 + dl + 1, threadIdx.x, blockDim.x, add_one);
             }
         }
         __syncthreads();
-        for (uint32_t i = threadIdx.x; i < cells; i += blockDim.x) {
-            const uint32_t v = band[i];
-            if (v) {
+        for (int dl = 0; dl < d1 - d0; ++dl) {
+            uint32_t *bd = band + (uint32_t)dl * cells;
+            uint64_t *Gd = G + (uint64_t)dl * step;
+            for (uint32_t i = threadIdx.x; i < cells; i += blockDim.x) {
+                const uint32_t v = bd[i];
+                if (v == 0u) continue;
+                bd[i] = 0u;
                 const uint32_t lo = i >> lgB, hi = lo + (i & (B - 1u));
-                atomicAdd(reinterpret_cast<unsigned long long *>(&G[(uint64_t)lo * ng + hi]), (unsigned long long)v);
+                atomicAdd(reinterpret_cast<unsigned long long *>(&Gd[(uint64_t)lo * ng + hi]), (unsigned long long)v);
             }
         }
         __syncthreads();
@@ -2074,7 +2098,7 @@ static hipError_t set_feature_kernel_attrs() {
 
 hipError_t launch_band(const StepArgs &a, uint32_t grid, hipStream_t st) {
     if (a.band_vox == 0u || a.g_cap == 0u || grid == 0u) return hipSuccess;
-    const uint32_t lds = (uint32_t)a.ng * a.band_w * 4u;
+    const uint32_t lds = (uint32_t)a.ng * a.band_w * a.band_dirs * 4u;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_band),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;

@@ -64,8 +64,9 @@ constexpr size_t kPinBytes = 512u << 10, kPinUp = 128u << 10, kPinDown = kPinByt
 constexpr uint32_t kOnePassLabels = 1u << 17;
 // Banded accumulation (hash mode, symmetric matrices): ROIs above
 // kBandMinVox voxels (and above the split size), LDS band of at most
-// kBandLds bytes, work items of about kBandTile bbox voxels.
-constexpr uint32_t kBandMinVox = 32768u, kBandLds = 128u * 1024u, kBandTile = 256u * 1024u, kBandMinW = 8u;
+// kBandLds bytes, work items of at least about kBandTile bbox voxels, bands
+// of at least kBandWide levels per direction when several share a pass.
+constexpr uint32_t kBandMinVox = 32768u, kBandLds = 128u * 1024u, kBandTile = 64u * 1024u, kBandMinW = 8u, kBandWide = 32u;
 
 int log_level() {
     static int lvl = -1;
@@ -576,20 +577,51 @@ struct Config {
     uint32_t small_kp = 0, small_cap = 0;   // with this many directions per pass and slots per direction
     uint32_t band_vox = 0;   // ROIs above this go to the banded kernel (0: none)
     uint32_t band_w = 0;     // band width (power of two)
+    uint32_t band_dirs = 1;  // directions counted in one pass
 };
 
-// The banded kernel takes the large ROIs of hash-mode plans (triangle larger
-// than LDS) with symmetric matrices: band width = the largest power of two
-// whose ng x width 32-bit cells fit kBandLds.
-void set_band(Config &c, uint32_t ng) {
+// The banded kernel takes the large ROIs of hash-mode plans with symmetric
+// matrices: band width = the largest power of two whose ng x width 32-bit
+// cells fit kBandLds, for the most directions at once (each pass reads the
+// region again) that leave a band of kBandWide levels: a narrower one sends
+// too many pairs to global memory (60 M voxels at 1024 levels: the step took
+// 1002 us with one direction of 32 levels, 3212 with two of 16; at 512 levels
+// two of 32 took 690, one of 64 took 833).
+void set_band(Config &c, uint32_t ng, int K) {
     c.band_vox = 0u;
     c.band_w = 0u;
     if ((c.mode != 1 && c.mode != 4) || c.nonsym) return;
-    uint32_t w = 1u;
-    while (w * 2u <= ng && (uint64_t)ng * (w * 2u) * 4u <= kBandLds) w *= 2u;
-    if (w < kBandMinW) return;
-    c.band_w = w;
-    c.band_vox = std::max(c.split_vox, kBandMinVox);
+    for (int dirs : {4, 2, 1}) {
+        if (dirs > 1 && dirs > K) continue;
+        uint32_t w = 1u;
+        while (w * 2u <= ng && (uint64_t)ng * (w * 2u) * (uint32_t)dirs * 4u <= kBandLds) w *= 2u;
+        c.band_dirs = (uint32_t)dirs;
+        c.band_w = w;
+        if (w >= kBandWide) break;
+    }
+    if (c.band_w < kBandMinW) c.band_w = 0u;
+    else c.band_vox = std::max(c.split_vox, kBandMinVox);
+}
+
+// Voxels of a banded ROI's box per work item: as many as give every CU one
+// item, as a block ends in a merge of its nonzero cells into global memory
+// (one region of 60 M voxels, 1024 levels: 921 items of 2^18 voxels 535 us,
+// 256 items 435), at least kBandTile (one of 4 M voxels: the step took 312 us
+// at 2^18 voxels, 249 at 2^16).
+uint32_t band_tile(const Work &w, const Config &c, uint32_t n_cu, int K) {
+    if (c.band_vox == 0u) return kBandTile;
+    const uint32_t sets = ((uint32_t)K + c.band_dirs - 1u) / c.band_dirs;
+    uint64_t total = 0;
+    for (const RoiDesc &r : w.h_rois)
+        if (r.n > c.band_vox) total += (uint64_t)r.rows * (uint32_t)(r.x1 - r.x0 + 1);
+    uint64_t tile = std::max<uint64_t>(kBandTile, total * sets / n_cu);
+    for (; tile < total && tile < 0x40000000u; tile += tile / 16u) {
+        uint64_t items = 0;
+        for (const RoiDesc &r : w.h_rois)
+            if (r.n > c.band_vox) items += band_blocks(r.rows, (uint32_t)(r.x1 - r.x0 + 1), (uint32_t)tile) * (uint64_t)sets;
+        if (items <= n_cu) break;
+    }
+    return (uint32_t)std::min<uint64_t>(tile, 0x40000000u);
 }
 
 const char *mode_name(int m) {
@@ -743,7 +775,7 @@ Config packed_config(const nyx_ctx *ctx, const Work &w, uint32_t ng, int K, int 
         }
     }
     if (best.mode != 4) return best;
-    set_band(best, ng);
+    set_band(best, ng, K);
     if (!force_split) {
         // voxels and items by size class, as the device will bucket them
         double vox[kClasses] = {}, num[kClasses] = {};
@@ -876,7 +908,7 @@ std::vector<Config> candidate_configs(const nyx_ctx *ctx, const Work &w, uint32_
                 c.mode = 1; c.kp = kp; c.block = block; c.hash_cap = hc; c.split_vox = split; c.tile_vox = split;
                 c.list_cap = list_cap; c.force_split = force_split; c.tile_scale = tile_scale;
                 c.nonsym = nonsym ? 1 : 0;
-                set_band(c, ng);
+                set_band(c, ng, K);
                 out.push_back(c);
                 return out;
             }
@@ -907,9 +939,14 @@ Config default_config(const std::vector<Config> &cands, const Work &w, uint32_t 
         any_scan |= c.mode == 2 || c.mode == 3;
         any_hash |= c.mode == 4;
     }
-    if (any_hash && (tri > 16u * avg || !any_scan))
-        for (const Config &c : cands)
-            if (c.mode == 4) return c;
+    for (const Config &c : cands) {
+        if (c.mode != 4) continue;
+        // (the average of the regions that the banded kernel would leave it)
+        uint64_t vox = 0, n = 0;
+        for (const RoiDesc &r : w.h_rois)
+            if (!c.band_vox || r.n <= c.band_vox) { vox += r.n; ++n; }
+        if (!any_scan || tri > 16u * (n ? std::max<uint64_t>(1u, vox / n) : avg)) return c;
+    }
     const bool prefer_scan = any_scan && (any_hash || tri <= 8u * avg);
     // among the candidates of the preferred kind: fewest passes over the
     // voxels per work-group slot (passes / work-groups per CU); ties keep the
@@ -1089,7 +1126,8 @@ nyx_status setup_step(nyx_ctx *ctx, Work &w, const Config &cfg, const nyx_offset
     a.split_chunks = chunks;
     a.band_vox = cfg.band_vox;
     a.band_w = cfg.band_w;
-    a.band_tile = kBandTile;
+    a.band_dirs = cfg.band_dirs;
+    a.band_tile = band_tile(w, cfg, (uint32_t)ctx->n_cu, K);
     for (int k = 0; k < K; ++k) {
         a.off[k][0] = off[k].dz;
         a.off[k][1] = off[k].dy;
@@ -1194,12 +1232,12 @@ std::string describe(const Config &c, const nyx_plan *p, uint64_t items, uint32_
     char buf[640];
     snprintf(buf, sizeof buf,
              "mode=%s kp=%u copies=%u symmetric=%d block=%u grid=%u lds=%uB split_vox=%u tile_vox=%u tile_scale=%g "
-             "list_cap=%u hash_cap=%u small_cls=%u small_kp=%u small_cap=%u small_grid=%u small_lds=%uB band_vox=%u band_w=%u band_voxels=%llu rois=%u items=%llu split_rois=%u ng=%d K=%d "
+             "list_cap=%u hash_cap=%u small_cls=%u small_kp=%u small_cap=%u small_grid=%u small_lds=%uB band_vox=%u band_w=%u band_dirs=%u band_voxels=%llu rois=%u items=%llu split_rois=%u ng=%d K=%d "
              "tuned_ms=%.4f",
              mode_name(c.mode), c.kp, p->w.args.lds.copies, c.nonsym ? 0 : 1, c.block, p->grid, p->w.args.lds.bytes, c.split_vox,
              c.tile_vox, (double)c.tile_scale, c.list_cap, c.hash_cap, p->small_cls, p->small_cls ? c.small_kp : 0u,
              p->small_cls ? c.small_cap : 0u, p->small_cls ? p->small_grid : 0u, p->small_cls ? p->small_lds.bytes : 0u,
-             c.band_vox, c.band_w,
+             c.band_vox, c.band_w, c.band_dirs,
              (unsigned long long)band_voxels, p->w.n_rois,
              (unsigned long long)items,
              n_split, p->ng, p->K, (double)p->tuned_ms);

@@ -164,12 +164,12 @@ struct StepArgs {
     DirSumsY *dsums_y;          // roi_cap * K column-marginal sums (non-symmetric matrices only)
     int32_t nonsym;             // 1: ordered counts P = C (full ng x ng squares), 0: symmetric P = C + C^T
     uint32_t *split_roi;        // g_cap: ROI row of each split slot
-    // Banded accumulation of large split ROIs whose triangle does not fit LDS:
-    // ROIs above band_vox voxels (0: none) are counted by k_band, one
-    // (ROI, direction, block of bbox rows of about band_tile voxels) per work
-    // item, into an LDS band of ng x band_w cells (|i - j| < band_w, a power
-    // of two) merged once into the ROI's global matrix.
-    uint32_t band_vox, band_w, band_tile;
+    // Banded accumulation of large split ROIs: those above band_vox voxels
+    // (0: none) are counted by k_band, one (ROI, set of band_dirs directions,
+    // block of bbox rows of about band_tile voxels) per work item, into an LDS
+    // band of ng x band_w cells (|i - j| < band_w, a power of two) per
+    // direction, merged once into the ROI's global matrix.
+    uint32_t band_vox, band_w, band_dirs, band_tile;
     uint32_t *band_roi;         // g_cap: ROI rows of the banded ROIs
     // Reduced sums of split ROIs (symmetric matrices) in two passes: chunks
     // of rows of each global matrix in parallel (marginals and cell totals),

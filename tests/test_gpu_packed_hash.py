@@ -14,6 +14,7 @@ pytestmark = pytest.mark.gpu
 FLAT = [(0, 0, 1), (0, 1, 0), (0, 1, 1), (0, 1, -1)]
 TURNED = [(0, 0, -1), (0, 1, -1), (0, 1, 0), (0, -1, -1)]
 FAR = [(0, 0, -1), (0, 1, -1), (0, 1, 2), (0, 3, 0)]
+TWICE = [(0, 0, 1), (0, 1, 0), (0, 0, -1), (0, 1, 1), (0, 1, -1)]
 DEEP = [(0, 0, 1), (0, 1, 0), (1, 0, 0), (1, 1, -1), (-1, 1, 1)]
 CLUSHADE, CLUPROM = 3, 2
 UNIT = [6, 8, 12, 16, 17, 23, 26]     # CORR, the entropies and the information measures: error against 1
@@ -46,6 +47,12 @@ def _images(kind):
     small = [(1, 1), (1, 2), (2, 2), (5, 7), (8, 8), (9, 15), (16, 16), (17, 40), (40, 17)]
     if kind == "cells":
         return [_plane(rng, 60, 300, small), _plane(rng, 40, 100, [(1, 64), (30, 30)])]
+    if kind == "banded":
+        # regions the banded kernel takes: a frame around small ones, and a whole image
+        I, L = _plane(rng, 230, 420, small + [(1, 1)] * 9)
+        ramp = (np.arange(230)[:, None] * 40 + np.arange(420) * 25 + rng.integers(0, 90, (230, 420))).astype(np.uint16)
+        L[L == 0] = 100
+        return [(ramp[None], L), (I[:, :190, :190].copy(), np.full((1, 190, 190), 3, np.uint32))]
     # a region of two tiles, one of one row wider than a tile, one near the split
     return [_plane(rng, 250, 5000, small + [(100, 80), (64, 64), (1, 4800), (110, 200)])]
 
@@ -76,7 +83,8 @@ def _want(nyx, ctx, images, bins, offs, symmetric):
 
 CASES = [(k, b, o, s) for k in ("cells", "large") for b in (64, 128, 256, 512, 1024, 2047) for o, s in
          ((FLAT, True), (TURNED, False), (FAR, b % 512 > 0))] + [("volume", b, DEEP, True) for b in (129, 700)] + \
-        [("cells", b, FLAT, True) for b in (2048, 4095, 4096)]
+        [("cells", b, FLAT, True) for b in (2048, 4095, 4096)] + \
+        [("banded", b, o, True) for b in (200, 300, 512, 600, 1024, 2000) for o in (FLAT, FAR, TWICE)]
 
 
 @pytest.mark.parametrize("fp64", [True, False])

@@ -511,25 +511,47 @@ template <> __device__ __forceinline__ double mi_resum_threshold<double>() { ret
 constexpr uint32_t kWideLevels = 256u;
 template <class Src> struct is_tri_scan : std::false_type {};
 template <bool P> struct is_tri_scan<SrcTriScan<P>> : std::true_type {};
-// Marginals of one matrix, zeroed u32 LDS words: counters of 32 bits, or of
-// 16 bits two to a word (HALF: every marginal of the item stays below 2^16).
-template <bool HALF> struct Marg;
-template <> struct Marg<false> {
+// Marginals of one matrix, zeroed u32 LDS words: counters of 32 bits; those,
+// but the first and the last marginal (of equal length) in the halves of the
+// same words (kPair: these two stay below 2^16); or counters of 16 bits two to
+// a word (kHalf: every marginal of the item stays below 2^16).
+enum MargKind { kWords, kPair, kHalf };
+template <int KIND> struct Marg;
+template <> struct Marg<kWords> {
     uint32_t *w;
     __device__ __forceinline__ explicit Marg(uint32_t *w_) : w(w_) {}
+    // the marginal that begins after i counters; the last one of a set
     __device__ __forceinline__ Marg at(uint32_t i) const { return Marg(w + i); }
+    __device__ __forceinline__ Marg last(uint32_t i) const { return Marg(w + i); }
     __device__ __forceinline__ void add(uint32_t i, uint32_t v) const { atomicAdd(&w[i], v); }
     __device__ __forceinline__ uint32_t operator[](uint32_t i) const { return w[i]; }
-    // zeroes the first n counters
-    template <class Grp> __device__ __forceinline__ void clear(const Grp &g, uint32_t n) const {
+    // zeroes a set of n counters whose last marginal has ng
+    template <class Grp> __device__ __forceinline__ void clear(const Grp &g, uint32_t n, uint32_t) const {
         for (uint32_t i = (uint32_t)g.rank(); i < n; i += (uint32_t)g.size()) w[i] = 0u;
     }
 };
-template <> struct Marg<true> {
+struct MargUpper {   // the last marginal of a kPair set: upper halves
+    uint32_t *w;
+    __device__ __forceinline__ void add(uint32_t i, uint32_t v) const { atomicAdd(&w[i], v << 16); }
+    __device__ __forceinline__ uint32_t operator[](uint32_t i) const { return w[i] >> 16; }
+};
+template <> struct Marg<kPair> {
+    uint32_t *w;
+    __device__ __forceinline__ explicit Marg(uint32_t *w_) : w(w_) {}
+    __device__ __forceinline__ Marg<kWords> at(uint32_t i) const { return Marg<kWords>(w + i); }
+    __device__ __forceinline__ MargUpper last(uint32_t) const { return MargUpper{w}; }
+    __device__ __forceinline__ void add(uint32_t i, uint32_t v) const { atomicAdd(&w[i], v); }
+    __device__ __forceinline__ uint32_t operator[](uint32_t i) const { return w[i] & 0xFFFFu; }
+    template <class Grp> __device__ __forceinline__ void clear(const Grp &g, uint32_t n, uint32_t ng) const {
+        for (uint32_t i = (uint32_t)g.rank(); i < n - ng; i += (uint32_t)g.size()) w[i] = 0u;
+    }
+};
+template <> struct Marg<kHalf> {
     uint32_t *w;
     uint32_t off;            // first counter
     __device__ __forceinline__ explicit Marg(uint32_t *w_, uint32_t off_ = 0u) : w(w_), off(off_) {}
     __device__ __forceinline__ Marg at(uint32_t i) const { return Marg(w, off + i); }
+    __device__ __forceinline__ Marg last(uint32_t i) const { return at(i); }
     __device__ __forceinline__ void add(uint32_t i, uint32_t v) const {
         i += off;
         atomicAdd(&w[i >> 1], v << ((i & 1u) << 4));
@@ -537,8 +559,8 @@ template <> struct Marg<true> {
     __device__ __forceinline__ uint32_t operator[](uint32_t i) const {
         return (uint32_t)reinterpret_cast<const uint16_t *>(w)[off + i];
     }
-    // zeroes the first n counters of the whole set (off 0)
-    template <class Grp> __device__ __forceinline__ void clear(const Grp &g, uint32_t n) const {
+    // zeroes a set of n counters (off 0)
+    template <class Grp> __device__ __forceinline__ void clear(const Grp &g, uint32_t n, uint32_t) const {
         for (uint32_t i = (uint32_t)g.rank(); i < (n + 1u) >> 1; i += (uint32_t)g.size()) w[i] = 0u;
     }
 };
@@ -553,8 +575,8 @@ __device__ __forceinline__ void level_sweep(uint32_t r0, uint32_t gs, uint32_t n
         for (uint32_t u = 0; u < U; ++u) fn(i0 + u * gs, v[u]);
     }
 }
-template <uint32_t U, class M, class Fn>
-__device__ __forceinline__ void level_sweep(uint32_t r0, uint32_t gs, uint32_t n, const M &a, const M &b, Fn &&fn) {
+template <uint32_t U, class M, class N, class Fn>
+__device__ __forceinline__ void level_sweep(uint32_t r0, uint32_t gs, uint32_t n, const M &a, const N &b, Fn &&fn) {
     for (uint32_t i0 = r0; i0 < n; i0 += U * gs) {
         uint32_t v[U], w[U];
 #pragma unroll
@@ -575,9 +597,11 @@ __device__ __forceinline__ void level_sweep(uint32_t r0, uint32_t gs, uint32_t n
 // per-lane integer sums: double where every partial and total stays below
 // 2^53 (small work items; required by the batched reduction), uint64_t
 // otherwise.  Returns T (0: direction empty).
-template <class Acc, class ISum, class Grp, class Src, bool H>
+template <class Acc, class ISum, class Grp, class Src, int H>
 __device__ uint64_t dir_sums(const Grp &g, const Src &src, const Marg<H> &marg, uint32_t ng, DirSums *out) {
-    const Marg<H> R = marg, Sp = marg.at(ng), Sm = marg.at(3u * ng - 1u);
+    const Marg<H> R = marg;
+    const auto Sp = marg.at(ng);
+    const auto Sm = marg.last(3u * ng - 1u);
     static_assert(!Grp::kBatched || std::is_same<ISum, double>::value, "batched sums are exact doubles");
     const int r0 = g.rank(), gs = g.size();
     // One sweep over the nonzero cells: marginals and cell terms.  A cell
@@ -676,7 +700,7 @@ __device__ uint64_t dir_sums(const Grp &g, const Src &src, const Marg<H> &marg, 
     if (T == 0) {
         g.sync();
         if (r0 == 0) out->T = 0;
-        marg.clear(g, 4u * ng - 1u);
+        marg.clear(g, 4u * ng - 1u, ng);
         src.clear(g);
         g.sync();
         return 0;
@@ -751,7 +775,7 @@ __device__ uint64_t dir_sums(const Grp &g, const Src &src, const Marg<H> &marg, 
     }
     // Clean up for the next direction / item.
     g.sync();
-    marg.clear(g, 4u * ng - 1u);
+    marg.clear(g, 4u * ng - 1u, ng);
     src.clear(g);
     g.sync();
     return T;
@@ -763,7 +787,7 @@ __device__ uint64_t dir_sums(const Grp &g, const Src &src, const Marg<H> &marg, 
 // sum and difference marginals: ng, ng, 2 ng - 1 and ng), zeroed again on
 // return; *out and *outy receive the sums (the column-marginal ones in *outy).  Every total is
 // reduced value by value in exact integers or double.  Returns T.
-template <class Acc, class Grp, class Src, bool H>
+template <class Acc, class Grp, class Src, int H>
 __device__ uint64_t dir_sums_ns(const Grp &g, const Src &src, const Marg<H> &marg, uint32_t ng, DirSums *out,
                                 DirSumsY *outy) {
     const Marg<H> R = marg, Cm = marg.at(ng), Sp = marg.at(2u * ng), Sm = marg.at(4u * ng - 1u);
@@ -906,7 +930,7 @@ __device__ uint64_t dir_sums_ns(const Grp &g, const Src &src, const Marg<H> &mar
         out->MI = MI;
     }
     g.sync();
-    marg.clear(g, 5u * ng - 1u);
+    marg.clear(g, 5u * ng - 1u, 0u);
     src.clear(g);
     g.sync();
     return T;

@@ -1198,7 +1198,7 @@ __device__ __forceinline__ void accumulate_sweep3d(const RoiDesc &rd, const Item
 
 // One direction of a finished item: features (unsplit ROI) or a 64-bit
 // atomic merge into the ROI's global matrix (tile of a split ROI).
-template <class Acc, bool NS, bool H = false, class Src>
+template <class Acc, bool NS, int H = kWords, class Src>
 __device__ __forceinline__ void dir_or_flush(const StepArgs &a, const WaveGrp &g, const Src &s, bool split,
                                              const RoiDesc &rd, uint32_t roi, int d, uint32_t *MARG, uint32_t ng) {
     if (split) {
@@ -1227,8 +1227,10 @@ __device__ __forceinline__ void dir_or_flush(const StepArgs &a, const WaveGrp &g
 // layouts whose LDS leaves room for one work-group per CU only (eight waves
 // instead of four then share the CU's latency).  VOL: the 3D row sweep, with
 // neither the 2D sweep nor the staged ring; at most 128 VGPRs, so that two
-// work-groups of 512 threads fit a CU.
-template <int MODE, class OutT, bool NS, int BS, bool VOL>
+// work-groups of 512 threads fit a CU.  PAIR: marginals in shared words (a
+// kernel of its own: as a choice at run time it cost the smallest plans 1.5 us
+// of 43).
+template <int MODE, class OutT, bool NS, int BS, bool VOL, bool PAIR = false>
 __global__ __launch_bounds__(BS, VOL ? 4 : ((BS == 256 && sizeof(OutT) == 4) ? 5 : 1)) void k_batch(StepArgs a,
                                                                                       uint32_t direct_roi) {
     extern __shared__ __align__(16) uint8_t smem[];
@@ -1245,7 +1247,7 @@ __global__ __launch_bounds__(BS, VOL ? 4 : ((BS == 256 && sizeof(OutT) == 4) ? 5
     const uint32_t ng = (uint32_t)a.ng;
     constexpr bool ns = NS;   // ordered counts: squares, gather accumulation, four marginals
     constexpr bool half = MODE == 4;   // marginals of 16 bits (items are small)
-    const uint32_t marg_words = half ? ((ns ? 5u : 4u) * ng + 1u) >> 1 : (ns ? 5u : 4u) * ng;
+    const uint32_t marg_words = half ? ((ns ? 5u : 4u) * ng + 1u) >> 1 : (ns ? 5u : (PAIR ? 3u : 4u)) * ng;
     uint32_t *MARG = reinterpret_cast<uint32_t *>(smem + Ly.marg_off) + w * marg_words;
 
     // LDS starts clean and every item leaves it clean.
@@ -1400,13 +1402,13 @@ __global__ __launch_bounds__(BS, VOL ? 4 : ((BS == 256 && sizeof(OutT) == 4) ? 5
                     if constexpr (MODE == 4) {
                         SrcPacked s{reinterpret_cast<uint32_t *>(smem + Ly.u_off) + dl * Ly.hash_cap, slots,
                                     Ly.lvl_bits, Ly.cnt_bits};
-                        dir_or_flush<Acc, NS, true>(a, g, s, split, rd, roi, d0 + dl, MARG, ng);
+                        dir_or_flush<Acc, NS, kHalf>(a, g, s, split, rd, roi, d0 + dl, MARG, ng);
                     } else if constexpr (MODE == 2 || MODE == 3) {
                         SrcTriScan<MODE == 3> s{Ud, ns ? ng * ng : (ng * (ng + 1u)) >> 1,
                                                 reinterpret_cast<uint16_t *>(BUF) +
                                                     (uint32_t)w * scan_buf_entries(SrcTriScan<MODE == 3>::kPerRead),
                                                 Ly.copies, Ly.tri_pad, ns ? ng : 0u};
-                        dir_or_flush<Acc, NS>(a, g, s, split, rd, roi, a.merged ? 0 : d0 + dl, MARG, ng);
+                        dir_or_flush<Acc, NS, PAIR ? kPair : kWords>(a, g, s, split, rd, roi, a.merged ? 0 : d0 + dl, MARG, ng);
                     } else if constexpr (MODE == 0) {
                         SrcDenseList s{lst, n, Ud};
                         dir_or_flush<Acc, NS>(a, g, s, split, rd, roi, d0 + dl, MARG, ng);
@@ -1576,9 +1578,9 @@ __global__ __launch_bounds__(1024) void k_split_features(StepArgs a) {
     SrcSquare s{a.G + ((uint64_t)slot * K + d) * (uint64_t)ng * ng, ng, a.nonsym != 0};
     const uint64_t at = (uint64_t)roi * K + d;
     if (a.nonsym)
-        dir_sums_ns<Acc>(g, s, Marg<false>(R), ng, a.dsums + at, a.dsums_y + at);
+        dir_sums_ns<Acc>(g, s, Marg<kWords>(R), ng, a.dsums + at, a.dsums_y + at);
     else
-        dir_sums<Acc, uint64_t>(g, s, Marg<false>(R), ng, a.dsums + at);
+        dir_sums<Acc, uint64_t>(g, s, Marg<kWords>(R), ng, a.dsums + at);
 }
 
 // Split ROIs with symmetric matrices, first pass: one work-group per (slot,
@@ -1887,9 +1889,9 @@ __global__ __launch_bounds__(512) void k_coo_features(StepArgs a, const uint64_t
     SrcCoo src{keys + seg[s], vals + seg[s], (uint32_t)(seg[s + 1] - seg[s]),
                ((uint64_t)(s / K) << 38) | ((uint64_t)(s % K) << 32), ng, &a.counters[C_ERR], a.nonsym != 0};
     if (a.nonsym)
-        dir_sums_ns<Acc>(g, src, Marg<false>(R), ng, sums + s, sums_y + s);
+        dir_sums_ns<Acc>(g, src, Marg<kWords>(R), ng, sums + s, sums_y + s);
     else
-        dir_sums<Acc, uint64_t>(g, src, Marg<false>(R), ng, sums + s);
+        dir_sums<Acc, uint64_t>(g, src, Marg<kWords>(R), ng, sums + s);
 }
 
 // ================================================================== launchers
@@ -1990,16 +1992,18 @@ hipError_t launch_bin_image(const StepArgs &a, uint16_t *bins, uint64_t total_vo
     return hipSuccess;
 }
 
-template <int MODE, class OutT, bool NS, int BS, bool VOL>
+template <int MODE, class OutT, bool NS, int BS, bool VOL, bool PAIR = false>
 static hipError_t launch_batch_b(const StepArgs &a, uint32_t grid, uint32_t direct_roi, hipStream_t st) {
+    if constexpr (MODE == 3 && !NS && !PAIR)
+        if (a.lds.marg_pair) return launch_batch_b<MODE, OutT, NS, BS, VOL, true>(a, grid, direct_roi, st);
     static bool attr_done = false;
     if (!attr_done) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_batch<MODE, OutT, NS, BS, VOL>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_batch<MODE, OutT, NS, BS, VOL, PAIR>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
         attr_done = true;
     }
-    hipLaunchKernelGGL((k_batch<MODE, OutT, NS, BS, VOL>), dim3(grid), dim3(BS), a.lds.bytes, st, a, direct_roi);
+    hipLaunchKernelGGL((k_batch<MODE, OutT, NS, BS, VOL, PAIR>), dim3(grid), dim3(BS), a.lds.bytes, st, a, direct_roi);
     NYX_CHECK_LAUNCH();
     return hipSuccess;
 }

@@ -651,8 +651,9 @@ uint32_t u_words(int mode, uint32_t ng, bool nonsym = false) {
 // Marginal words per reducing wave: row, sum and difference marginals, plus
 // the column marginal of an ordered matrix.
 // (16-bit counters in the packed hash mode, whose items are small).
-uint32_t marg_words(uint32_t ng, bool nonsym, int mode = 0) {
-    const uint32_t n = (nonsym ? 5u : 4u) * ng;
+// (pair: row and difference marginals share words).
+uint32_t marg_words(uint32_t ng, bool nonsym, int mode = 0, bool pair = false) {
+    const uint32_t n = (nonsym ? 5u : (pair ? 3u : 4u)) * ng;
     return mode == 4 ? (n + 1u) / 2u : n;
 }
 
@@ -672,7 +673,7 @@ uint32_t packed_item_max(uint32_t ng) {
 
 // ring: reserve an LDS level ring for the staged accumulation, sized to the
 // LDS the work-group can take without lowering its occupancy.
-LdsLayout make_layout(const Config &c, uint32_t ng, int K, bool ring) {
+LdsLayout lay_out(const Config &c, uint32_t ng, int K, bool ring, bool pair) {
     LdsLayout L;
     memset(&L, 0, sizeof L);
     L.mode = (uint32_t)c.mode;
@@ -705,7 +706,8 @@ LdsLayout make_layout(const Config &c, uint32_t ng, int K, bool ring) {
     L.lcnt_off = take(c.kp * 4u);
     L.buf_off = take((c.mode == 2 || c.mode == 3) ? L.nwaves * scan_buf_entries(scan_cells(c.mode)) * 2u : 0u);
     L.marg_sets = std::min(L.nwaves, c.merged ? 1u : c.kp);   // one set per wave that reduces a matrix
-    L.marg_off = take(L.marg_sets * marg_words(ng, c.nonsym != 0, c.mode) * 4u);
+    L.marg_off = take(L.marg_sets * marg_words(ng, c.nonsym != 0, c.mode, pair) * 4u);
+    L.marg_pair = pair ? 1u : 0u;
     L.misc_off = take(128u * 4u);
     if ((c.mode == 2 || c.mode == 3) && !c.nonsym) L.ro_off = take((ng + 1u) * 4u);
     L.item_off = take((uint32_t)kTicketChunk * kItemBytes);
@@ -726,6 +728,21 @@ LdsLayout make_layout(const Config &c, uint32_t ng, int K, bool ring) {
 // Work-groups of the persistent kernel per CU for a given LDS footprint.
 uint32_t groups_per_cu(uint64_t lds_bytes) {
     return (uint32_t)std::min<uint64_t>(kMaxGroupsPerCu, kLdsBudget / std::max<uint64_t>(lds_bytes, 1u));
+}
+
+// The row and difference marginals of a symmetric matrix share words where
+// that lets a layout fit, or a second work-group onto a CU, and an unsplit
+// item's marginals (at most twice its voxels) stay below 2^16.  At 128 levels:
+// 4 directions two groups instead of one (2000 cells, batch kernel 104 us with
+// the best other split, 88 so), 8 directions 512 threads instead of 256 (4400
+// cells, distances 1 and 2: 696, 454).  From two groups to three it lost at
+// 100 levels (320, 363).
+LdsLayout make_layout(const Config &c, uint32_t ng, int K, bool ring) {
+    const LdsLayout L = lay_out(c, ng, K, ring, false);
+    if (c.mode != 3 || c.nonsym || c.merged || c.split_vox > 32767u || groups_per_cu(L.bytes) > 1u)
+        return L;
+    const LdsLayout P = lay_out(c, ng, K, ring, true);
+    return groups_per_cu(P.bytes) > groups_per_cu(L.bytes) ? P : L;
 }
 
 // Largest voxel count any work item can hold under a split rule.

@@ -135,6 +135,7 @@ struct LdsLayout {
     uint32_t list_cap;    // entries per direction list
     uint32_t hash_cap;    // slots: power of two (hash mode), or per direction (packed hash)
     uint32_t lvl_bits, cnt_bits;   // packed hash: a slot is hi level | lo level | count
+    uint32_t marg_pair;   // 1: row and difference marginals share words
     uint32_t item_max;    // packed hash: most voxels a table takes (room and cnt_bits)
     uint32_t u_off, list_off, lcnt_off, marg_off, feat_off, sums_off, misc_off, hkey_off, hcnt_off, buf_off;
     uint32_t item_off;    // staged descriptors of the current ticket (work-group kernel)

@@ -1,9 +1,9 @@
-"""The packed hash of many levels, the tickets and the ordered row sweep on the
-GPU: regions from one voxel to several tiles, plans at the edges of the key and
-count fields (level counts at powers of two, the largest it takes, and one
-beyond), planes and volumes, symmetric and ordered, against the features of the
-exact counts; and a plan whose images change under it to regions that its
-tables cannot take whole."""
+"""The packed hash of many levels, the tickets, the ordered row sweep, the banded
+regions and the shared marginal words on the GPU: regions from one voxel to
+several tiles, plans at the edges of the key and count fields (level counts at
+powers of two, the largest it takes, and one beyond), planes and volumes,
+symmetric and ordered, against the features of the exact counts; and a plan
+whose images change under it to regions that its tables cannot take whole."""
 from __future__ import annotations
 
 import numpy as np
@@ -12,6 +12,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 FLAT = [(0, 0, 1), (0, 1, 0), (0, 1, 1), (0, 1, -1)]
+RINGS = FLAT + [(0, 0, 2), (0, 2, 0), (0, 2, 2), (0, 2, -2)]
 TURNED = [(0, 0, -1), (0, 1, -1), (0, 1, 0), (0, -1, -1)]
 FAR = [(0, 0, -1), (0, 1, -1), (0, 1, 2), (0, 3, 0)]
 TWICE = [(0, 0, 1), (0, 1, 0), (0, 0, -1), (0, 1, 1), (0, 1, -1)]
@@ -84,6 +85,7 @@ def _want(nyx, ctx, images, bins, offs, symmetric):
 CASES = [(k, b, o, s) for k in ("cells", "large") for b in (64, 128, 256, 512, 1024, 2047) for o, s in
          ((FLAT, True), (TURNED, False), (FAR, b % 512 > 0))] + [("volume", b, DEEP, True) for b in (129, 700)] + \
         [("cells", b, FLAT, True) for b in (2048, 4095, 4096)] + \
+        [("cells", b, o, True) for b in (120, 126, 180) for o in (FLAT, RINGS)] + [("large", 128, RINGS, True)] + \
         [("banded", b, o, True) for b in (200, 300, 512, 600, 1024, 2000) for o in (FLAT, FAR, TWICE)]
 
 

@@ -17,6 +17,8 @@
 #include <hip/hip_runtime.h>
 #include <limits.h>
 
+#include <algorithm>
+
 #include "nyx_device.h"
 #include "nyx_features.h"
 #include "nyx_launch.h"
@@ -1752,7 +1754,7 @@ __global__ __launch_bounds__(1024) void k_split_finish(StepArgs a) {
 // Rows [0, n) with n = min(*n_ptr, n_cap) (n_cap without n_ptr).
 template <class OutT>
 __global__ __launch_bounds__(128, 4) void k_features(StepArgs a, const DirSums *ds, const DirSumsY *dsy,
-                                                  uint32_t n_cap, const uint32_t *n_ptr) {
+                                                  uint32_t n_cap, const uint32_t *n_ptr, uint32_t rpb) {
     extern __shared__ __align__(16) uint8_t smem[];
     // staged in the output precision: single-precision tables take half the
     // LDS, so twice as many work-groups fit a CU; they keep cluster shade and
@@ -1760,7 +1762,6 @@ __global__ __launch_bounds__(128, 4) void k_features(StepArgs a, const DirSums *
     constexpr bool kXd = sizeof(OutT) == 4;
     OutT *feat = reinterpret_cast<OutT *>(smem);
     const uint32_t K = (uint32_t)a.K_out;
-    const uint32_t rpb = blockDim.x / K;
     double *xd = reinterpret_cast<double *>(smem + (size_t)rpb * K * kNumFeat * sizeof(OutT));
     const uint32_t n = n_ptr ? min(*n_ptr, n_cap) : n_cap;
     const uint32_t row0 = blockIdx.x * rpb;
@@ -2143,11 +2144,15 @@ hipError_t launch_split_finalize(const StepArgs &a, hipStream_t st) {
 hipError_t launch_features(const StepArgs &a, const DirSums *ds, const DirSumsY *dsy, uint32_t n_cap,
                            const uint32_t *n_ptr, hipStream_t st) {
     if (n_cap == 0) return hipSuccess;
-    const uint32_t block = 128u, rpb = block / (uint32_t)a.K_out;
+    // Rows per work-group: as many as its lanes take, but no more than leave
+    // two work-groups per CU, as a thread writes its share of the rows' (K + 1)
+    // 30 features one after the other (80 regions in 3 work-groups: 26.5 us,
+    // in 80: 6.1; 2000 in 63: 27.3, in 667: 8.4).
+    const uint32_t block = 128u, rpb = std::max(1u, std::min(block / (uint32_t)a.K_out, n_cap / 512u));
     const uint32_t grid = (n_cap + rpb - 1u) / rpb;
     const uint32_t lds = rpb * (uint32_t)a.K_out * (a.fp64 ? kNumFeat * 8u : kNumFeat * 4u + 16u);
-    if (a.fp64) hipLaunchKernelGGL(k_features<double>, dim3(grid), dim3(block), lds, st, a, ds, dsy, n_cap, n_ptr);
-    else hipLaunchKernelGGL(k_features<float>, dim3(grid), dim3(block), lds, st, a, ds, dsy, n_cap, n_ptr);
+    if (a.fp64) hipLaunchKernelGGL(k_features<double>, dim3(grid), dim3(block), lds, st, a, ds, dsy, n_cap, n_ptr, rpb);
+    else hipLaunchKernelGGL(k_features<float>, dim3(grid), dim3(block), lds, st, a, ds, dsy, n_cap, n_ptr, rpb);
     NYX_CHECK_LAUNCH();
     return hipSuccess;
 }

@@ -191,6 +191,8 @@ struct nyx_ctx {
     int n_cu = 0;
     std::string err;
     hipStream_t capture_stream = nullptr;
+    hipStream_t side_stream = nullptr;    // a captured step's second branch, forked and joined by these events
+    hipEvent_t fork_event = nullptr, join_event = nullptr;
     uint8_t *scratch = nullptr;   // this device's no-allocation scratch (device address)
     Arena pool;                   // device block of the one-shot calls
     uint8_t *pin = nullptr;       // kPinBytes of pinned host memory for the calls' small copies
@@ -1185,11 +1187,22 @@ nyx_status set_outputs(nyx_ctx *ctx, StepArgs &a, nyx_roi_table *rois, void *tab
 
 // The batch kernel over the queue: one launch, or one for the larger size
 // classes and one, with a layout of its own, for the smaller.
-hipError_t launch_batches(const nyx_plan *p, hipStream_t st) {
+void release_streams(nyx_ctx *c) {
+    if (c->join_event) (void)hipEventDestroy(c->join_event);
+    if (c->fork_event) (void)hipEventDestroy(c->fork_event);
+    if (c->side_stream) (void)hipStreamDestroy(c->side_stream);
+    if (c->capture_stream) (void)hipStreamDestroy(c->capture_stream);
+}
+
+hipError_t launch_batch_main(const nyx_plan *p, hipStream_t st) {
     StepArgs a = p->w.args;
     if (p->small_cls) a.cls_lo = p->small_cls;
-    hipError_t e = launch_batch(a, p->grid, p->block, kNone, st);
-    if (e != hipSuccess || !p->small_cls) return e;
+    return launch_batch(a, p->grid, p->block, kNone, st);
+}
+
+hipError_t launch_batch_small(const nyx_plan *p, hipStream_t st) {
+    if (!p->small_cls) return hipSuccess;
+    StepArgs a = p->w.args;
     a.cls_lo = 0u;
     a.cls_hi = p->small_cls;
     a.tickets = C_TICKETS2;
@@ -1201,10 +1214,55 @@ hipError_t launch_batches(const nyx_plan *p, hipStream_t st) {
     return launch_batch(a, p->small_grid, 256u, kNone, st);
 }
 
+hipError_t launch_batches(const nyx_plan *p, hipStream_t st) {
+    const hipError_t e = launch_batch_main(p, st);
+    return e != hipSuccess ? e : launch_batch_small(p, st);
+}
+
+// The counting kernels of a captured step: the small size classes on a branch
+// of the graph of their own, beside the banded regions and the main launch
+// (they share no counters, and add to matrices and records of different
+// regions).  Started first, the work-groups with the large LDS layouts leave
+// room for some of the small ones; the other way round they found none.
+hipError_t launch_counting_forked(const nyx_plan *p, hipStream_t st) {
+    const nyx_ctx *ctx = p->ctx;
+    const StepArgs &a = p->w.args;
+    bool banded = false;
+    for (const RoiDesc &r : p->w.h_rois) banded |= a.band_vox != 0u && r.n > a.band_vox;
+    hipError_t e = hipEventRecord(ctx->fork_event, st);
+    if (e == hipSuccess) e = hipStreamWaitEvent(ctx->side_stream, ctx->fork_event, 0);
+    if (e == hipSuccess && banded) e = launch_band(a, (uint32_t)ctx->n_cu, st);
+    if (e == hipSuccess) e = launch_batch_main(p, st);
+    if (e == hipSuccess && !banded) e = launch_band(a, (uint32_t)ctx->n_cu, st);
+    if (e == hipSuccess) e = launch_batch_small(p, ctx->side_stream);
+    if (e == hipSuccess) e = hipEventRecord(ctx->join_event, ctx->side_stream);
+    if (e == hipSuccess) e = hipStreamWaitEvent(st, ctx->join_event, 0);
+    return e;
+}
+
+// Whether a captured step forks: the branch costs about 10 us of joins, so the
+// planned regions outside the small classes have to be worth it.  Step, one
+// stream and two, in us: 2000 cells of 100-5000 voxels at 256 levels 292 and
+// 248, at 512 levels 380 and 316; 10000 small regions and one of 60 M voxels
+// at 1024 levels 996 and 929; 8000 regions all in the small classes 201 and 211.
+bool worth_forking(const nyx_plan *p) {
+    if (!p->small_cls) return false;
+    const StepArgs &a = p->w.args;
+    uint64_t all = 0, large = 0;
+    for (const RoiDesc &r : p->w.h_rois) {
+        const uint32_t W = (uint32_t)(r.x1 - r.x0 + 1);
+        all += r.n;
+        if ((a.band_vox && r.n > a.band_vox) ||
+            (uint32_t)size_class(item_bound(r.n, r.rows, W, tiles_for(r.n, r.rows, W, a.split_vox, a.tile_vox))) >= p->small_cls)
+            large += r.n;
+    }
+    return large * 16u > all;
+}
+
 // The full step on a stream.  per_roi: one accumulation launch per ROI.
 // scanned: the label statistics are those of the discovery just made on this
 // stream (one-shot calls), so the images are not scanned again.
-nyx_status enqueue_step(nyx_plan *p, hipStream_t st, bool per_roi, bool scanned = false) {
+nyx_status enqueue_step(nyx_plan *p, hipStream_t st, bool per_roi, bool scanned = false, bool fork = false) {
     nyx_ctx *ctx = p->ctx;
     const StepArgs &a = p->w.args;
     if (scanned) {
@@ -1215,12 +1273,15 @@ nyx_status enqueue_step(nyx_plan *p, hipStream_t st, bool per_roi, bool scanned 
     }
     HIPC(ctx, launch_compact(a, 0u, 0xFFFFFFFFu, st));
     HIPC(ctx, launch_zero_split(a, st));
-    if (!per_roi) {
+    fork = fork && !per_roi && worth_forking(p);
+    if (fork) {
+        HIPC(ctx, launch_counting_forked(p, st));
+    } else if (!per_roi) {
         HIPC(ctx, launch_batches(p, st));
     } else {
         for (uint32_t r = 0; r < p->w.n_rois; ++r) HIPC(ctx, launch_batch(a, p->roi_tiles[r], p->block, r, st));
     }
-    HIPC(ctx, launch_band(a, (uint32_t)ctx->n_cu, st));
+    if (!fork) HIPC(ctx, launch_band(a, (uint32_t)ctx->n_cu, st));
     HIPC(ctx, launch_split_finalize(a, st));
     HIPC(ctx, launch_features(a, a.dsums, a.dsums_y, a.roi_cap, a.counters + C_NROIS, st));
     return NYX_OK;
@@ -1336,7 +1397,11 @@ nyx_status nyx_create(nyx_ctx **out, int device_ordinal) {
         return NYX_ERR_DEVICE;
     }
     c->pin = static_cast<uint8_t *>(pin);
-    if (hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking) != hipSuccess) {
+    if (hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking) != hipSuccess ||
+        hipStreamCreateWithFlags(&c->side_stream, hipStreamNonBlocking) != hipSuccess ||
+        hipEventCreateWithFlags(&c->fork_event, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&c->join_event, hipEventDisableTiming) != hipSuccess) {
+        release_streams(c);
         (void)hipHostFree(c->pin);
         delete c;
         return NYX_ERR_DEVICE;
@@ -1347,7 +1412,7 @@ nyx_status nyx_create(nyx_ctx **out, int device_ordinal) {
 
 void nyx_destroy(nyx_ctx *ctx) {
     if (!ctx) return;
-    if (ctx->capture_stream) (void)hipStreamDestroy(ctx->capture_stream);
+    release_streams(ctx);
     if (ctx->pool.base) (void)hipFree(ctx->pool.base);
     if (ctx->pin) (void)hipHostFree(ctx->pin);
     delete ctx;
@@ -1797,7 +1862,7 @@ nyx_status nyx_plan_execute(nyx_plan *p, nyx_roi_table *rois, void *table, nyx_s
         set_outputs(ctx, p->w.args, rois, table, p->w.n_rois);
         hipStream_t cs = ctx->capture_stream;
         HIPC(ctx, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-        nyx_status s = enqueue_step(p, cs, false);
+        nyx_status s = enqueue_step(p, cs, false, false, true);
         hipGraph_t g = nullptr;
         hipError_t e = hipStreamEndCapture(cs, &g);
         if (s != NYX_OK) { if (g) (void)hipGraphDestroy(g); return s; }

@@ -1247,7 +1247,7 @@ __global__ __launch_bounds__(BS, VOL ? 4 : ((BS == 256 && sizeof(OutT) == 4) ? 5
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));   // wave index: uniform
     const int K = a.K;
     const uint32_t ng = (uint32_t)a.ng;
-    constexpr bool ns = NS;   // ordered counts: squares, gather accumulation, four marginals
+    constexpr bool ns = NS;   // ordered counts: squares, four marginals
     constexpr bool half = MODE == 4;   // marginals of 16 bits (items are small)
     const uint32_t marg_words = half ? ((ns ? 5u : 4u) * ng + 1u) >> 1 : (ns ? 5u : (PAIR ? 3u : 4u)) * ng;
     uint32_t *MARG = reinterpret_cast<uint32_t *>(smem + Ly.marg_off) + w * marg_words;

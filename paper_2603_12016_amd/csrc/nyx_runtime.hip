@@ -758,9 +758,6 @@ uint64_t max_item_vox(const std::vector<RoiDesc> &rois, uint32_t split_vox, uint
     return m;
 }
 
-// Feasible LDS configurations for this workload, one per accumulation mode,
-// each with as many directions per pass as fit.  Dense triangles first; the
-// hash table only when no dense triangle fits.
 // Packed hash tables, one per direction of a pass, for items much smaller
 // than their triangle.  The main launch takes any item up to the split size;
 // items of the smaller size classes take a second one whose tables (and so
@@ -834,6 +831,9 @@ Config packed_config(const nyx_ctx *ctx, const Work &w, uint32_t ng, int K, int 
     return best;
 }
 
+// Feasible LDS configurations for this workload, one per accumulation mode,
+// each with as many directions per pass as fit.  Dense triangles first, then
+// the packed hash; the hash of 64-bit slots only when none of them fits.
 // merged: every offset counts into one LDS triangle in one pass, so only the
 // dense scan modes qualify, and packed 16-bit counters need K x (voxels of an
 // item) < 65536 (offered only when that bound leaves the load-balance tile
@@ -907,8 +907,8 @@ std::vector<Config> candidate_configs(const nyx_ctx *ctx, const Work &w, uint32_
         if (c.mode == 4) out.push_back(c);
     }
     if (!out.empty() || fixed >= kLdsBudget || merged || copies > 1u) return out;
-    // hash mode: items small enough that kp directions of pairs fill at most
-    // half the table
+    // hash of 64-bit slots: items small enough that kp directions of pairs fill
+    // at most half the table
     for (uint32_t kp = (uint32_t)K; kp >= 1u; --kp) {
         for (uint32_t hc = 1u << 14; hc >= 512u; hc >>= 1) {
             uint32_t per_dir = hc / (2u * kp);

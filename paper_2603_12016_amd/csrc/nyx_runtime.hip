@@ -346,7 +346,8 @@ nyx_status build_label_dict(nyx_ctx *ctx, Work &w, int32_t n, hipStream_t st) {
 
 // A one-shot call: its buffers come from the context's block, which earlier
 // calls have finished with (each waits for its stream before it returns, and
-// this guard waits where one fails on the way).
+// this guard waits where one fails on the way).  Made once the arguments are
+// found good and the context's device is the current one.
 struct OneShot {
     hipStream_t st;
     bool done = false;
@@ -1701,10 +1702,8 @@ nyx_status nyx_glcm_features(nyx_ctx *ctx, const nyx_glcm *glcm, const nyx_roi_t
 
 namespace {
 
-// Validation, ROI discovery and the untimed default configuration of a plan
-// (shared by nyx_plan_create and the no-allocation entry point).
-nyx_status plan_init(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_images, const nyx_extract_opts *opts,
-                     nyx_plan *p, hipStream_t st, std::vector<Config> &cands, Config &cfg) {
+// The arguments of a plan or of a whole pass.
+nyx_status validate_extract(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_images, const nyx_extract_opts *opts) {
     nyx_status s = validate_images(ctx, imgs, n_images);
     if (s != NYX_OK) return s;
     if ((s = validate_offsets(ctx, imgs, n_images, opts->offsets_host, opts->n_offsets)) != NYX_OK) return s;
@@ -1716,7 +1715,15 @@ nyx_status plan_init(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_images, cons
         return fail(ctx, NYX_ERR_INVALID, "aggregate must be NYX_AGG_PER_OFFSET or NYX_AGG_MERGED");
     if (opts->copies != 0 && opts->copies != 1 && opts->copies != 2 && opts->copies != 4)
         return fail(ctx, NYX_ERR_INVALID, "copies must be 0, 1, 2 or 4");
-    HIPC(ctx, hipSetDevice(ctx->device));
+    return NYX_OK;
+}
+
+// ROI discovery and the untimed default configuration of a plan, of validated
+// arguments on the context's device (shared by nyx_plan_create and the whole
+// passes).
+nyx_status plan_init(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_images, const nyx_extract_opts *opts,
+                     nyx_plan *p, hipStream_t st, std::vector<Config> &cands, Config &cfg) {
+    nyx_status s = NYX_OK;
     p->ctx = ctx;
     p->imgs.assign(imgs, imgs + n_images);
     p->K = opts->n_offsets;
@@ -1771,6 +1778,8 @@ nyx_status nyx_plan_create(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_images
     if (!ctx) return NYX_ERR_INVALID;
     if (!out || !opts) return fail(ctx, NYX_ERR_INVALID, "NULL argument");
     *out = nullptr;
+    nyx_status s = validate_extract(ctx, imgs, n_images, opts);
+    if (s != NYX_OK) return s;
     // The images may have been written on any stream: the plan's own stream
     // reads them from here on.
     HIPC(ctx, hipSetDevice(ctx->device));
@@ -1779,8 +1788,7 @@ nyx_status nyx_plan_create(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_images
     std::unique_ptr<nyx_plan> p(new nyx_plan());
     std::vector<Config> cands;
     Config cfg;
-    nyx_status s = plan_init(ctx, imgs, n_images, opts, p.get(), st, cands, cfg);
-    if (s != NYX_OK) return s;
+    if ((s = plan_init(ctx, imgs, n_images, opts, p.get(), st, cands, cfg)) != NYX_OK) return s;
     const bool merged = opts->aggregate == NYX_AGG_MERGED;
     const uint32_t copies0 = opts->copies > 0 ? (uint32_t)opts->copies : 1u;
     if (opts->autotune) {
@@ -1965,12 +1973,15 @@ nyx_status nyx_extract_batch(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_imag
         nyx_plan_destroy(p);
         return s;
     }
+    nyx_status s = validate_extract(ctx, imgs, n_images, opts);
+    if (s != NYX_OK) return s;
+    HIPC(ctx, hipSetDevice(ctx->device));
     OneShot call(ctx, st);
     nyx_plan p;
     p.w.use_arena(&ctx->pool);
     std::vector<Config> cands;
     Config cfg;
-    nyx_status s = plan_init(ctx, imgs, n_images, opts, &p, st, cands, cfg);
+    s = plan_init(ctx, imgs, n_images, opts, &p, st, cands, cfg);
     if (s == NYX_OK) s = configure(&p, cfg, opts);
     if (s != NYX_OK) return s;
     return call.end(extract_once(&p, rois, table, table_capacity_rows, st, true));
@@ -1982,7 +1993,10 @@ nyx_status nyx_extract_batch_noalloc(nyx_ctx *ctx, const nyx_image *imgs, int32_
     if (!ctx) return NYX_ERR_INVALID;
     if (!opts) return fail(ctx, NYX_ERR_INVALID, "NULL argument");
     if (!ctx->scratch) return fail(ctx, NYX_ERR_DEVICE, "no scratch address for device %d", ctx->device);
+    nyx_status s = validate_extract(ctx, imgs, n_images, opts);
+    if (s != NYX_OK) return s;
     hipStream_t st = (hipStream_t)stream;
+    HIPC(ctx, hipSetDevice(ctx->device));
     // every device buffer of the step is carved from this device's scratch
     Arena ar;
     ar.base = ctx->scratch;
@@ -1991,7 +2005,7 @@ nyx_status nyx_extract_batch_noalloc(nyx_ctx *ctx, const nyx_image *imgs, int32_
     p.w.use_arena(&ar);
     std::vector<Config> cands;
     Config cfg;
-    nyx_status s = plan_init(ctx, imgs, n_images, opts, &p, st, cands, cfg);
+    s = plan_init(ctx, imgs, n_images, opts, &p, st, cands, cfg);
     if (s == NYX_OK) s = configure(&p, cfg, opts);
     if (s != NYX_OK) {
         if (ar.wanted > ar.cap)

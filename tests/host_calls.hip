@@ -1,0 +1,284 @@
+// host_calls.hip -- test harness (not part of the library): the library's host
+// code on a HIP runtime of its own, without a GPU.  Device memory is host
+// memory, copies happen at once, and of the kernels only what the host reads
+// back takes place: the label maxima, the counters and the ROI descriptors,
+// which a check plants.  What the host does -- the current device of every
+// allocation, pinned copies that a stream has not been waited for, launches
+// and their arguments, captured and instantiated graphs -- is written down and
+// looked at by the checks.  Usage: host_calls CHECK; exit status 0: holds.
+#include <hip/hip_runtime.h>
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+#include <sys/mman.h>
+
+#include <functional>
+#include <map>
+#include <set>
+#include <string>
+#include <vector>
+
+#include "nyx.h"
+#include "nyx_types.h"
+
+using nyx::RoiDesc;
+using nyx::StepArgs;
+
+struct Launch {
+    std::string name;
+    const void *fn;
+    dim3 grid, block;
+    hipStream_t stream;
+    bool has_args;
+    StepArgs a;
+};
+
+namespace host {
+
+int device = 0;
+std::map<void *, size_t> memory;         // device allocations
+std::vector<int> alloc_device;           // current device of each
+uint8_t *pin = nullptr;
+size_t pin_bytes = 0;
+std::map<hipStream_t, int> pinned;       // copies from or to pinned memory not waited for
+// (a library's kernels are registered before this file's globals are made)
+std::map<const void *, std::string> &kernels() {
+    static std::map<const void *, std::string> m;
+    return m;
+}
+std::vector<Launch> launches;
+std::vector<const void *> occupancy;     // kernels whose occupancy was asked for
+hipStream_t capturing = nullptr;
+std::set<hipStream_t> captured;          // streams of the launches in the graph being captured
+std::vector<size_t> graph_streams;       // streams of each instantiated graph
+uint32_t max_label = 0;
+std::vector<RoiDesc> rois;
+
+RoiDesc box(uint32_t n, uint32_t rows, uint32_t width) {
+    RoiDesc r{};
+    r.n = n; r.rows = rows; r.vmax = 1000u;
+    r.x1 = (int)width - 1; r.y1 = (int)rows - 1;
+    r.n_tiles = 1u; r.tcols = 1u; r.gslot = nyx::kNone;
+    return r;
+}
+
+void emulate(const std::string &k, void **args) {
+    if (k.find("k_max_label") != std::string::npos) {
+        const int n = *static_cast<int *>(args[1]);
+        uint32_t *out = *static_cast<uint32_t **>(args[2]);
+        for (int i = 0; i < n; ++i) out[i] = max_label;
+    } else if (k.find("k_reset") != std::string::npos) {
+        memset(static_cast<StepArgs *>(args[0])->counters, 0, 4u * *static_cast<uint32_t *>(args[1]));
+    } else if (k.find("k_compact_write") != std::string::npos) {
+        const StepArgs &a = *static_cast<StepArgs *>(args[0]);
+        a.counters[nyx::C_NROIS] = (uint32_t)rois.size();
+        for (size_t r = 0; r < rois.size() && r < a.roi_cap; ++r) a.rois[r] = rois[r];
+    }
+}
+
+bool takes_step(const std::string &k) {
+    for (const char *s : {"k_batch", "k_band", "k_compact_write", "k_features"})
+        if (k.find(s) != std::string::npos) return true;
+    return false;
+}
+
+void *map_memory(size_t n) {
+    void *p = mmap(nullptr, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+    return p == MAP_FAILED ? nullptr : p;
+}
+
+bool is_pinned(const void *p) {
+    return pin && p >= static_cast<const void *>(pin) && p < static_cast<const void *>(pin + pin_bytes);
+}
+
+}  // namespace host
+
+// ------------------------------------------------------------ the runtime
+extern "C" {
+
+hipError_t hipGetDeviceCount(int *n) { *n = 2; return hipSuccess; }
+hipError_t hipSetDevice(int d) { host::device = d; return hipSuccess; }
+hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int) {
+    memset(p, 0, sizeof *p);
+    p->multiProcessorCount = 256;
+    return hipSuccess;
+}
+const char *hipGetErrorString(hipError_t) { return "error"; }
+hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipGetSymbolAddress(void **p, const void *) {
+    static void *s = host::map_memory(NYX_NOALLOC_SCRATCH_BYTES);
+    *p = s;
+    return hipSuccess;
+}
+hipError_t hipMalloc(void **p, size_t n) {
+    if (!(*p = host::map_memory(n))) return hipErrorOutOfMemory;
+    host::memory[*p] = n;
+    host::alloc_device.push_back(host::device);
+    return hipSuccess;
+}
+hipError_t hipFree(void *p) {
+    auto it = host::memory.find(p);
+    if (it != host::memory.end()) {
+        munmap(p, it->second);
+        host::memory.erase(it);
+    }
+    host::pinned.clear();   // (waits for the device)
+    return hipSuccess;
+}
+hipError_t hipHostMalloc(void **p, size_t n, unsigned int) {
+    host::pin = static_cast<uint8_t *>(*p = calloc(1, n));
+    host::pin_bytes = n;
+    return hipSuccess;
+}
+hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t st) {
+    memcpy(d, s, n);
+    if (host::is_pinned(d) || host::is_pinned(s)) ++host::pinned[st];
+    return hipSuccess;
+}
+hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) { memset(d, v, n); return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned int) {
+    *s = reinterpret_cast<hipStream_t>(malloc(16));
+    return hipSuccess;
+}
+hipError_t hipStreamDestroy(hipStream_t s) { free(s); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) { host::pinned.erase(s); return hipSuccess; }
+hipError_t hipDeviceSynchronize(void) { host::pinned.clear(); return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned int) { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *e) { *e = reinterpret_cast<hipEvent_t>(malloc(16)); return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t e) { free(e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { host::pinned.clear(); return hipSuccess; }
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 1.f; return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *f, int, size_t) {
+    host::occupancy.push_back(f);
+    *n = 2;
+    return hipSuccess;
+}
+hipError_t hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode) {
+    host::capturing = s;
+    host::captured.clear();
+    return hipSuccess;
+}
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t *g) {
+    host::capturing = nullptr;
+    *g = reinterpret_cast<hipGraph_t>(malloc(16));
+    return hipSuccess;
+}
+hipError_t hipGraphInstantiate(hipGraphExec_t *e, hipGraph_t, hipGraphNode_t *, char *, size_t) {
+    *e = reinterpret_cast<hipGraphExec_t>(malloc(16));
+    host::graph_streams.push_back(host::captured.size());
+    return hipSuccess;
+}
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t e) { free(e); return hipSuccess; }
+hipError_t hipGraphDestroy(hipGraph_t g) { free(g); return hipSuccess; }
+
+struct Config { dim3 grid, block; size_t shared; hipStream_t stream; };
+static Config pushed;
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t sh, hipStream_t st) {
+    pushed = Config{g, b, sh, st};
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *sh, hipStream_t *st) {
+    *g = pushed.grid; *b = pushed.block; *sh = pushed.shared; *st = pushed.stream;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t, hipStream_t st) {
+    const std::string &k = host::kernels()[f];
+    Launch l{k, f, g, b, st, host::takes_step(k), StepArgs{}};
+    if (l.has_args) l.a = *static_cast<StepArgs *>(args[0]);
+    host::launches.push_back(l);
+    if (host::capturing) host::captured.insert(st);
+    else host::emulate(k, args);
+    return hipSuccess;
+}
+void **__hipRegisterFatBinary(const void *) { static void *m; return &m; }
+void __hipUnregisterFatBinary(void **) {}
+void __hipRegisterFunction(void **, const void *f, char *, const char *name, unsigned int, void *, void *, dim3 *, dim3 *,
+                           int *) {
+    host::kernels()[f] = name;
+}
+void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
+
+}  // extern "C"
+
+// ----------------------------------------------------------------- checks
+namespace {
+
+int failures = 0;
+#define EXPECT(c)                                                        \
+    do {                                                                 \
+        if (!(c)) { printf("%s:%d: %s\n", __FILE__, __LINE__, #c); ++failures; } \
+    } while (0)
+
+const hipStream_t kStream = reinterpret_cast<hipStream_t>(0x1000);
+uint16_t *const kI = reinterpret_cast<uint16_t *>(0x10000);   // images are not read here
+uint32_t *const kL = reinterpret_cast<uint32_t *>(0x20000);
+nyx_offset kFlat[4] = {{0, 0, 1}, {0, 1, 0}, {0, 1, 1}, {0, 1, -1}};
+
+nyx_ctx *context(int dev = 0) {
+    nyx_ctx *c = nullptr;
+    EXPECT(nyx_create(&c, dev) == NYX_OK);
+    return c;
+}
+
+nyx_image image(int64_t ny, int64_t nx, int64_t nz = 1) {
+    nyx_image m{};
+    m.intensity = kI; m.labels = kL;
+    m.nz = nz; m.ny = ny; m.nx = nx;
+    return m;
+}
+
+nyx_extract_opts options(int bins, int K = 4) {
+    nyx_extract_opts o{};
+    o.n_bins = bins;
+    o.offsets_host = kFlat;
+    o.n_offsets = K;
+    o.symmetric = 1;
+    o.precision = NYX_FP32;
+    o.accum_mode = -1;
+    return o;
+}
+
+size_t pending() { return host::pinned.size(); }
+
+// The call makes its memory on the context's device, and none for arguments
+// that it refuses.
+void extract_device() {
+    nyx_ctx *c = context(1);
+    (void)hipSetDevice(0);
+    host::alloc_device.clear();
+    nyx_image im = image(64, 64);
+    nyx_extract_opts o = options(1);
+    nyx_roi_table t{};
+    int64_t n = 0;
+    t.n_rois_host = &n;
+    EXPECT(nyx_extract_batch(c, &im, 1, &o, &t, kI, 100, kStream) == NYX_ERR_INVALID);
+    EXPECT(host::alloc_device.empty());
+    o.n_bins = 16;
+    (void)hipSetDevice(0);
+    EXPECT(nyx_extract_batch(c, &im, 1, &o, &t, kI, 100, kStream) == NYX_OK);
+    EXPECT(!host::alloc_device.empty());
+    for (int d : host::alloc_device) EXPECT(d == 1);
+    nyx_destroy(c);
+}
+
+struct Check { const char *name; void (*run)(); };
+const Check kChecks[] = {
+    {"extract_device", extract_device},
+};
+
+}  // namespace
+
+int main(int argc, char **argv) {
+    for (const Check &c : kChecks)
+        if (argc == 2 && strcmp(argv[1], c.name) == 0) {
+            c.run();
+            return failures ? 1 : 0;
+        }
+    printf("no such check\n");
+    return 2;
+}

@@ -344,14 +344,29 @@ nyx_status build_label_dict(nyx_ctx *ctx, Work &w, int32_t n, hipStream_t st) {
     return NYX_OK;
 }
 
-// A one-shot call: its buffers come from the context's block, which earlier
-// calls have finished with (each waits for its stream before it returns, and
-// this guard waits where one fails on the way).  Made once the arguments are
-// found good and the context's device is the current one.
-struct OneShot {
+// Waits for a call's stream where the call fails on the way: copies from the
+// pinned memory and kernels on scratch that the next call uses, perhaps on
+// another stream, may be under way.
+struct CallGuard {
     hipStream_t st;
     bool done = false;
-    OneShot(nyx_ctx *ctx, hipStream_t s) : st(s) {
+    explicit CallGuard(hipStream_t s) : st(s) {}
+    ~CallGuard() {
+        if (!done) (void)hipStreamSynchronize(st);
+    }
+    // the call's result; on success it has waited itself
+    nyx_status end(nyx_status s) {
+        done = s == NYX_OK;
+        return s;
+    }
+};
+
+// A one-shot call: its buffers come from the context's block, which earlier
+// calls have finished with (each waits for its stream before it returns).
+// Made once the arguments are found good and the context's device is the
+// current one.
+struct OneShot : CallGuard {
+    OneShot(nyx_ctx *ctx, hipStream_t s) : CallGuard(s) {
         Arena &p = ctx->pool;
         const size_t want = std::min(std::max(p.demand + p.demand / 4u, kPoolMin), kPoolMax);
         if (!p.base || (p.demand > p.cap && want > p.cap)) {
@@ -368,13 +383,6 @@ struct OneShot {
         }
         p.spill = true;
         p.used = p.demand = p.wanted = 0;
-    }
-    ~OneShot() {
-        if (!done) (void)hipStreamSynchronize(st);
-    }
-    nyx_status end(nyx_status s) {
-        done = s == NYX_OK;
-        return s;
     }
 };
 
@@ -1997,6 +2005,7 @@ nyx_status nyx_extract_batch_noalloc(nyx_ctx *ctx, const nyx_image *imgs, int32_
     if (s != NYX_OK) return s;
     hipStream_t st = (hipStream_t)stream;
     HIPC(ctx, hipSetDevice(ctx->device));
+    CallGuard call(st);
     // every device buffer of the step is carved from this device's scratch
     Arena ar;
     ar.base = ctx->scratch;
@@ -2014,7 +2023,7 @@ nyx_status nyx_extract_batch_noalloc(nyx_ctx *ctx, const nyx_image *imgs, int32_
                         ar.wanted);
         return s;
     }
-    return extract_once(&p, rois, table, table_capacity_rows, st, true);
+    return call.end(extract_once(&p, rois, table, table_capacity_rows, st, true));
 }
 
 }  // extern "C"

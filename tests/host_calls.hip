@@ -266,9 +266,22 @@ void extract_device() {
     nyx_destroy(c);
 }
 
+// A batch whose label tables outgrow the fixed scratch is refused, and nothing
+// of the call is left to run.
+void noalloc_wait() {
+    nyx_ctx *c = context();
+    nyx_image im = image(3000, 3000);
+    nyx_extract_opts o = options(16);
+    host::max_label = 8000000u;
+    EXPECT(nyx_extract_batch_noalloc(c, &im, 1, &o, nullptr, kI, 100, kStream) == NYX_ERR_CAPACITY);
+    EXPECT(pending() == 0);
+    nyx_destroy(c);
+}
+
 struct Check { const char *name; void (*run)(); };
 const Check kChecks[] = {
     {"extract_device", extract_device},
+    {"noalloc_wait", noalloc_wait},
 };
 
 }  // namespace

@@ -1496,7 +1496,7 @@ nyx_status nyx_glcm_accumulate(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_im
     if (rois && rois->n_rois_host && *rois->n_rois_host != (int64_t)w.n_rois)
         return fail(ctx, NYX_ERR_INVALID, "ROI table has %lld rows, images have %u ROIs",
                     (long long)*rois->n_rois_host, w.n_rois);
-    if (bins) {
+    if (bins && w.n_rois) {   // (without a ROI nothing below waits for the copy)
         uint64_t off = 0;
         for (auto &d : w.h_imgs) { d.B = bins + off; off += d.nvox; }
         HIPC(ctx, copy_up(ctx, w.imgs.p, w.h_imgs.data(), sizeof(ImgDesc) * n_images, 0, st));

@@ -278,10 +278,24 @@ void noalloc_wait() {
     nyx_destroy(c);
 }
 
+// No label anywhere and a bin image: nothing is left to run either.
+void accumulate_wait() {
+    nyx_ctx *c = context();
+    nyx_image im = image(64, 64);
+    int64_t nnz = -1;
+    nyx_glcm out{};
+    out.nnz_host = &nnz;
+    EXPECT(nyx_glcm_accumulate(c, &im, 1, nullptr, kI, kFlat, 4, 1, 16, &out, kStream) == NYX_OK);
+    EXPECT(nnz == 0 && out.n_rois == 0);
+    EXPECT(pending() == 0);
+    nyx_destroy(c);
+}
+
 struct Check { const char *name; void (*run)(); };
 const Check kChecks[] = {
     {"extract_device", extract_device},
     {"noalloc_wait", noalloc_wait},
+    {"accumulate_wait", accumulate_wait},
 };
 
 }  // namespace

@@ -68,6 +68,10 @@ constexpr uint32_t kOnePassLabels = 1u << 17;
 // of at least kBandWide levels per direction when several share a pass.
 constexpr uint32_t kBandMinVox = 32768u, kBandLds = 128u * 1024u, kBandTile = 64u * 1024u, kBandMinW = 8u, kBandWide = 32u;
 
+// Most device memory the packed hash may take beyond the configuration it
+// takes the place of.
+constexpr uint64_t kPackedExtra = 1ull << 30;
+
 int log_level() {
     static int lvl = -1;
     if (lvl < 0) {
@@ -840,6 +844,60 @@ Config packed_config(const nyx_ctx *ctx, const Work &w, uint32_t ng, int K, int 
     return best;
 }
 
+// Item and split-slot counts implied by a configuration.
+void count_items(const std::vector<RoiDesc> &rois, const Config &c, uint64_t *items, uint32_t *n_split,
+                 std::vector<uint32_t> *tiles) {
+    uint64_t it = 0;
+    uint32_t ns = 0;
+    if (tiles) tiles->resize(rois.size());
+    for (size_t i = 0; i < rois.size(); ++i) {
+        const RoiDesc &r = rois[i];
+        const bool band = c.band_vox && r.n > c.band_vox;
+        Tiling t = tiles_for(r.n, r.rows, (uint32_t)(r.x1 - r.x0 + 1), c.split_vox, c.tile_vox);
+        uint32_t nt = band ? 0u : t.row_blocks * t.col_blocks;
+        it += nt;
+        if (nt > 1u || band || c.force_split) ++ns;
+        if (tiles) (*tiles)[i] = nt;
+    }
+    *items = it;
+    *n_split = ns;
+}
+
+// Device memory of a step's queue, matrices and records.
+uint64_t step_bytes(const Work &w, int K_out, uint32_t ng, bool nonsym, uint64_t items, uint32_t n_split) {
+    const uint64_t mats = (uint64_t)n_split * K_out, mats1 = (uint64_t)std::max<uint32_t>(n_split, 1u) * K_out;
+    const uint64_t records = (uint64_t)std::max<uint32_t>(w.n_rois, 1u) * K_out;
+    return (uint64_t)kClasses * std::max<uint64_t>(items, 1u) * 8u + mats * ng * ng * 8u + records * sizeof(DirSums) +
+           (nonsym ? records * sizeof(DirSumsY) : 16u) + n_split * 8u +
+           mats1 * (16u * ng + 32u + 8u * std::max(1u, ng / 8u));
+}
+
+// Whether the packed hash `c` may take the place of `d`, what else the levels
+// and regions fit.  Its tables hold fewer voxels, so it may split regions that
+// `d` takes whole, and each of them then costs its matrices in global memory,
+// cleared, merged into and reduced every pass at about 0.5 us a MB.  Measured
+// savings are 1.3e-6 us a triangle cell of every item and direction against
+// dense triangles, and 0.004 us an item and direction, or more, against 64-bit
+// slots; so the extra bytes may be about those cells, or 7 KB each.  (400
+// regions of 1100 voxels, one direction: 1100 levels 214 us in 64-bit slots and
+// 1952 split in packed tables, 2048 levels 259 and 5780; 400 regions of 20000
+// voxels among 30000 of 400 at 256 levels: 7039 us as triangles, 1441 packed
+// with the 400 split.)  limit: bytes that the step may take (0: no limit).
+bool packed_worth(const Work &w, const Config &c, const Config &d, uint32_t ng, int K, uint64_t limit) {
+    uint64_t items_c, items_d;
+    uint32_t split_c, split_d;
+    count_items(w.h_rois, c, &items_c, &split_c, nullptr);
+    count_items(w.h_rois, d, &items_d, &split_d, nullptr);
+    const uint64_t need_c = step_bytes(w, K, ng, c.nonsym != 0, items_c, split_c),
+                   need_d = step_bytes(w, K, ng, d.nonsym != 0, items_d, split_d);
+    if (need_c <= need_d) return true;
+    const uint64_t each = d.mode == 1 ? 7168u : mat_cells(ng, c.nonsym != 0);
+    return need_c - need_d <= std::min<uint64_t>(items_d * (uint64_t)K * each, kPackedExtra) &&
+           (limit == 0u || need_c <= limit);
+}
+
+Config default_config(const std::vector<Config> &cands, const Work &w, uint32_t ng, int K);
+
 // Feasible LDS configurations for this workload, one per accumulation mode,
 // each with as many directions per pass as fit.  Dense triangles first, then
 // the packed hash; the hash of 64-bit slots only when none of them fits.
@@ -848,10 +906,10 @@ Config packed_config(const nyx_ctx *ctx, const Work &w, uint32_t ng, int K, int 
 // item) < 65536 (offered only when that bound leaves the load-balance tile
 // size alone; 32-bit counters otherwise).  copies: privatised copies of each
 // dense scan triangle (list and hash modes keep one); tile_scale scales the
-// load-balance share above which ROIs are split.
+// load-balance share above which ROIs are split; limit: see packed_worth.
 std::vector<Config> candidate_configs(const nyx_ctx *ctx, const Work &w, uint32_t ng, int K, int force_split,
                                       uint32_t block, bool merged = false, uint32_t copies = 1u,
-                                      float tile_scale = 1.f, bool nonsym = false) {
+                                      float tile_scale = 1.f, bool nonsym = false, uint64_t limit = 0) {
     std::vector<Config> out;
     const uint32_t nw = block / kWave;
     const uint32_t tri = mat_cells(ng, nonsym);
@@ -911,14 +969,16 @@ std::vector<Config> candidate_configs(const nyx_ctx *ctx, const Work &w, uint32_
         }
     }
     out.insert(out.end(), later.begin(), later.end());
-    if (!merged && copies == 1u && packed_item_max(ng) > 0u) {
-        const Config c = packed_config(ctx, w, ng, K, force_split, block, lb, nonsym, tile_scale);
-        if (c.mode == 4) out.push_back(c);
+    if (merged || copies > 1u) return out;
+    Config packed;
+    if (packed_item_max(ng) > 0u) packed = packed_config(ctx, w, ng, K, force_split, block, lb, nonsym, tile_scale);
+    if (!out.empty()) {
+        if (packed.mode == 4 && packed_worth(w, packed, default_config(out, w, ng, K), ng, K, limit)) out.push_back(packed);
+        return out;
     }
-    if (!out.empty() || fixed >= kLdsBudget || merged || copies > 1u) return out;
     // hash of 64-bit slots: items small enough that kp directions of pairs fill
     // at most half the table
-    for (uint32_t kp = (uint32_t)K; kp >= 1u; --kp) {
+    for (uint32_t kp = (uint32_t)K; kp >= 1u && fixed < kLdsBudget; --kp) {
         for (uint32_t hc = 1u << 14; hc >= 512u; hc >>= 1) {
             uint32_t per_dir = hc / (2u * kp);
             if (per_dir < 64u) continue;
@@ -937,11 +997,12 @@ std::vector<Config> candidate_configs(const nyx_ctx *ctx, const Work &w, uint32_
                 c.list_cap = list_cap; c.force_split = force_split; c.tile_scale = tile_scale;
                 c.nonsym = nonsym ? 1 : 0;
                 set_band(c, ng, K);
-                out.push_back(c);
+                out.push_back(packed.mode == 4 && packed_worth(w, packed, c, ng, K, limit) ? packed : c);
                 return out;
             }
         }
     }
+    if (packed.mode == 4) out.push_back(packed);
     return out;
 }
 
@@ -1005,25 +1066,6 @@ nyx_status choose_config(nyx_ctx *ctx, const Work &w, uint32_t ng, int K, int fo
 bool is_mode(const Config &c, int mode, const std::vector<Config> &cands) {
     if (mode != 1) return c.mode == mode && mode != 4;
     return (c.mode == 1 || c.mode == 4) && (cands.front().mode == 1 || cands.front().mode == 4);
-}
-
-// Item and split-slot counts implied by a configuration.
-void count_items(const std::vector<RoiDesc> &rois, const Config &c, uint64_t *items, uint32_t *n_split,
-                 std::vector<uint32_t> *tiles) {
-    uint64_t it = 0;
-    uint32_t ns = 0;
-    if (tiles) tiles->resize(rois.size());
-    for (size_t i = 0; i < rois.size(); ++i) {
-        const RoiDesc &r = rois[i];
-        const bool band = c.band_vox && r.n > c.band_vox;
-        Tiling t = tiles_for(r.n, r.rows, (uint32_t)(r.x1 - r.x0 + 1), c.split_vox, c.tile_vox);
-        uint32_t nt = band ? 0u : t.row_blocks * t.col_blocks;
-        it += nt;
-        if (nt > 1u || band || c.force_split) ++ns;
-        if (tiles) (*tiles)[i] = nt;
-    }
-    *items = it;
-    *n_split = ns;
 }
 
 // Row-sweep eligibility: all images 2D and every offset of each pass one of
@@ -1117,9 +1159,7 @@ nyx_status setup_step(nyx_ctx *ctx, Work &w, const Config &cfg, const nyx_offset
     const uint64_t sums_bytes = (uint64_t)std::max<uint32_t>(w.n_rois, 1u) * K_out * sizeof(DirSums);
     const uint64_t sums_y_bytes =
         cfg.nonsym ? (uint64_t)std::max<uint32_t>(w.n_rois, 1u) * K_out * sizeof(DirSumsY) : 16u;
-    const uint64_t mats0 = (uint64_t)std::max<uint32_t>(n_split, 1u) * K_out;
-    uint64_t need = (uint64_t)kClasses * bucket_cap * 8u + g_bytes + sums_bytes + sums_y_bytes + n_split * 8u +
-                    mats0 * (16u * ng + 32u + 8u * std::max(1u, ng / 8u));
+    uint64_t need = step_bytes(w, K_out, ng, cfg.nonsym != 0, items, n_split);
     for (auto &b : w.tab) need += b.bytes;
     need += w.rois.bytes + w.counters.bytes;
     if (ws_bytes) *ws_bytes = (int64_t)need;
@@ -1726,6 +1766,23 @@ nyx_status validate_extract(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_image
     return NYX_OK;
 }
 
+// Bytes that a step's buffers may take: what the caller's cap, or a fixed
+// scratch (with room for the buffers' alignment), leaves beside the label
+// tables and ROI records; 0: no limit.
+uint64_t step_limit(const Work &w, const nyx_extract_opts *opts) {
+    uint64_t limit = 0;
+    if (opts->workspace_cap_bytes > 0) {
+        uint64_t used = w.rois.bytes + w.counters.bytes;
+        for (const DevBuf &b : w.tab) used += b.bytes;
+        limit = std::max<uint64_t>(1u, (uint64_t)opts->workspace_cap_bytes - std::min<uint64_t>(used, opts->workspace_cap_bytes));
+    }
+    if (const Arena *ar = w.rois.arena; ar && !ar->spill) {
+        const uint64_t used = Arena::up(ar->used) + 16u * 256u, left = used < ar->cap ? ar->cap - used : 1u;
+        limit = limit ? std::min(limit, left) : left;
+    }
+    return limit;
+}
+
 // ROI discovery and the untimed default configuration of a plan, of validated
 // arguments on the context's device (shared by nyx_plan_create and the whole
 // passes).
@@ -1743,7 +1800,8 @@ nyx_status plan_init(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_images, cons
     // the default plan: one copy (or the forced count) at the load-balance tile size
     const uint32_t copies0 = opts->copies > 0 ? (uint32_t)opts->copies : 1u;
     const bool nonsym = opts->symmetric == 0;
-    cands = candidate_configs(ctx, p->w, (uint32_t)p->ng, p->K, 0, 256, merged, copies0, 1.f, nonsym);
+    cands = candidate_configs(ctx, p->w, (uint32_t)p->ng, p->K, 0, 256, merged, copies0, 1.f, nonsym,
+                              step_limit(p->w, opts));
     if (cands.empty())
         return fail(ctx, NYX_ERR_UNSUPPORTED, "no LDS configuration fits n_bins=%d with %d offsets%s%s", p->ng, p->K,
                     merged ? " merged in one pass" : "", copies0 > 1u ? " with privatised copies" : "");
@@ -1806,7 +1864,8 @@ nyx_status nyx_plan_create(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_images
             for (float ts : {0.5f, 1.f, 2.f}) {
                 if (cp == copies0 && ts == 1.f) continue;
                 for (const Config &c :
-                     candidate_configs(ctx, p->w, (uint32_t)p->ng, p->K, 0, 256, merged, cp, ts, opts->symmetric == 0))
+                     candidate_configs(ctx, p->w, (uint32_t)p->ng, p->K, 0, 256, merged, cp, ts, opts->symmetric == 0,
+                                       step_limit(p->w, opts)))
                     if (cp == 1u || c.copies == cp) cands.push_back(c);
             }
         }

@@ -12,7 +12,7 @@
 #include <string.h>
 #include <sys/mman.h>
 
-#include <functional>
+#include <algorithm>
 #include <map>
 #include <set>
 #include <string>
@@ -51,7 +51,7 @@ std::vector<const void *> occupancy;     // kernels whose occupancy was asked fo
 hipStream_t capturing = nullptr;
 std::set<hipStream_t> captured;          // streams of the launches in the graph being captured
 std::vector<size_t> graph_streams;       // streams of each instantiated graph
-uint32_t max_label = 0;
+uint32_t max_label = 0;                  // of the images, at least the number of ROIs
 std::vector<RoiDesc> rois;
 
 RoiDesc box(uint32_t n, uint32_t rows, uint32_t width) {
@@ -66,7 +66,7 @@ void emulate(const std::string &k, void **args) {
     if (k.find("k_max_label") != std::string::npos) {
         const int n = *static_cast<int *>(args[1]);
         uint32_t *out = *static_cast<uint32_t **>(args[2]);
-        for (int i = 0; i < n; ++i) out[i] = max_label;
+        for (int i = 0; i < n; ++i) out[i] = std::max(max_label, (uint32_t)rois.size());
     } else if (k.find("k_reset") != std::string::npos) {
         memset(static_cast<StepArgs *>(args[0])->counters, 0, 4u * *static_cast<uint32_t *>(args[1]));
     } else if (k.find("k_compact_write") != std::string::npos) {
@@ -291,11 +291,53 @@ void accumulate_wait() {
     nyx_destroy(c);
 }
 
+bool described(const nyx_plan *p, const char *what) { return strstr(nyx_plan_describe(p), what) != nullptr; }
+
+// Many levels: a hash whose tables hold few voxels splits regions that the
+// other configuration takes whole, and every split region costs its matrices
+// in global memory.  It is not taken where these outgrow what it saves, nor
+// where a limit on the scratch takes the other one only.
+void packed_memory() {
+    nyx_ctx *c = context();
+    nyx_image im = image(2000, 2000);
+    int64_t n = 0;
+    for (int bins : {1100, 1500, 2048, 4096}) {
+        host::rois.assign(1000, host::box(bins == 4096 ? 300u : 1100u, 50u, 24u));
+        nyx_extract_opts o = options(bins, 1);
+        o.workspace_cap_bytes = 64 << 20;
+        nyx_plan *p = nullptr;
+        EXPECT(nyx_plan_create(c, &im, 1, &o, &p, &n) == NYX_OK);
+        if (p) EXPECT(described(p, "split_rois=0 "));
+        nyx_plan_destroy(p);
+        nyx_roi_table t{};
+        t.capacity = 1000;
+        EXPECT(nyx_extract_batch_noalloc(c, &im, 1, &o, &t, kI, 1000, kStream) == NYX_OK);
+    }
+    // a few split regions among many small ones: taken, but for a limit
+    host::rois.assign(20000, host::box(250u, 20u, 20u));
+    for (int k = 0; k < 40; ++k) host::rois[500 * k] = host::box(17000u, 160u, 120u);
+    nyx_image big[8];
+    for (nyx_image &b : big) b = image(2000, 2000);
+    for (int k = 0; k < 800; ++k) host::rois.push_back(host::box(16000u, 160u, 120u));
+    nyx_extract_opts o = options(256);
+    nyx_plan *p = nullptr;
+    EXPECT(nyx_plan_create(c, big, 8, &o, &p, &n) == NYX_OK);
+    if (p) EXPECT(described(p, "mode=hash") && described(p, "split_rois=40 "));
+    nyx_plan_destroy(p);
+    o.workspace_cap_bytes = 60 << 20;
+    p = nullptr;
+    EXPECT(nyx_plan_create(c, big, 8, &o, &p, &n) == NYX_OK);
+    if (p) EXPECT(described(p, "mode=dense") && described(p, "split_rois=0 "));
+    nyx_plan_destroy(p);
+    nyx_destroy(c);
+}
+
 struct Check { const char *name; void (*run)(); };
 const Check kChecks[] = {
     {"extract_device", extract_device},
     {"noalloc_wait", noalloc_wait},
     {"accumulate_wait", accumulate_wait},
+    {"packed_memory", packed_memory},
 };
 
 }  // namespace

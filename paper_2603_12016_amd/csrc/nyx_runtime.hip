@@ -622,21 +622,28 @@ void set_band(Config &c, uint32_t ng, int K) {
 // item, as a block ends in a merge of its nonzero cells into global memory
 // (one region of 60 M voxels, 1024 levels: 921 items of 2^18 voxels 535 us,
 // 256 items 435), at least kBandTile (one of 4 M voxels: the step took 312 us
-// at 2^18 voxels, 249 at 2^16).
+// at 2^18 voxels, 249 at 2^16).  Where regions smaller than a CU's share make
+// that uneven, half a share, so that the tickets balance the work (a region of
+// 64 M voxels beside 20 of 40000, 600 levels, k_band: 643 us with 256 items in
+// all, 497 with half shares, 535 with 2^18 voxels; beside 300 at 1024 levels
+// the whole step took 29.0 ms with the large region in one item, 4.8 so).
 uint32_t band_tile(const Work &w, const Config &c, uint32_t n_cu, int K) {
     if (c.band_vox == 0u) return kBandTile;
     const uint32_t sets = ((uint32_t)K + c.band_dirs - 1u) / c.band_dirs;
+    std::vector<std::pair<uint32_t, uint32_t>> box;   // rows and width of the banded ROIs
     uint64_t total = 0;
     for (const RoiDesc &r : w.h_rois)
-        if (r.n > c.band_vox) total += (uint64_t)r.rows * (uint32_t)(r.x1 - r.x0 + 1);
-    uint64_t tile = std::max<uint64_t>(kBandTile, total * sets / n_cu);
-    for (; tile < total && tile < 0x40000000u; tile += tile / 16u) {
+        if (r.n > c.band_vox) {
+            box.emplace_back(r.rows, (uint32_t)(r.x1 - r.x0 + 1));
+            total += (uint64_t)r.rows * box.back().second;
+        }
+    const uint64_t share = std::min<uint64_t>(std::max<uint64_t>(kBandTile, total * sets / n_cu), 0x20000000u);
+    for (uint64_t tile = share; tile <= share + share / 8u && box.size() * sets <= n_cu; tile += tile / 16u) {
         uint64_t items = 0;
-        for (const RoiDesc &r : w.h_rois)
-            if (r.n > c.band_vox) items += band_blocks(r.rows, (uint32_t)(r.x1 - r.x0 + 1), (uint32_t)tile) * (uint64_t)sets;
-        if (items <= n_cu) break;
+        for (const auto &b : box) items += band_blocks(b.first, b.second, (uint32_t)tile) * (uint64_t)sets;
+        if (items <= n_cu) return (uint32_t)tile;
     }
-    return (uint32_t)std::min<uint64_t>(tile, 0x40000000u);
+    return (uint32_t)std::max<uint64_t>(kBandTile, share / 2u);
 }
 
 const char *mode_name(int m) {

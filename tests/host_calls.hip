@@ -332,12 +332,36 @@ void packed_memory() {
     nyx_destroy(c);
 }
 
+// Banded regions more than the CUs: the largest is still cut into its share.
+void band_blocks_of_many() {
+    nyx_ctx *c = context();
+    nyx_image im = image(8000, 10000);
+    int64_t n = 0;
+    host::rois.assign(300, host::box(40000u, 200u, 200u));
+    host::rois.push_back(host::box(60000000u, 8000u, 8000u));
+    nyx_extract_opts o = options(1024);
+    nyx_plan *p = nullptr;
+    EXPECT(nyx_plan_create(c, &im, 1, &o, &p, &n) == NYX_OK);
+    EXPECT(nyx_plan_execute(p, nullptr, kI, kStream) == NYX_OK);
+    int seen = 0;
+    for (const Launch &l : host::launches) {
+        if (l.name.find("k_band") == std::string::npos) continue;
+        ++seen;
+        const uint64_t sets = (4u + l.a.band_dirs - 1u) / l.a.band_dirs;
+        EXPECT(nyx::band_blocks(8000u, 8000u, l.a.band_tile) * sets >= 100u);
+    }
+    EXPECT(seen == 1);
+    nyx_plan_destroy(p);
+    nyx_destroy(c);
+}
+
 struct Check { const char *name; void (*run)(); };
 const Check kChecks[] = {
     {"extract_device", extract_device},
     {"noalloc_wait", noalloc_wait},
     {"accumulate_wait", accumulate_wait},
     {"packed_memory", packed_memory},
+    {"band_blocks_of_many", band_blocks_of_many},
 };
 
 }  // namespace

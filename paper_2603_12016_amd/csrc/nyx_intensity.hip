@@ -832,6 +832,18 @@ uint32_t intensity_tile_vox(uint64_t total_vox, uint32_t n_cu) {
     return (uint32_t)(t > kFoMinTile ? (t < (1u << 20) ? t : (1u << 20)) : kFoMinTile);
 }
 
+// Values of its range that a ROI may have per voxel where it is split: its
+// histogram is cleared, filled (past the LDS window by global atomics) and
+// walked four times, so a region of few voxels and many values is better taken
+// whole by one work-group.  Where the image alone does not fill the chip (tiles
+// of the least size) the walk competes with the whole region's latency, about
+// half of it a value of what it is a voxel; where it does, with its work.  Call
+// in us, values from 0 to 65000, split always, then by this rule: one
+// 2048 x 2048 image in regions of 4200 voxels 1602 and 311, of 20000 711 and
+// 472, of 60000 578 and 698 (whole: 868); eight in regions of 20000 3685 and
+// 858, of 60000 2355 and 1121, of 250000 1806 and 1742 (whole: 3381).
+uint32_t intensity_split_values(uint32_t tile_vox) { return tile_vox > kFoMinTile ? 1u : 2u; }
+
 hipError_t launch_intensity(const StepArgs &a, uint32_t items, uint32_t n_cu, int fp64, void *slots, void *sums,
                             void *table, uint32_t table_rows, hipStream_t st) {
     if (items == 0u || a.roi_cap == 0u) return hipSuccess;

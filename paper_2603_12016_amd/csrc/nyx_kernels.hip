@@ -408,7 +408,8 @@ __global__ __launch_bounds__(1024) void k_compact_write(StepArgs a, uint32_t roi
     const bool take = a.enqueue && row >= roi_lo && row < roi_hi;
     // banded ROIs get a global matrix but no work items of the batch kernel
     const bool band = a.band_vox != 0u && rd.n > a.band_vox;
-    const Tiling tl = tiles_for(rd.n, rd.rows, (uint32_t)(rd.x1 - rd.x0 + 1), a.split_vox, a.tile_vox);
+    Tiling tl = tiles_for(rd.n, rd.rows, (uint32_t)(rd.x1 - rd.x0 + 1), a.split_vox, a.tile_vox);
+    if (a.aux_values && (uint64_t)rd.n * a.aux_values < rd.vmax - rd.vmin + 1u) tl = Tiling{1u, 1u};
     nt = band ? 0u : tl.row_blocks * tl.col_blocks;
     rd.n_tiles = nt;
     rd.tcols = band ? 1u : tl.col_blocks;

@@ -33,6 +33,7 @@ hipError_t launch_coo_features(const StepArgs &a, const uint64_t *keys, const ui
 uint64_t intensity_slot_bytes(uint32_t n_split, uint32_t n_aux);
 uint64_t intensity_sums_bytes(uint32_t n_rois);
 uint32_t intensity_tile_vox(uint64_t total_vox, uint32_t n_cu);
+uint32_t intensity_split_values(uint32_t tile_vox);
 hipError_t launch_intensity(const StepArgs &a, uint32_t items, uint32_t n_cu, int fp64, void *slots, void *sums,
                             void *table, uint32_t table_rows, hipStream_t st);
 uint32_t neighbourhood_lds_bytes(uint32_t ng, int any_volume);

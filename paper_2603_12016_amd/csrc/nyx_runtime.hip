@@ -402,7 +402,7 @@ hipError_t copy_up(nyx_ctx *ctx, void *dst, const void *src, size_t n, size_t at
 // Tile queue asked of discovery: ROIs above tile_vox voxels are split.
 struct TileQueue {
     uint32_t tile_vox = 0;
-    int aux_values = 0;   // split ROIs get storage for one counter per value of their range
+    uint32_t aux_values = 0;   // StepArgs::aux_values
 };
 
 // Work queue of a family whose items are tiles of about tile_vox voxels: the
@@ -1628,7 +1628,8 @@ nyx_status nyx_intensity_features(nyx_ctx *ctx, const nyx_image *imgs, int32_t n
     HIPC(ctx, hipSetDevice(ctx->device));
     uint64_t vox = 0;
     for (int i = 0; i < n_images; ++i) vox += (uint64_t)(imgs[i].nz * imgs[i].ny * imgs[i].nx);
-    const TileQueue tq{intensity_tile_vox(vox, (uint32_t)ctx->n_cu), 1};
+    const uint32_t tile = intensity_tile_vox(vox, (uint32_t)ctx->n_cu);
+    const TileQueue tq{tile, intensity_split_values(tile)};
     OneShot call(ctx, st);
     Work w;
     w.use_arena(&ctx->pool);

@@ -190,7 +190,10 @@ struct StepArgs {
     uint32_t tile_vox;          // target voxels per tile of a split ROI
     int32_t force_split;        // 1: every ROI goes through the global matrices
     int32_t enqueue;            // 0: compaction builds the ROI table only
-    int32_t aux_values;         // 1: a split ROI gets a counter per value of its range (RoiDesc::aux)
+    // a split ROI gets a counter per value of its range (RoiDesc::aux), and a
+    // ROI is split only where it holds 1 / aux_values as many voxels (0: no
+    // such counters, and no such condition)
+    uint32_t aux_values;
     int32_t fp64;               // feature table element type
     void *table;
     uint32_t table_rows;

@@ -62,6 +62,11 @@ constexpr size_t kPinBytes = 512u << 10, kPinUp = 128u << 10, kPinDown = kPinByt
 // Discovery fills the ROI descriptors (and the tile queue) in one go, sized by
 // the label table, up to this many entries; above, the ROIs are counted first.
 constexpr uint32_t kOnePassLabels = 1u << 17;
+// Replays with the same outputs after which a plan's step is captured anew in
+// two branches: that costs about 210 us more than one branch does, what some
+// five replays give back (a caller that alternates two tables paid it on every
+// call: 359 us a step before there was a branch, 441 with it, 243 so).
+constexpr uint32_t kForkAfter = 4u;
 // Banded accumulation (hash mode, symmetric matrices): ROIs above
 // kBandMinVox voxels (and above the split size), LDS band of at most
 // kBandLds bytes, work items of at least about kBandTile bbox voxels, bands
@@ -233,9 +238,15 @@ struct nyx_plan {
     // second launch of the batch kernel (packed hash): the size classes below small_cls
     uint32_t small_cls = 0, small_kp = 0, small_grid = 0;
     LdsLayout small_lds{};
+    bool banded = false, fork = false; // a planned ROI is banded; a step that is repeated forks
     std::vector<uint32_t> roi_tiles;   // per-ROI tile count for the per-ROI path
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
+    // The step as a graph writing graph_table and graph_rois: of one branch,
+    // and of two once it has been replayed `replays` times.
+    struct Graph {
+        hipGraph_t graph = nullptr;
+        hipGraphExec_t exec = nullptr;
+    } plain, forked;
+    uint32_t replays = 0;
     void *graph_table = nullptr;
     nyx_roi_table graph_rois{};
     std::string desc;
@@ -1283,20 +1294,18 @@ hipError_t launch_batches(const nyx_plan *p, hipStream_t st) {
 hipError_t launch_counting_forked(const nyx_plan *p, hipStream_t st) {
     const nyx_ctx *ctx = p->ctx;
     const StepArgs &a = p->w.args;
-    bool banded = false;
-    for (const RoiDesc &r : p->w.h_rois) banded |= a.band_vox != 0u && r.n > a.band_vox;
     hipError_t e = hipEventRecord(ctx->fork_event, st);
     if (e == hipSuccess) e = hipStreamWaitEvent(ctx->side_stream, ctx->fork_event, 0);
-    if (e == hipSuccess && banded) e = launch_band(a, (uint32_t)ctx->n_cu, st);
+    if (e == hipSuccess && p->banded) e = launch_band(a, (uint32_t)ctx->n_cu, st);
     if (e == hipSuccess) e = launch_batch_main(p, st);
-    if (e == hipSuccess && !banded) e = launch_band(a, (uint32_t)ctx->n_cu, st);
+    if (e == hipSuccess && !p->banded) e = launch_band(a, (uint32_t)ctx->n_cu, st);
     if (e == hipSuccess) e = launch_batch_small(p, ctx->side_stream);
     if (e == hipSuccess) e = hipEventRecord(ctx->join_event, ctx->side_stream);
     if (e == hipSuccess) e = hipStreamWaitEvent(st, ctx->join_event, 0);
     return e;
 }
 
-// Whether a captured step forks: the branch costs about 10 us of joins, so the
+// Whether a captured step may fork: the branch costs about 10 us of joins, so the
 // planned regions outside the small classes have to be worth it.  Step, one
 // stream and two, in us: 2000 cells of 100-5000 voxels at 256 levels 292 and
 // 248, at 512 levels 380 and 316; 10000 small regions and one of 60 M voxels
@@ -1315,7 +1324,8 @@ bool worth_forking(const nyx_plan *p) {
     return large * 16u > all;
 }
 
-// The full step on a stream.  per_roi: one accumulation launch per ROI.
+// The full step on a stream.  per_roi: one accumulation launch per ROI; fork:
+// the counting kernels on two branches (into a capture only).
 // scanned: the label statistics are those of the discovery just made on this
 // stream (one-shot calls), so the images are not scanned again.
 nyx_status enqueue_step(nyx_plan *p, hipStream_t st, bool per_roi, bool scanned = false, bool fork = false) {
@@ -1329,7 +1339,6 @@ nyx_status enqueue_step(nyx_plan *p, hipStream_t st, bool per_roi, bool scanned 
     }
     HIPC(ctx, launch_compact(a, 0u, 0xFFFFFFFFu, st));
     HIPC(ctx, launch_zero_split(a, st));
-    fork = fork && !per_roi && worth_forking(p);
     if (fork) {
         HIPC(ctx, launch_counting_forked(p, st));
     } else if (!per_roi) {
@@ -1340,6 +1349,30 @@ nyx_status enqueue_step(nyx_plan *p, hipStream_t st, bool per_roi, bool scanned 
     if (!fork) HIPC(ctx, launch_band(a, (uint32_t)ctx->n_cu, st));
     HIPC(ctx, launch_split_finalize(a, st));
     HIPC(ctx, launch_features(a, a.dsums, a.dsums_y, a.roi_cap, a.counters + C_NROIS, st));
+    return NYX_OK;
+}
+
+void drop_graphs(nyx_plan *p) {
+    for (nyx_plan::Graph *g : {&p->plain, &p->forked}) {
+        if (g->exec) (void)hipGraphExecDestroy(g->exec);
+        if (g->graph) (void)hipGraphDestroy(g->graph);
+        *g = nyx_plan::Graph{};
+    }
+    p->graph_table = nullptr;
+}
+
+// A plan's step, with the outputs set, as a graph.
+nyx_status capture_step(nyx_plan *p, bool fork, nyx_plan::Graph *to) {
+    nyx_ctx *ctx = p->ctx;
+    hipStream_t cs = ctx->capture_stream;
+    HIPC(ctx, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
+    nyx_status s = enqueue_step(p, cs, false, false, fork);
+    hipGraph_t g = nullptr;
+    hipError_t e = hipStreamEndCapture(cs, &g);
+    if (s != NYX_OK) { if (g) (void)hipGraphDestroy(g); return s; }
+    if (e != hipSuccess) return fail(ctx, NYX_ERR_DEVICE, "graph capture: %s", hipGetErrorString(e));
+    to->graph = g;
+    HIPC(ctx, hipGraphInstantiate(&to->exec, g, nullptr, nullptr, 0));
     return NYX_OK;
 }
 
@@ -1408,6 +1441,9 @@ nyx_status configure(nyx_plan *p, const Config &cfg, const nyx_extract_opts *opt
     uint64_t items;
     uint32_t n_split;
     count_items(p->w.h_rois, cfg, &items, &n_split, &p->roi_tiles);
+    p->banded = false;
+    for (const RoiDesc &r : p->w.h_rois) p->banded |= cfg.band_vox != 0u && r.n > cfg.band_vox;
+    p->fork = worth_forking(p);
     p->cfg = nyx_plan::Cfg{cfg.mode, cfg.kp, cfg.block, cfg.split_vox, cfg.tile_vox, cfg.list_cap, cfg.hash_cap,
                            cfg.force_split};
     p->desc = describe(cfg, p, items, n_split);
@@ -1938,24 +1974,21 @@ nyx_status nyx_plan_execute(nyx_plan *p, nyx_roi_table *rois, void *table, nyx_s
     nyx_roi_table key{};
     if (rois) key = *rois;
     key.n_rois_host = nullptr;
-    bool same = p->exec && p->graph_table == table && memcmp(&key, &p->graph_rois, sizeof key) == 0;
-    if (!same) {
-        if (p->exec) { (void)hipGraphExecDestroy(p->exec); p->exec = nullptr; }
-        if (p->graph) { (void)hipGraphDestroy(p->graph); p->graph = nullptr; }
+    if (!p->plain.exec || p->graph_table != table || memcmp(&key, &p->graph_rois, sizeof key) != 0) {
+        drop_graphs(p);
         set_outputs(ctx, p->w.args, rois, table, p->w.n_rois);
-        hipStream_t cs = ctx->capture_stream;
-        HIPC(ctx, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-        nyx_status s = enqueue_step(p, cs, false, false, true);
-        hipGraph_t g = nullptr;
-        hipError_t e = hipStreamEndCapture(cs, &g);
-        if (s != NYX_OK) { if (g) (void)hipGraphDestroy(g); return s; }
-        if (e != hipSuccess) return fail(ctx, NYX_ERR_DEVICE, "graph capture: %s", hipGetErrorString(e));
-        p->graph = g;
-        HIPC(ctx, hipGraphInstantiate(&p->exec, g, nullptr, nullptr, 0));
+        nyx_status s = capture_step(p, false, &p->plain);
+        if (s != NYX_OK) return s;
         p->graph_table = table;
         p->graph_rois = key;
+        p->replays = 0;
+    } else if (p->fork && p->replays < kForkAfter && ++p->replays == kForkAfter) {
+        // (the plain graph stays: a replay of it may still be under way)
+        set_outputs(ctx, p->w.args, rois, table, p->w.n_rois);
+        nyx_status s = capture_step(p, true, &p->forked);
+        if (s != NYX_OK) return s;
     }
-    HIPC(ctx, hipGraphLaunch(p->exec, st));
+    HIPC(ctx, hipGraphLaunch(p->forked.exec ? p->forked.exec : p->plain.exec, st));
     if (rois && rois->n_rois_host) *rois->n_rois_host = p->w.n_rois;
     return NYX_OK;
 }
@@ -1981,9 +2014,7 @@ nyx_status nyx_plan_profile(nyx_plan *p, void *table, float *ms_host, nyx_stream
     hipStream_t st = (hipStream_t)stream;
     set_outputs(ctx, p->w.args, nullptr, table, p->w.n_rois);
     // the graph (if any) was captured with other outputs; drop it
-    if (p->exec) { (void)hipGraphExecDestroy(p->exec); p->exec = nullptr; }
-    if (p->graph) { (void)hipGraphDestroy(p->graph); p->graph = nullptr; }
-    p->graph_table = nullptr;
+    drop_graphs(p);
     static_assert(NYX_PHASE_COUNT == 8, "one event interval per phase");
     hipEvent_t ev[NYX_PHASE_COUNT + 1];
     for (auto &e : ev) HIPC(ctx, hipEventCreate(&e));
@@ -2028,8 +2059,7 @@ const char *nyx_plan_describe(const nyx_plan *p) { return p ? p->desc.c_str() : 
 void nyx_plan_destroy(nyx_plan *p) {
     if (!p) return;
     (void)hipSetDevice(p->ctx->device);
-    if (p->exec) (void)hipGraphExecDestroy(p->exec);
-    if (p->graph) (void)hipGraphDestroy(p->graph);
+    drop_graphs(p);
     delete p;
 }
 

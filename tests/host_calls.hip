@@ -355,6 +355,27 @@ void band_blocks_of_many() {
     nyx_destroy(c);
 }
 
+// A graph of two branches takes several times as long to instantiate: it is
+// made for outputs that come back, not for ones that change with every call.
+void forks_when_repeated() {
+    nyx_ctx *c = context();
+    nyx_image im = image(2000, 2000);
+    int64_t n = 0;
+    host::rois.assign(6000, host::box(200u, 15u, 15u));
+    for (size_t r = 0; r < host::rois.size(); r += 20) host::rois[r] = host::box(3000u, 60u, 55u);
+    nyx_extract_opts o = options(256);
+    nyx_plan *p = nullptr;
+    EXPECT(nyx_plan_create(c, &im, 1, &o, &p, &n) == NYX_OK);
+    for (int k = 0; k < 20; ++k) EXPECT(nyx_plan_execute(p, nullptr, kI + 64 * (k & 1), kStream) == NYX_OK);
+    for (size_t s : host::graph_streams) EXPECT(s == 1);
+    EXPECT(host::graph_streams.size() == 20);
+    host::graph_streams.clear();
+    for (int k = 0; k < 20; ++k) EXPECT(nyx_plan_execute(p, nullptr, kI, kStream) == NYX_OK);
+    EXPECT(host::graph_streams == std::vector<size_t>({1, 2}));
+    nyx_plan_destroy(p);
+    nyx_destroy(c);
+}
+
 struct Check { const char *name; void (*run)(); };
 const Check kChecks[] = {
     {"extract_device", extract_device},
@@ -362,6 +383,7 @@ const Check kChecks[] = {
     {"accumulate_wait", accumulate_wait},
     {"packed_memory", packed_memory},
     {"band_blocks_of_many", band_blocks_of_many},
+    {"forks_when_repeated", forks_when_repeated},
 };
 
 }  // namespace

@@ -27,7 +27,8 @@ def host_calls():
     return exe
 
 
-@pytest.mark.parametrize("check", ["extract_device", "noalloc_wait", "accumulate_wait", "packed_memory", "band_blocks_of_many"])
+@pytest.mark.parametrize("check", ["extract_device", "noalloc_wait", "accumulate_wait", "packed_memory",
+                                   "band_blocks_of_many", "forks_when_repeated"])
 def test_host_calls(host_calls, check):
     r = subprocess.run([host_calls, check], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr

@@ -207,6 +207,62 @@ struct nyx_ctx {
     uint8_t *pin = nullptr;       // kPinBytes of pinned host memory for the calls' small copies
 };
 
+// The sizes of a batch's ROIs by size class (size_class of their voxels), with
+// each class's sums: what the planner asks of the ROIs up to a number of voxels
+// comes from the sums of the classes below, and only larger ones are looked at
+// one by one.  (Over the descriptors, each of its dozen questions walked all of
+// them: a plan of 150000 regions took 17 ms on the host.)
+struct RoiSizes {
+    struct Box {
+        uint32_t n, rows, width;
+    };
+    struct Sum {
+        uint64_t count = 0, vox = 0;
+        uint32_t most = 0;   // voxels of the largest
+        void add(uint32_t n) {
+            ++count;
+            vox += n;
+            most = std::max(most, n);
+        }
+        void add(const Sum &o) {
+            count += o.count;
+            vox += o.vox;
+            most = std::max(most, o.most);
+        }
+    };
+    std::vector<Box> box;                  // by class, ascending
+    size_t first[kClasses + 1] = {};
+    Sum of_class[kClasses], all;
+
+    void fill(const std::vector<RoiDesc> &rois) {
+        *this = RoiSizes{};
+        for (const RoiDesc &r : rois) of_class[size_class(r.n)].add(r.n);
+        for (int cl = 0; cl < kClasses; ++cl) {
+            first[cl + 1] = first[cl] + of_class[cl].count;
+            all.add(of_class[cl]);
+        }
+        box.resize(rois.size());
+        size_t at[kClasses];
+        std::copy(first, first + kClasses, at);
+        for (const RoiDesc &r : rois)
+            box[at[size_class(r.n)]++] = Box{r.n, r.rows, (uint32_t)(r.x1 - r.x0 + 1)};
+    }
+    // the ROIs of at most v voxels
+    Sum up_to(uint32_t v) const {
+        Sum s;
+        const uint32_t c = size_class(v);
+        for (uint32_t cl = 0; cl < c; ++cl) s.add(of_class[cl]);
+        for (size_t i = first[c]; i < first[c + 1]; ++i)
+            if (box[i].n <= v) s.add(box[i].n);
+        return s;
+    }
+    // every ROI of more than v voxels
+    template <class Fn> void above(uint32_t v, Fn &&fn) const {
+        for (size_t i = first[size_class(v)]; i < box.size(); ++i)
+            if (box[i].n > v) fn(box[i]);
+    }
+};
+
 // All device state of one discovery/step over a batch of images.
 struct Work {
     std::vector<ImgDesc> h_imgs;
@@ -217,6 +273,7 @@ struct Work {
     uint32_t n_rois = 0;
     uint64_t total_vox = 0;
     std::vector<RoiDesc> h_rois;
+    RoiSizes sizes;                    // of h_rois
     StepArgs args{};
     bool have_rois = false;            // h_rois holds the descriptors
     // Carve every buffer from `ar` (nullptr: hipMalloc).
@@ -239,7 +296,6 @@ struct nyx_plan {
     uint32_t small_cls = 0, small_kp = 0, small_grid = 0;
     LdsLayout small_lds{};
     bool banded = false, fork = false; // a planned ROI is banded; a step that is repeated forks
-    std::vector<uint32_t> roi_tiles;   // per-ROI tile count for the per-ROI path
     // The step as a graph writing graph_table and graph_rois: of one branch,
     // and of two once it has been replayed `replays` times.
     struct Graph {
@@ -566,6 +622,7 @@ nyx_status discover(nyx_ctx *ctx, const nyx_image *imgs, int32_t n, Work &w, hip
     if (w.n_rois <= spec) {
         const RoiDesc *h = reinterpret_cast<const RoiDesc *>(ctx->pin + kPinUp + kHead);
         w.h_rois.assign(h, h + w.n_rois);
+        w.sizes.fill(w.h_rois);
         w.have_rois = true;
     }
     w.rois.shrink(sizeof(RoiDesc) * std::max<uint32_t>(w.n_rois, 1u));
@@ -584,6 +641,7 @@ nyx_status fetch_rois(nyx_ctx *ctx, Work &w, hipStream_t st) {
         HIPC(ctx, hipMemcpyAsync(w.h_rois.data(), w.rois.p, sizeof(RoiDesc) * w.n_rois, hipMemcpyDeviceToHost, st));
         HIPC(ctx, hipStreamSynchronize(st));
     }
+    w.sizes.fill(w.h_rois);
     w.have_rois = true;
     return NYX_OK;
 }
@@ -641,17 +699,16 @@ void set_band(Config &c, uint32_t ng, int K) {
 uint32_t band_tile(const Work &w, const Config &c, uint32_t n_cu, int K) {
     if (c.band_vox == 0u) return kBandTile;
     const uint32_t sets = ((uint32_t)K + c.band_dirs - 1u) / c.band_dirs;
-    std::vector<std::pair<uint32_t, uint32_t>> box;   // rows and width of the banded ROIs
+    std::vector<RoiSizes::Box> box;   // the banded ROIs
     uint64_t total = 0;
-    for (const RoiDesc &r : w.h_rois)
-        if (r.n > c.band_vox) {
-            box.emplace_back(r.rows, (uint32_t)(r.x1 - r.x0 + 1));
-            total += (uint64_t)r.rows * box.back().second;
-        }
+    w.sizes.above(c.band_vox, [&](const RoiSizes::Box &r) {
+        box.push_back(r);
+        total += (uint64_t)r.rows * r.width;
+    });
     const uint64_t share = std::min<uint64_t>(std::max<uint64_t>(kBandTile, total * sets / n_cu), 0x20000000u);
     for (uint64_t tile = share; tile <= share + share / 8u && box.size() * sets <= n_cu; tile += tile / 16u) {
         uint64_t items = 0;
-        for (const auto &b : box) items += band_blocks(b.first, b.second, (uint32_t)tile) * (uint64_t)sets;
+        for (const RoiSizes::Box &b : box) items += band_blocks(b.rows, b.width, (uint32_t)tile) * (uint64_t)sets;
         if (items <= n_cu) return (uint32_t)tile;
     }
     return (uint32_t)std::max<uint64_t>(kBandTile, share / 2u);
@@ -778,14 +835,19 @@ LdsLayout make_layout(const Config &c, uint32_t ng, int K, bool ring) {
     return groups_per_cu(P.bytes) > groups_per_cu(L.bytes) ? P : L;
 }
 
+// Work items of a ROI; banded ROIs (above band_vox voxels, 0: none) have none.
+uint32_t tile_count(uint32_t n, uint32_t rows, uint32_t width, uint32_t split_vox, uint32_t tile_vox, uint32_t band_vox) {
+    if (band_vox && n > band_vox) return 0u;
+    const Tiling t = tiles_for(n, rows, width, split_vox, tile_vox);
+    return t.row_blocks * t.col_blocks;
+}
+
 // Largest voxel count any work item can hold under a split rule.
-uint64_t max_item_vox(const std::vector<RoiDesc> &rois, uint32_t split_vox, uint32_t tile_vox) {
-    uint64_t m = 0;
-    for (const RoiDesc &r : rois) {
-        uint32_t W = (uint32_t)(r.x1 - r.x0 + 1);
-        Tiling t = tiles_for(r.n, r.rows, W, split_vox, tile_vox);
-        m = std::max<uint64_t>(m, item_bound(r.n, r.rows, W, t));
-    }
+uint64_t max_item_vox(const RoiSizes &rois, uint32_t split_vox, uint32_t tile_vox) {
+    uint64_t m = rois.up_to(split_vox).most;
+    rois.above(split_vox, [&](const RoiSizes::Box &r) {
+        m = std::max<uint64_t>(m, item_bound(r.n, r.rows, r.width, tiles_for(r.n, r.rows, r.width, split_vox, tile_vox)));
+    });
     return m;
 }
 
@@ -806,7 +868,7 @@ Config packed_config(const nyx_ctx *ctx, const Work &w, uint32_t ng, int K, int 
     // four directions in one 512-thread group per CU beat one in five groups).
     for (uint32_t kp = (uint32_t)K; kp >= 1u; kp = kp == 1u ? 0u : (kp + 1u) / 2u) {
         for (uint32_t split = std::min(lb, n_max);; split /= 2u) {
-            const uint64_t mi = max_item_vox(w.h_rois, split, split);
+            const uint64_t mi = max_item_vox(w.sizes, split, split);
             if (mi <= n_max) {
                 Config c;
                 c.mode = 4; c.kp = kp; c.block = block; c.split_vox = c.tile_vox = split;
@@ -826,13 +888,18 @@ Config packed_config(const nyx_ctx *ctx, const Work &w, uint32_t ng, int K, int 
     if (!force_split) {
         // voxels and items by size class, as the device will bucket them
         double vox[kClasses] = {}, num[kClasses] = {};
-        for (const RoiDesc &r : w.h_rois) {
-            if (best.band_vox && r.n > best.band_vox) continue;   // (no batch items)
-            const Tiling t = tiles_for(r.n, r.rows, (uint32_t)(r.x1 - r.x0 + 1), best.split_vox, best.tile_vox);
-            const uint32_t cl = size_class(item_bound(r.n, r.rows, (uint32_t)(r.x1 - r.x0 + 1), t));
+        const uint32_t sc = size_class(best.split_vox);
+        for (uint32_t cl = 0; cl < sc; ++cl) {
+            vox[cl] = (double)w.sizes.of_class[cl].vox;
+            num[cl] = (double)w.sizes.of_class[cl].count;
+        }
+        w.sizes.above((1u << sc) - 1u, [&](const RoiSizes::Box &r) {
+            if (best.band_vox && r.n > best.band_vox) return;   // (no batch items)
+            const Tiling t = tiles_for(r.n, r.rows, r.width, best.split_vox, best.tile_vox);
+            const uint32_t cl = size_class(item_bound(r.n, r.rows, r.width, t));
             vox[cl] += r.n;
             num[cl] += (double)t.row_blocks * t.col_blocks;
-        }
+        });
         const double fixed = 500.0 * (1.0 + ng / 256.0);
         const auto work = [&](uint32_t lo, uint32_t hi) {
             double s = 0.0;
@@ -863,22 +930,16 @@ Config packed_config(const nyx_ctx *ctx, const Work &w, uint32_t ng, int K, int 
 }
 
 // Item and split-slot counts implied by a configuration.
-void count_items(const std::vector<RoiDesc> &rois, const Config &c, uint64_t *items, uint32_t *n_split,
-                 std::vector<uint32_t> *tiles) {
-    uint64_t it = 0;
-    uint32_t ns = 0;
-    if (tiles) tiles->resize(rois.size());
-    for (size_t i = 0; i < rois.size(); ++i) {
-        const RoiDesc &r = rois[i];
-        const bool band = c.band_vox && r.n > c.band_vox;
-        Tiling t = tiles_for(r.n, r.rows, (uint32_t)(r.x1 - r.x0 + 1), c.split_vox, c.tile_vox);
-        uint32_t nt = band ? 0u : t.row_blocks * t.col_blocks;
+void count_items(const RoiSizes &rois, const Config &c, uint64_t *items, uint32_t *n_split) {
+    const uint64_t whole = rois.up_to(c.split_vox).count;
+    uint64_t it = whole, ns = c.force_split ? whole : 0u;
+    rois.above(c.split_vox, [&](const RoiSizes::Box &r) {
+        const uint32_t nt = tile_count(r.n, r.rows, r.width, c.split_vox, c.tile_vox, c.band_vox);
         it += nt;
-        if (nt > 1u || band || c.force_split) ++ns;
-        if (tiles) (*tiles)[i] = nt;
-    }
+        if (nt != 1u || c.force_split) ++ns;
+    });
     *items = it;
-    *n_split = ns;
+    *n_split = (uint32_t)ns;
 }
 
 // Device memory of a step's queue, matrices and records.
@@ -904,8 +965,8 @@ uint64_t step_bytes(const Work &w, int K_out, uint32_t ng, bool nonsym, uint64_t
 bool packed_worth(const Work &w, const Config &c, const Config &d, uint32_t ng, int K, uint64_t limit) {
     uint64_t items_c, items_d;
     uint32_t split_c, split_d;
-    count_items(w.h_rois, c, &items_c, &split_c, nullptr);
-    count_items(w.h_rois, d, &items_d, &split_d, nullptr);
+    count_items(w.sizes, c, &items_c, &split_c);
+    count_items(w.sizes, d, &items_d, &split_d);
     const uint64_t need_c = step_bytes(w, K, ng, c.nonsym != 0, items_c, split_c),
                    need_d = step_bytes(w, K, ng, d.nonsym != 0, items_d, split_d);
     if (need_c <= need_d) return true;
@@ -939,8 +1000,7 @@ std::vector<Config> candidate_configs(const nyx_ctx *ctx, const Work &w, uint32_
                (uint32_t)kTicketChunk * kItemBytes + ((ng + 1u) * 4u + 15u) / 16u * 16u + 64u * 4u + 64;
     };
     const uint32_t fixed = fixed_for(1u);
-    uint64_t total_vox = 0;
-    for (const RoiDesc &r : w.h_rois) total_vox += r.n;
+    const uint64_t total_vox = w.sizes.all.vox;
     // load balance: split ROIs that would take more than ~1/4 of one
     // work-group's share of the voxels
     uint64_t share = (uint64_t)((double)(total_vox / ((uint64_t)std::max(ctx->n_cu, 1) * 4u) + 1u) * tile_scale);
@@ -951,10 +1011,10 @@ std::vector<Config> candidate_configs(const nyx_ctx *ctx, const Work &w, uint32_
         if (copies > 1u && mode == 0) continue;   // the returning-atomic list keeps one triangle
         const uint32_t cell_max = merged ? 65535u / (uint32_t)K : 65535u;   // 16-bit counters
         uint32_t split = mode == 3 ? std::min<uint32_t>(lb, cell_max) : lb;
-        uint64_t mi = max_item_vox(w.h_rois, split, split);
+        uint64_t mi = max_item_vox(w.sizes, split, split);
         while (mode == 3 && mi > cell_max && split > 64u) {
             split /= 2u;
-            mi = max_item_vox(w.h_rois, split, split);
+            mi = max_item_vox(w.sizes, split, split);
         }
         if (mode == 3 && mi > cell_max) continue;
         if (merged && mode == 3 && split < std::min<uint32_t>(lb, 65535u)) continue;
@@ -1001,10 +1061,10 @@ std::vector<Config> candidate_configs(const nyx_ctx *ctx, const Work &w, uint32_
             uint32_t per_dir = hc / (2u * kp);
             if (per_dir < 64u) continue;
             uint32_t split = std::min<uint32_t>(per_dir, lb);
-            uint64_t mi = max_item_vox(w.h_rois, split, split);
+            uint64_t mi = max_item_vox(w.sizes, split, split);
             while (mi > per_dir && split > 16u) {
                 split /= 2u;
-                mi = max_item_vox(w.h_rois, split, split);
+                mi = max_item_vox(w.sizes, split, split);
             }
             if (mi > per_dir) continue;
             uint32_t list_cap = (uint32_t)std::max<uint64_t>(mi, 1u);
@@ -1037,9 +1097,8 @@ std::vector<Config> candidate_configs(const nyx_ctx *ctx, const Work &w, uint32_
 // the first and 118, 269, 774 us on the second; it stays for callers that ask
 // for it and where neither fits.)
 Config default_config(const std::vector<Config> &cands, const Work &w, uint32_t ng, int K) {
-    uint64_t total_vox = 0;
-    for (const RoiDesc &r : w.h_rois) total_vox += r.n;
-    const uint64_t avg = w.h_rois.empty() ? 1u : std::max<uint64_t>(1u, total_vox / w.h_rois.size());
+    const RoiSizes::Sum &all = w.sizes.all;
+    const uint64_t avg = all.count ? std::max<uint64_t>(1u, all.vox / all.count) : 1u;
     const uint64_t tri = (uint64_t)ng * (ng + 1u) / 2u;
     bool any_scan = false, any_hash = false;
     for (const Config &c : cands) {
@@ -1049,10 +1108,8 @@ Config default_config(const std::vector<Config> &cands, const Work &w, uint32_t 
     for (const Config &c : cands) {
         if (c.mode != 4) continue;
         // (the average of the regions that the banded kernel would leave it)
-        uint64_t vox = 0, n = 0;
-        for (const RoiDesc &r : w.h_rois)
-            if (!c.band_vox || r.n <= c.band_vox) { vox += r.n; ++n; }
-        if (!any_scan || tri > 16u * (n ? std::max<uint64_t>(1u, vox / n) : avg)) return c;
+        const RoiSizes::Sum left = c.band_vox ? w.sizes.up_to(c.band_vox) : all;
+        if (!any_scan || tri > 16u * (left.count ? std::max<uint64_t>(1u, left.vox / left.count) : avg)) return c;
     }
     const bool prefer_scan = any_scan && (any_hash || tri <= 8u * avg);
     // among the candidates of the preferred kind: fewest passes over the
@@ -1168,7 +1225,7 @@ nyx_status setup_step(nyx_ctx *ctx, Work &w, const Config &cfg, const nyx_offset
     StepArgs &a = w.args;
     uint64_t items;
     uint32_t n_split;
-    count_items(w.h_rois, cfg, &items, &n_split, nullptr);
+    count_items(w.sizes, cfg, &items, &n_split);
     if (g_cap_override) n_split = g_cap_override;
     if (items >= (1ull << 31)) return fail(ctx, NYX_ERR_UNSUPPORTED, "too many work items");
     uint32_t bucket_cap = (uint32_t)std::max<uint64_t>(items, 1u);
@@ -1313,15 +1370,16 @@ hipError_t launch_counting_forked(const nyx_plan *p, hipStream_t st) {
 bool worth_forking(const nyx_plan *p) {
     if (!p->small_cls) return false;
     const StepArgs &a = p->w.args;
-    uint64_t all = 0, large = 0;
-    for (const RoiDesc &r : p->w.h_rois) {
-        const uint32_t W = (uint32_t)(r.x1 - r.x0 + 1);
-        all += r.n;
+    const RoiSizes &rois = p->w.sizes;
+    const uint32_t sc = size_class(a.split_vox);
+    uint64_t large = 0;
+    for (uint32_t cl = p->small_cls; cl < sc; ++cl) large += rois.of_class[cl].vox;
+    rois.above((1u << sc) - 1u, [&](const RoiSizes::Box &r) {
         if ((a.band_vox && r.n > a.band_vox) ||
-            (uint32_t)size_class(item_bound(r.n, r.rows, W, tiles_for(r.n, r.rows, W, a.split_vox, a.tile_vox))) >= p->small_cls)
+            size_class(item_bound(r.n, r.rows, r.width, tiles_for(r.n, r.rows, r.width, a.split_vox, a.tile_vox))) >= p->small_cls)
             large += r.n;
-    }
-    return large * 16u > all;
+    });
+    return large * 16u > rois.all.vox;
 }
 
 // The full step on a stream.  per_roi: one accumulation launch per ROI; fork:
@@ -1344,7 +1402,11 @@ nyx_status enqueue_step(nyx_plan *p, hipStream_t st, bool per_roi, bool scanned 
     } else if (!per_roi) {
         HIPC(ctx, launch_batches(p, st));
     } else {
-        for (uint32_t r = 0; r < p->w.n_rois; ++r) HIPC(ctx, launch_batch(a, p->roi_tiles[r], p->block, r, st));
+        for (uint32_t r = 0; r < p->w.n_rois; ++r) {
+            const RoiDesc &d = p->w.h_rois[r];
+            const uint32_t nt = tile_count(d.n, d.rows, (uint32_t)(d.x1 - d.x0 + 1), a.split_vox, a.tile_vox, a.band_vox);
+            HIPC(ctx, launch_batch(a, nt, p->block, r, st));
+        }
     }
     if (!fork) HIPC(ctx, launch_band(a, (uint32_t)ctx->n_cu, st));
     HIPC(ctx, launch_split_finalize(a, st));
@@ -1394,8 +1456,7 @@ nyx_status check_counters(nyx_ctx *ctx, Work &w, hipStream_t st) {
 
 std::string describe(const Config &c, const nyx_plan *p, uint64_t items, uint32_t n_split) {
     uint64_t band_voxels = 0;
-    for (const RoiDesc &r : p->w.h_rois)
-        if (c.band_vox && r.n > c.band_vox) band_voxels += r.n;
+    if (c.band_vox) band_voxels = p->w.sizes.all.vox - p->w.sizes.up_to(c.band_vox).vox;
     char buf[640];
     snprintf(buf, sizeof buf,
              "mode=%s kp=%u copies=%u symmetric=%d block=%u grid=%u lds=%uB split_vox=%u tile_vox=%u tile_scale=%g "
@@ -1440,9 +1501,8 @@ nyx_status configure(nyx_plan *p, const Config &cfg, const nyx_extract_opts *opt
     }
     uint64_t items;
     uint32_t n_split;
-    count_items(p->w.h_rois, cfg, &items, &n_split, &p->roi_tiles);
-    p->banded = false;
-    for (const RoiDesc &r : p->w.h_rois) p->banded |= cfg.band_vox != 0u && r.n > cfg.band_vox;
+    count_items(p->w.sizes, cfg, &items, &n_split);
+    p->banded = cfg.band_vox != 0u && p->w.sizes.all.most > cfg.band_vox;
     p->fork = worth_forking(p);
     p->cfg = nyx_plan::Cfg{cfg.mode, cfg.kp, cfg.block, cfg.split_vox, cfg.tile_vox, cfg.list_cap, cfg.hash_cap,
                            cfg.force_split};

@@ -376,6 +376,54 @@ void forks_when_repeated() {
     nyx_destroy(c);
 }
 
+uint32_t described_number(const nyx_plan *p, const char *key) {
+    const char *at = strstr(nyx_plan_describe(p), key);
+    EXPECT(at != nullptr);
+    return at ? (uint32_t)strtoul(at + strlen(key), nullptr, 10) : 0u;
+}
+
+// The items and split regions of a plan, counted region by region.
+void plan_counts() {
+    nyx_ctx *c = context();
+    nyx_image im = image(8000, 8000);
+    int64_t n = 0;
+    uint32_t x = 1u;
+    const auto next = [&](uint32_t below) {
+        x = x * 1664525u + 1013904223u;
+        return (x >> 8) % below;
+    };
+    for (int bins : {16, 100, 256, 700, 2048, 6000}) {
+        for (uint32_t count : {1u, 60u, 900u}) {
+            host::rois.clear();
+            for (uint32_t k = 0; k < count; ++k) {
+                const uint32_t rows = 1u + next(k % 9u == 0u ? 3000u : 90u), width = 1u + next(k % 7u == 0u ? 900u : 70u);
+                host::rois.push_back(host::box(1u + next(rows * width), rows, width));
+            }
+            for (uint32_t v : {4095u, 4096u, 4097u, 32767u, 32768u, 32769u}) host::rois.push_back(host::box(v, 190u, 180u));
+            nyx_extract_opts o = options(bins);
+            nyx_plan *p = nullptr;
+            EXPECT(nyx_plan_create(c, &im, 1, &o, &p, &n) == NYX_OK);
+            if (!p) continue;
+            const uint32_t split = described_number(p, "split_vox="), tile = described_number(p, "tile_vox="),
+                           band = described_number(p, "band_vox=");
+            uint64_t items = 0, n_split = 0, banded = 0;
+            for (const RoiDesc &r : host::rois) {
+                const uint32_t w = (uint32_t)(r.x1 + 1);
+                const nyx::Tiling t = nyx::tiles_for(r.n, r.rows, w, split, tile);
+                const bool b = band && r.n > band;
+                items += b ? 0u : t.row_blocks * t.col_blocks;
+                n_split += b || t.row_blocks * t.col_blocks > 1u;
+                banded += b ? r.n : 0u;
+            }
+            EXPECT(described_number(p, " items=") == items);
+            EXPECT(described_number(p, "split_rois=") == n_split);
+            EXPECT(described_number(p, "band_voxels=") == banded);
+            nyx_plan_destroy(p);
+        }
+    }
+    nyx_destroy(c);
+}
+
 struct Check { const char *name; void (*run)(); };
 const Check kChecks[] = {
     {"extract_device", extract_device},
@@ -384,6 +432,7 @@ const Check kChecks[] = {
     {"packed_memory", packed_memory},
     {"band_blocks_of_many", band_blocks_of_many},
     {"forks_when_repeated", forks_when_repeated},
+    {"plan_counts", plan_counts},
 };
 
 }  // namespace

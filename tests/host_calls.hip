@@ -402,7 +402,8 @@ void plan_counts() {
             for (uint32_t v : {4095u, 4096u, 4097u, 32767u, 32768u, 32769u}) host::rois.push_back(host::box(v, 190u, 180u));
             nyx_extract_opts o = options(bins);
             nyx_plan *p = nullptr;
-            EXPECT(nyx_plan_create(c, &im, 1, &o, &p, &n) == NYX_OK);
+            const nyx_status s = nyx_plan_create(c, &im, 1, &o, &p, &n);
+            EXPECT(s == NYX_OK || (bins == 6000 && s == NYX_ERR_UNSUPPORTED));   // (too wide a region for its tables)
             if (!p) continue;
             const uint32_t split = described_number(p, "split_vox="), tile = described_number(p, "tile_vox="),
                            band = described_number(p, "band_vox=");

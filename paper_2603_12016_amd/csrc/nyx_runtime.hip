@@ -500,7 +500,7 @@ nyx_status discover(nyx_ctx *ctx, const nyx_image *imgs, int32_t n, Work &w, hip
                     const TileQueue *tiles = nullptr) {
     w.h_imgs.resize(n);
     uint32_t chunk = 0;
-    uint64_t tv = 0;
+    uint64_t tv = 0, most_vox = 0;
     // one upload: image descriptors, first voxels, and the cleared label maxima
     std::vector<uint64_t> up((sizeof(ImgDesc) * n + 12u * n + 7u) / 8u, 0u);
     uint64_t *vbase = up.data() + sizeof(ImgDesc) / 8u * n;
@@ -524,6 +524,7 @@ nyx_status discover(nyx_ctx *ctx, const nyx_image *imgs, int32_t n, Work &w, hip
         }
         vbase[i] = tv;
         tv += d.nvox;
+        most_vox = std::max<uint64_t>(most_vox, d.nvox);
     }
     w.total_chunks = chunk;
     w.total_vox = tv;
@@ -539,7 +540,7 @@ nyx_status discover(nyx_ctx *ctx, const nyx_image *imgs, int32_t n, Work &w, hip
         big.resize(n);
         hmax = big.data();
     }
-    HIPC(ctx, launch_max_label(w.imgs.as<ImgDesc>(), n, tv, dmax, st));
+    HIPC(ctx, launch_max_label(w.imgs.as<ImgDesc>(), n, most_vox, dmax, st));
     HIPC(ctx, hipMemcpyAsync(hmax, dmax, sizeof(uint32_t) * n, hipMemcpyDeviceToHost, st));
     HIPC(ctx, hipStreamSynchronize(st));
     uint64_t total = 0;

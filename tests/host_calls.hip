@@ -425,6 +425,25 @@ void plan_counts() {
     nyx_destroy(c);
 }
 
+// A large image among many small ones is still read by many work-groups.
+void label_maximum_of_mixed_sizes() {
+    nyx_ctx *c = context();
+    std::vector<nyx_image> im(1000, image(64, 64));
+    im.push_back(image(6000, 10000));
+    nyx_roi_table t{};
+    int64_t n = 0;
+    t.n_rois_host = &n;
+    EXPECT(nyx_bin_rois(c, im.data(), (int32_t)im.size(), 16, &t, nullptr, kStream) == NYX_OK);
+    int seen = 0;
+    for (const Launch &l : host::launches) {
+        if (l.name.find("k_max_label") == std::string::npos) continue;
+        ++seen;
+        EXPECT(l.grid.x >= 256u && l.grid.y == 1001u);
+    }
+    EXPECT(seen == 1);
+    nyx_destroy(c);
+}
+
 struct Check { const char *name; void (*run)(); };
 const Check kChecks[] = {
     {"extract_device", extract_device},
@@ -434,6 +453,7 @@ const Check kChecks[] = {
     {"band_blocks_of_many", band_blocks_of_many},
     {"forks_when_repeated", forks_when_repeated},
     {"plan_counts", plan_counts},
+    {"label_maximum_of_mixed_sizes", label_maximum_of_mixed_sizes},
 };
 
 }  // namespace

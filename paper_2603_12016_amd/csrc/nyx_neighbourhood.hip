@@ -368,9 +368,13 @@ __host__ __device__ inline uint32_t nb_lds_bytes(uint32_t ng, uint32_t nn) {
 
 // Persistent: the tiles of the queue, one work-group each.  nn_max:
 // neighbours per voxel the LDS tables are laid out for (8 or 26); gtab:
-// tables of split ROIs, one per split slot, zero on entry.
+// tables of split ROIs, one per split slot, zero on entry.  At most 168 VGPRs,
+// three waves per SIMD: the features of small regions wait for their
+// reductions (466489 regions of 3 x 3 at 32 levels, call: 9.87 ms with a
+// work-group per region, 11.69 with 169 VGPRs, 8.80 so, 9.02 with 128 and
+// spills).
 template <class OutT>
-__global__ __launch_bounds__(kNbBlock) void k_neighbourhood(StepArgs a, uint32_t alpha, uint32_t nn_max,
+__global__ __launch_bounds__(kNbBlock, 3) void k_neighbourhood(StepArgs a, uint32_t alpha, uint32_t nn_max,
                                                             uint32_t *gtab, OutT *table, uint32_t table_rows) {
     __shared__ NbShared S;
     extern __shared__ __align__(16) uint8_t smem[];

@@ -2049,39 +2049,44 @@ hipError_t launch_batch(const StepArgs &a, uint32_t grid, uint32_t block, uint32
     }
 }
 
-template <int MODE, bool NS, bool VOL>
+template <int MODE, bool NS, bool VOL, bool PAIR = false>
 static const void *batch_kernel_m(int fp64, uint32_t block) {
     if (block == 512u)
-        return fp64 ? reinterpret_cast<const void *>(&k_batch<MODE, double, NS, 512, VOL>)
-                    : reinterpret_cast<const void *>(&k_batch<MODE, float, NS, 512, VOL>);
-    return fp64 ? reinterpret_cast<const void *>(&k_batch<MODE, double, NS, 256, VOL>)
-                : reinterpret_cast<const void *>(&k_batch<MODE, float, NS, 256, VOL>);
+        return fp64 ? reinterpret_cast<const void *>(&k_batch<MODE, double, NS, 512, VOL, PAIR>)
+                    : reinterpret_cast<const void *>(&k_batch<MODE, float, NS, 512, VOL, PAIR>);
+    return fp64 ? reinterpret_cast<const void *>(&k_batch<MODE, double, NS, 256, VOL, PAIR>)
+                : reinterpret_cast<const void *>(&k_batch<MODE, float, NS, 256, VOL, PAIR>);
 }
 
 template <int MODE>
-static const void *batch_kernel_k(int fp64, int ns, int vol, uint32_t block) {
+static const void *batch_kernel_k(const StepArgs &a, uint32_t block) {
     if constexpr (MODE != 0)
-        if (ns) return batch_kernel_m<MODE, true, false>(fp64, block);
-    return vol ? batch_kernel_m<MODE, false, true>(fp64, block) : batch_kernel_m<MODE, false, false>(fp64, block);
+        if (a.nonsym) return batch_kernel_m<MODE, true, false>(a.fp64, block);
+    if constexpr (MODE == 3)
+        if (a.lds.marg_pair)
+            return a.sweep3_ok ? batch_kernel_m<MODE, false, true, true>(a.fp64, block)
+                               : batch_kernel_m<MODE, false, false, true>(a.fp64, block);
+    return a.sweep3_ok ? batch_kernel_m<MODE, false, true>(a.fp64, block)
+                       : batch_kernel_m<MODE, false, false>(a.fp64, block);
 }
 
-static const void *batch_kernel(int mode, int fp64, int ns, int vol, uint32_t block) {
-    switch (mode) {
-        case 0: return batch_kernel_k<0>(fp64, ns, vol, block);
-        case 1: return batch_kernel_k<1>(fp64, ns, vol, block);
-        case 4: return batch_kernel_k<4>(fp64, ns, vol, block);
-        case 2: return batch_kernel_k<2>(fp64, ns, vol, block);
-        default: return batch_kernel_k<3>(fp64, ns, vol, block);
+// The kernel that launch_batch runs.
+static const void *batch_kernel(const StepArgs &a, uint32_t block) {
+    switch (a.lds.mode) {
+        case 0: return batch_kernel_k<0>(a, block);
+        case 1: return batch_kernel_k<1>(a, block);
+        case 4: return batch_kernel_k<4>(a, block);
+        case 2: return batch_kernel_k<2>(a, block);
+        default: return batch_kernel_k<3>(a, block);
     }
 }
 
-hipError_t batch_occupancy(int mode, int fp64, int ns, int vol, uint32_t block, uint32_t lds_bytes,
-                           int *blocks_per_cu) {
+hipError_t batch_occupancy(const StepArgs &a, uint32_t block, int *blocks_per_cu) {
     if (block != 256u && block != 512u) return hipErrorInvalidConfiguration;
-    const void *f = batch_kernel(mode, fp64, ns, vol, block);
+    const void *f = batch_kernel(a, block);
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, f, (int)block, (size_t)lds_bytes);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, f, (int)block, (size_t)a.lds.bytes);
 }
 
 static hipError_t set_feature_kernel_attrs() {

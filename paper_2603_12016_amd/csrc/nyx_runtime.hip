@@ -1484,8 +1484,7 @@ nyx_status configure(nyx_plan *p, const Config &cfg, const nyx_extract_opts *opt
                     kLdsBudget);
     p->block = cfg.block;
     int occ = 0;
-    HIPC(ctx, batch_occupancy(cfg.mode, p->prec == NYX_FP64, cfg.nonsym, p->w.args.sweep3_ok, cfg.block,
-                              p->w.args.lds.bytes, &occ));
+    HIPC(ctx, batch_occupancy(p->w.args, cfg.block, &occ));
     p->grid = (uint32_t)ctx->n_cu * (uint32_t)std::max(occ, 1);
     p->small_cls = cfg.mode == 4 ? cfg.small_cls : 0u;
     if (p->small_cls) {
@@ -1496,8 +1495,8 @@ nyx_status configure(nyx_plan *p, const Config &cfg, const nyx_extract_opts *opt
         StepArgs t = p->w.args;
         set_sweep(t, p->w.h_imgs, opts->offsets_host, p->K, s.kp);
         if (cfg.nonsym) t.sweep3_ok = 0;
-        p->small_lds = make_layout(s, (uint32_t)p->ng, p->K, !t.sweep_ok && !t.sweep3_ok);
-        HIPC(ctx, batch_occupancy(cfg.mode, p->prec == NYX_FP64, cfg.nonsym, t.sweep3_ok, 256u, p->small_lds.bytes, &occ));
+        p->small_lds = t.lds = make_layout(s, (uint32_t)p->ng, p->K, !t.sweep_ok && !t.sweep3_ok);
+        HIPC(ctx, batch_occupancy(t, 256u, &occ));
         p->small_grid = (uint32_t)ctx->n_cu * (uint32_t)std::max(occ, 1);
     }
     uint64_t items;

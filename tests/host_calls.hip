@@ -444,6 +444,36 @@ void label_maximum_of_mixed_sizes() {
     nyx_destroy(c);
 }
 
+// The grid of the batch kernel comes from the occupancy of the kernel that runs.
+void occupancy_of_the_kernel_launched() {
+    nyx_ctx *c = context();
+    nyx_image im = image(2000, 2000), vol = image(200, 200, 100);
+    int64_t n = 0;
+    int paired = 0;
+    for (int bins : {64, 120, 128, 256}) {
+        for (int sym : {1, 0}) {
+            for (const nyx_image *m : {&im, &vol}) {
+                host::rois.assign(2000, host::box(1250u, 40u, 40u));
+                host::occupancy.clear();
+                host::launches.clear();
+                nyx_extract_opts o = options(bins);
+                o.symmetric = sym;
+                nyx_plan *p = nullptr;
+                EXPECT(nyx_plan_create(c, m, 1, &o, &p, &n) == NYX_OK);
+                EXPECT(nyx_plan_execute(p, nullptr, kI, kStream) == NYX_OK);
+                for (const Launch &l : host::launches) {
+                    if (l.name.find("k_batch") == std::string::npos) continue;
+                    paired += l.a.lds.marg_pair != 0u;
+                    EXPECT(std::count(host::occupancy.begin(), host::occupancy.end(), l.fn) > 0);
+                }
+                nyx_plan_destroy(p);
+            }
+        }
+    }
+    EXPECT(paired > 0);
+    nyx_destroy(c);
+}
+
 struct Check { const char *name; void (*run)(); };
 const Check kChecks[] = {
     {"extract_device", extract_device},
@@ -454,6 +484,7 @@ const Check kChecks[] = {
     {"forks_when_repeated", forks_when_repeated},
     {"plan_counts", plan_counts},
     {"label_maximum_of_mixed_sizes", label_maximum_of_mixed_sizes},
+    {"occupancy_of_the_kernel_launched", occupancy_of_the_kernel_launched},
 };
 
 }  // namespace

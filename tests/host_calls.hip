@@ -474,6 +474,35 @@ void occupancy_of_the_kernel_launched() {
     nyx_destroy(c);
 }
 
+// The tiles of a region: a partition of its box, none with more voxels than the
+// bound that its size class and its table are taken from.
+void tiles_of_a_box() {
+    uint32_t x = 7u;
+    const auto next = [&](uint32_t below) {
+        x = x * 1664525u + 1013904223u;
+        return (x >> 8) % below;
+    };
+    std::vector<uint8_t> hit;
+    for (int k = 0; k < 4000; ++k) {
+        const uint32_t rows = 1u + next(k % 5 ? 120u : 3000u), width = 1u + next(k % 3 ? 90u : 700u);
+        const uint32_t area = rows * width, n = k % 4 ? 1u + next(area) : area, split = 1u + next(k % 2 ? 64u : 4096u);
+        const nyx::Tiling t = nyx::tiles_for(n, rows, width, split, split);
+        const uint32_t tiles = t.row_blocks * t.col_blocks, bound = nyx::item_bound(n, rows, width, t);
+        hit.assign(area, 0);
+        for (uint32_t i = 0; i < tiles; ++i) {
+            uint32_t ra, rb, ca, cb;
+            nyx::tile_bounds(rows, width, tiles, t.col_blocks, i, &ra, &rb, &ca, &cb);
+            if (ra >= rb || ca >= cb) continue;
+            EXPECT(rb <= rows && cb <= width);
+            EXPECT(std::min(n, (rb - ra) * (cb - ca)) <= bound);
+            for (uint32_t r = ra; r < std::min(rb, rows); ++r)
+                for (uint32_t c = ca; c < std::min(cb, width); ++c) ++hit[r * width + c];
+        }
+        EXPECT((size_t)std::count(hit.begin(), hit.end(), 1) == hit.size());
+        if (failures) return;
+    }
+}
+
 struct Check { const char *name; void (*run)(); };
 const Check kChecks[] = {
     {"extract_device", extract_device},
@@ -485,6 +514,7 @@ const Check kChecks[] = {
     {"plan_counts", plan_counts},
     {"label_maximum_of_mixed_sizes", label_maximum_of_mixed_sizes},
     {"occupancy_of_the_kernel_launched", occupancy_of_the_kernel_launched},
+    {"tiles_of_a_box", tiles_of_a_box},
 };
 
 }  // namespace

@@ -135,7 +135,7 @@ typedef struct nyx_extract_opts {
     const nyx_offset *offsets_host;
     int32_t n_offsets;
     int32_t symmetric;           /* 1: P = C + C^T; 0: ordered counts P = C (dense square per
-                                    direction in LDS, or the hash table; gather accumulation) */
+                                    direction in LDS, or the hash table) */
     nyx_precision precision;     /* feature output type */
     int32_t autotune;            /* 1: time candidate kernel configurations at plan time */
     int32_t accum_mode;          /* -1 = automatic; else force one accumulation mode:
@@ -281,8 +281,10 @@ nyx_status nyx_neighbourhood_features(nyx_ctx *ctx, const nyx_image *imgs_host, 
 
 /* Whole path in one call (regional GLCM texture of every ROI, Supplementary
  * Tables S3 and S7, with the hyper-parameters n_bins and offsets of Methods,
- * "Feature Control and Tunability"): plan, execute once, destroy the plan.
- * rois (nullable) and table are caller-owned device buffers; a table or ROI
+ * "Feature Control and Tunability"): one discovery, configuration and step on
+ * `stream`, which reads the images behind the work already enqueued there and
+ * is waited for before the call returns (with opts->autotune a plan is made,
+ * executed once and destroyed).  rois (nullable) and table are caller-owned device buffers; a table or ROI
  * capacity below the ROI count gives NYX_ERR_CAPACITY with the count in
  * *rois->n_rois_host. */
 nyx_status nyx_extract_batch(nyx_ctx *ctx, const nyx_image *imgs_host, int32_t n_images,

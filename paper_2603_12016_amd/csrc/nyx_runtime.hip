@@ -822,12 +822,13 @@ uint32_t groups_per_cu(uint64_t lds_bytes) {
 }
 
 // The row and difference marginals of a symmetric matrix share words where
-// that lets a layout fit, or a second work-group onto a CU, and an unsplit
-// item's marginals (at most twice its voxels) stay below 2^16.  At 128 levels:
-// 4 directions two groups instead of one (2000 cells, batch kernel 104 us with
-// the best other split, 88 so), 8 directions 512 threads instead of 256 (4400
-// cells, distances 1 and 2: 696, 454).  From two groups to three it lost at
-// 100 levels (320, 363).
+// that lets a second work-group onto a CU (or one of 512 threads in the place
+// of 256: widen_block) and an unsplit item's marginals (at most twice its
+// voxels) stay below 2^16; what fits at all is found without it.  At 128
+// levels: 4 directions two groups instead of one (2000 cells, batch kernel 104
+// us with the best other split, 88 so), 8 directions 512 threads instead of
+// 256 (4400 cells, distances 1 and 2: 696, 454).  From two groups to three it
+// lost at 100 levels (320, 363).
 LdsLayout make_layout(const Config &c, uint32_t ng, int K, bool ring) {
     const LdsLayout L = lay_out(c, ng, K, ring, false);
     if (c.mode != 3 || c.nonsym || c.merged || c.split_vox > 32767u || groups_per_cu(L.bytes) > 1u)
@@ -980,7 +981,8 @@ Config default_config(const std::vector<Config> &cands, const Work &w, uint32_t 
 
 // Feasible LDS configurations for this workload, one per accumulation mode,
 // each with as many directions per pass as fit.  Dense triangles first, then
-// the packed hash; the hash of 64-bit slots only when none of them fits.
+// the packed hash where it is worth its splits (packed_worth); where no
+// triangle fits, the hash of 64-bit slots in its place.
 // merged: every offset counts into one LDS triangle in one pass, so only the
 // dense scan modes qualify, and packed 16-bit counters need K x (voxels of an
 // item) < 65536 (offered only when that bound leaves the load-balance tile
@@ -1310,8 +1312,6 @@ nyx_status set_outputs(nyx_ctx *ctx, StepArgs &a, nyx_roi_table *rois, void *tab
     return NYX_OK;
 }
 
-// The batch kernel over the queue: one launch, or one for the larger size
-// classes and one, with a layout of its own, for the smaller.
 void release_streams(nyx_ctx *c) {
     if (c->join_event) (void)hipEventDestroy(c->join_event);
     if (c->fork_event) (void)hipEventDestroy(c->fork_event);
@@ -1319,6 +1319,8 @@ void release_streams(nyx_ctx *c) {
     if (c->capture_stream) (void)hipStreamDestroy(c->capture_stream);
 }
 
+// The batch kernel over the queue: one launch, or one for the larger size
+// classes and one, with a layout of its own, for the smaller.
 hipError_t launch_batch_main(const nyx_plan *p, hipStream_t st) {
     StepArgs a = p->w.args;
     if (p->small_cls) a.cls_lo = p->small_cls;

@@ -203,10 +203,10 @@ struct StepArgs {
     uint16_t *o_min, *o_max;
     int32_t *o_bbox;
     LdsLayout lds;
-    // 2D distance-1 row-sweep accumulation: per pass, the local direction slot
-    // of the H, V, D45, D135 neighbour classes (-1 = absent)
     uint32_t cls_lo, cls_hi;    // size classes [cls_lo, cls_hi) of this launch of the batch kernel
     uint32_t tickets;           // its ticket counters (C_TICKETS or C_TICKETS2)
+    // 2D distance-1 row-sweep accumulation: per pass, the local direction slot
+    // of the H, V, D45, D135 neighbour classes (-1 = absent)
     int32_t sweep_ok;
     int8_t sweep[kMaxSweepPasses][4];
     uint32_t sweep_flip[kMaxSweepPasses];   // ordered counts: bit dl where direction dl runs against its class

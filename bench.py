@@ -69,6 +69,12 @@ def stored_traffic(kernel: str, workload: str):
     return t["fetch_kib"] * 1024.0 * t["fetch_scale"] + t["write_kib"] * 1024.0 * t["write_scale"]
 
 
+def launch_key(r) -> tuple:
+    """What tells a step's launches of one kernel apart in a counter CSV (the
+    batch kernel runs twice where small size classes have a launch of their own)."""
+    return r["Kernel_Name"], r.get("Workgroup_Size"), r.get("LDS_Block_Size")
+
+
 def summarize_pmc(fetch_csv: str, write_csv: str, workload: str, copy_bytes: int, command: str) -> None:
     """Writes profiles/<kernel>_<workload>_traffic.txt (JSON) for every kernel in
     KERNEL_SYMBOLS from the counter CSVs of a FETCH_SIZE and a WRITE_SIZE run
@@ -84,8 +90,8 @@ def summarize_pmc(fetch_csv: str, write_csv: str, workload: str, copy_bytes: int
                     continue
                 for k, sym in list(KERNEL_SYMBOLS.items()) + [("copy", COPY_SYMBOL)]:
                     if sym in r["Kernel_Name"]:
-                        vals.setdefault(k, []).append(float(r["Counter_Value"]))
-        return {k: statistics.median(v) for k, v in vals.items()}
+                        vals.setdefault(k, {}).setdefault(launch_key(r), []).append(float(r["Counter_Value"]))
+        return {k: sum(statistics.median(v) for v in by.values()) for k, by in vals.items()}
     fetch, write = per_kernel(fetch_csv, "FETCH_SIZE"), per_kernel(write_csv, "WRITE_SIZE")
     fs = copy_bytes / (fetch["copy"] * 1024.0)
     ws = copy_bytes / (write["copy"] * 1024.0)
@@ -133,8 +139,8 @@ def summarize_trace(stats_csv: str, workload: str, command: str, top: int = 14) 
 def summarize_sq(sq_csv: str, workload: str, command: str, roi_vox: int) -> None:
     """Writes profiles/<kernel>_<workload>_counters.md from a rocprofv3 --pmc
     run of this script with the SQ counters below: the median per dispatch of
-    every counter for each kernel in KERNEL_SYMBOLS, and what follows from
-    them (SQ_BUSY_CYCLES is summed over the 32 shader engines, the LDS
+    every counter for each kernel in KERNEL_SYMBOLS, added over its launches in
+    a step, and what follows from them (SQ_BUSY_CYCLES is summed over the 32 shader engines, the LDS
     conflict counters over the 256 CUs; a wave64 VALU instruction occupies its
     SIMD for 4 cycles)."""
     import csv
@@ -144,13 +150,14 @@ def summarize_sq(sq_csv: str, workload: str, command: str, roi_vox: int) -> None
         for r in csv.DictReader(f):
             for k, sym in KERNEL_SYMBOLS.items():
                 if sym in r["Kernel_Name"]:
-                    vals.setdefault(k, {}).setdefault(r["Counter_Name"], []).append(float(r["Counter_Value"]))
-    med = {k: {c: statistics.median(v) for c, v in cs.items()} for k, cs in vals.items()}
+                    vals.setdefault(k, {}).setdefault(r["Counter_Name"], {}).setdefault(launch_key(r), []).append(
+                        float(r["Counter_Value"]))
+    med = {k: {c: sum(statistics.median(v) for v in by.values()) for c, by in cs.items()} for k, cs in vals.items()}
     names = sorted({c for cs in med.values() for c in cs})
     ks = [k for k in KERNEL_SYMBOLS if k in med]
     lines = [f"# rocprofv3 SQ counters: {workload}", "", "Command (from the repository root on the GPU host):", "",
              f"    {command}", "", f"Sources: `paper_2603_12016_amd/csrc` digest {source_digest()}.", "",
-             "Median per dispatch.", "", "| counter | " + " | ".join(ks) + " |", "|---" * (len(ks) + 1) + "|"]
+             "Medians per dispatch, added over a kernel's launches in a step.", "", "| counter | " + " | ".join(ks) + " |", "|---" * (len(ks) + 1) + "|"]
     for c in names:
         lines.append(f"| {c} | " + " | ".join(f"{med[k].get(c, float('nan')):.4g}" for k in ks) + " |")
     lines += ["", "| derived | " + " | ".join(ks) + " |", "|---" * (len(ks) + 1) + "|"]

@@ -284,9 +284,9 @@ nyx_status nyx_neighbourhood_features(nyx_ctx *ctx, const nyx_image *imgs_host, 
  * "Feature Control and Tunability"): one discovery, configuration and step on
  * `stream`, which reads the images behind the work already enqueued there and
  * is waited for before the call returns (with opts->autotune a plan is made,
- * executed once and destroyed).  rois (nullable) and table are caller-owned device buffers; a table or ROI
- * capacity below the ROI count gives NYX_ERR_CAPACITY with the count in
- * *rois->n_rois_host. */
+ * executed once and destroyed).  rois (nullable) and table are caller-owned
+ * device buffers; a table or ROI capacity below the ROI count gives
+ * NYX_ERR_CAPACITY with the count in *rois->n_rois_host. */
 nyx_status nyx_extract_batch(nyx_ctx *ctx, const nyx_image *imgs_host, int32_t n_images,
                              const nyx_extract_opts *opts, nyx_roi_table *rois, void *table,
                              int64_t table_capacity_rows, nyx_stream stream);

@@ -1082,11 +1082,13 @@ __device__ __forceinline__ void accumulate_sweep2d(const RoiDesc &rd, const Item
 // of its plane and of the next one are loaded in one batch, levels formed
 // once per row, left and right neighbours come by DPP wave shifts and the
 // rows above and below from the lane's own window, so a voxel's 13 pairs
-// cost 2.4 loads, no LDS reads and no barrier.  Bound by VALU issue (some
-// 140 operations a voxel, most of them the 13 cell indices) and the LDS
-// atomics' conflicts; 500 ellipsoids of a 512 x 512 x 256 volume at 64 levels:
-// 1094 us through the staged ring (two LDS reads' latency a pair at eight
-// wavefronts on a CU, two barriers a chunk), 413 us so.
+// cost 2.4 loads, no LDS reads and no barrier.  Bound by VALU issue (most of
+// it the 13 cell indices; the vector units are busy 79 % of the whole kernel,
+// 7.6 wave instructions a ROI voxel with the scans of the triangles) and the
+// LDS atomics' conflicts (29 % of its cycles, bank and address); 500 ellipsoids
+// of a 512 x 512 x 256 volume at 64 levels: 1094 us through the staged ring
+// (two LDS reads' latency a pair at eight wavefronts on a CU, two barriers a
+// chunk), 353 us so.
 // slots: 1 + the local direction slot of forward neighbour class c (class3d)
 // in bits 4 c .. 4 c + 3, 0 where it is not in this pass.
 constexpr int kSweep3Rows = 8;

@@ -34,10 +34,12 @@
 // added to its table in global memory, and k_nb_split finishes them.  The
 // features come from exact integer moments of S (GLM, GLV, DCM, DCV, the
 // non-uniformities, energy) and double sums (the weighted emphases, entropy,
-// and the NGTDM pair sums over the levels present).  Bound by instructions
-// (26 compares a voxel) and LDS atomics; 60 regions of 10^3-60^3 voxels in a
-// 128 x 256 x 256 volume at 32 levels took 8.85 ms a call with one work-group
-// per region and gathered neighbours (60 work-groups on 256 CUs), 0.94 ms so.
+// and the NGTDM pair sums over the levels present).  Bound by latency and by
+// instructions (26 compares a voxel): the vector units are busy 46 % of the
+// time with two wavefronts per SIMD, LDS conflicts take 1 %.  60 regions of
+// 10^3-60^3 voxels in a 128 x 256 x 256 volume at 32 levels took 7.4 ms a call
+// with one work-group per region and gathered neighbours (60 work-groups on
+// 256 CUs), 0.34 ms so, 0.11 of them in this kernel.
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -295,21 +297,22 @@ __device__ void nb_features(const NbTab &t, NbShared &S, uint32_t ng, uint32_t n
     }
     // pair sums: every term is symmetric and vanishes for i = j, so each
     // unordered pair is visited once (a wavefront per first level) and
-    // counted twice
+    // counted twice; the busyness denominator is summed in voxels, exactly, as
+    // it can vanish with several levels present
     for (uint32_t a = threadIdx.x / kWave; a < ngp; a += (uint32_t)kNbWaves) {
         const uint32_t i = t.occ[a];
-        const double pi = (double)t.iso[i] * inv_nvp, li = (double)(i + 1u), si_ = t.sl[i];
+        const double ni = (double)t.iso[i], pi = ni * inv_nvp, li = (double)(i + 1u), si_ = t.sl[i];
         for (uint32_t c = a + 1u + (uint32_t)lane(); c < ngp; c += (uint32_t)kWave) {
             const uint32_t j = t.occ[c];
-            const double pj = (double)t.iso[j] * inv_nvp, lj = (double)(j + 1u), d = li - lj;
+            const double nj = (double)t.iso[j], pj = nj * inv_nvp, lj = (double)(j + 1u), d = li - lj;
             g[2] += pi * pj * d * d;
-            g[3] += fabs(li * pi - lj * pj);
+            g[3] += fabs(li * ni - lj * nj);   // whole numbers, below 2^53 in all
             g[4] += fabs(d) * (pi * si_ + pj * t.sl[j]) / (pi + pj);
             g[5] += (pi + pj) * d * d;
         }
     }
     block_sums<kNbWaves>(g, S.red);
-    const double ps = g[0], ssum = g[1], con = 2.0 * g[2], bden = 2.0 * g[3], cpx = 2.0 * g[4], str = 2.0 * g[5];
+    const double ps = g[0], ssum = g[1], con = 2.0 * g[2], bden = nvp ? 2.0 * g[3] / (double)nvp : 0.0, cpx = 2.0 * g[4], str = 2.0 * g[5];
     __syncthreads();   // every thread is done with the tables
     if (threadIdx.x != 0) return;
     double f[NB_COUNT];

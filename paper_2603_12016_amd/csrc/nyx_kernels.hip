@@ -662,7 +662,9 @@ __device__ __forceinline__ void add_pair(const StepArgs &a, uint8_t *smem, uint3
         // holds the key takes a plain add, else the first free one is claimed
         // by compare-and-swap, else the next bucket is probed.  (Slot by slot,
         // a wavefront waited for its longest of 64 probe chains.)  Bound by
-        // the two LDS round trips a pair and the 16 waves a CU's tables leave:
+        // the two LDS round trips a pair at the 16 waves a CU's tables leave,
+        // and by issue (vector units 63 % busy over the kernel, LDS conflicts
+        // 2 %, on 10000 regions of 30-300 voxels at 1024 levels):
         // 2000 cells at 256 levels 470 us as a list of first touches in dense
         // triangles, 212 here; a 1024-level image (67 M voxels in 10000 small
         // regions and one band) 600 in 64-bit slots, 330 here.

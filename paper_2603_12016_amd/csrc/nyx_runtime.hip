@@ -1994,7 +1994,7 @@ nyx_status nyx_plan_create(nyx_ctx *ctx, const nyx_image *imgs, int32_t n_images
         float best = 1e30f;
         for (const Config &c : cands) {
             if (opts->accum_mode >= 0 && !is_mode(c, opts->accum_mode, cands)) continue;
-            if ((s = configure(p.get(), c, opts)) != NYX_OK) continue;
+            if (configure(p.get(), c, opts) != NYX_OK) continue;   // (too large for the cap, or for the device)
             set_outputs(ctx, p->w.args, nullptr, tmp.p, p->w.n_rois);
             if ((s = enqueue_step(p.get(), st, false)) != NYX_OK) break;
             hipError_t he = hipEventRecord(ev[0], st);

@@ -503,6 +503,28 @@ void tiles_of_a_box() {
     }
 }
 
+// A candidate that outgrows the caller's cap is passed over, also where it is
+// the last one that the tuning looks at.
+void tuning_under_a_cap() {
+    nyx_ctx *c = context();
+    nyx_image im = image(6000, 6000);
+    int64_t n = 0;
+    host::rois.assign(1500, host::box(12000u, 120u, 110u));
+    for (int k = 0; k < 100; ++k) host::rois.push_back(host::box(30000u, 180u, 170u));
+    nyx_extract_opts o = options(200);
+    o.accum_mode = 0;
+    o.workspace_cap_bytes = 400 << 20;
+    nyx_plan *p = nullptr;
+    EXPECT(nyx_plan_create(c, &im, 1, &o, &p, &n) == NYX_OK);
+    nyx_plan_destroy(p);
+    o.autotune = 1;
+    p = nullptr;
+    EXPECT(nyx_plan_create(c, &im, 1, &o, &p, &n) == NYX_OK);
+    if (p) EXPECT(described_number(p, "split_rois=") == 100u);
+    nyx_plan_destroy(p);
+    nyx_destroy(c);
+}
+
 struct Check { const char *name; void (*run)(); };
 const Check kChecks[] = {
     {"extract_device", extract_device},
@@ -515,6 +537,7 @@ const Check kChecks[] = {
     {"label_maximum_of_mixed_sizes", label_maximum_of_mixed_sizes},
     {"occupancy_of_the_kernel_launched", occupancy_of_the_kernel_launched},
     {"tiles_of_a_box", tiles_of_a_box},
+    {"tuning_under_a_cap", tuning_under_a_cap},
 };
 
 }  // namespace

@@ -148,6 +148,7 @@ struct DevBuf {
             owned = true;
         } else {
             p = nullptr;
+            (void)hipGetLastError();   // reported here: not to be found by the check of a later launch
         }
         return e;
     }

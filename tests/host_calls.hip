@@ -36,6 +36,8 @@ struct Launch {
 namespace host {
 
 int device = 0;
+size_t memory_limit = ~(size_t)0;        // of one allocation
+hipError_t last_error = hipSuccess;
 std::map<void *, size_t> memory;         // device allocations
 std::vector<int> alloc_device;           // current device of each
 uint8_t *pin = nullptr;
@@ -104,14 +106,18 @@ hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int) {
     return hipSuccess;
 }
 const char *hipGetErrorString(hipError_t) { return "error"; }
-hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipGetLastError(void) {
+    const hipError_t e = host::last_error;
+    host::last_error = hipSuccess;
+    return e;
+}
 hipError_t hipGetSymbolAddress(void **p, const void *) {
     static void *s = host::map_memory(NYX_NOALLOC_SCRATCH_BYTES);
     *p = s;
     return hipSuccess;
 }
 hipError_t hipMalloc(void **p, size_t n) {
-    if (!(*p = host::map_memory(n))) return hipErrorOutOfMemory;
+    if (n > host::memory_limit || !(*p = host::map_memory(n))) return host::last_error = hipErrorOutOfMemory;
     host::memory[*p] = n;
     host::alloc_device.push_back(host::device);
     return hipSuccess;
@@ -525,6 +531,29 @@ void tuning_under_a_cap() {
     nyx_destroy(c);
 }
 
+// A call that runs out of device memory says so, and the next one is none the
+// worse: the runtime's last error, which every launch is checked by, is clear.
+void out_of_memory_is_over() {
+    nyx_ctx *c = context();
+    nyx_image im = image(4000, 4000);
+    int64_t n = 0;
+    host::rois.assign(500, host::box(6000u, 80u, 90u));
+    nyx_extract_opts o = options(256);
+    nyx_roi_table t{};
+    t.capacity = 500;
+    host::memory_limit = 100 << 20;
+    EXPECT(nyx_extract_batch(c, &im, 1, &o, &t, kI, 500, kStream) == NYX_ERR_OOM);
+    EXPECT(hipGetLastError() == hipSuccess);
+    nyx_plan *p = nullptr;
+    EXPECT(nyx_plan_create(c, &im, 1, &o, &p, &n) == NYX_ERR_OOM);
+    EXPECT(hipGetLastError() == hipSuccess);
+    host::rois.resize(10);
+    EXPECT(nyx_extract_batch(c, &im, 1, &o, &t, kI, 500, kStream) == NYX_OK);
+    EXPECT(nyx_plan_create(c, &im, 1, &o, &p, &n) == NYX_OK);
+    nyx_plan_destroy(p);
+    nyx_destroy(c);
+}
+
 struct Check { const char *name; void (*run)(); };
 const Check kChecks[] = {
     {"extract_device", extract_device},
@@ -538,6 +567,7 @@ const Check kChecks[] = {
     {"occupancy_of_the_kernel_launched", occupancy_of_the_kernel_launched},
     {"tiles_of_a_box", tiles_of_a_box},
     {"tuning_under_a_cap", tuning_under_a_cap},
+    {"out_of_memory_is_over", out_of_memory_is_over},
 };
 
 }  // namespace

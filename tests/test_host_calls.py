@@ -30,7 +30,8 @@ def host_calls():
 @pytest.mark.parametrize("check", ["extract_device", "noalloc_wait", "accumulate_wait", "packed_memory",
                                    "band_blocks_of_many", "forks_when_repeated", "plan_counts",
                                    "label_maximum_of_mixed_sizes", "occupancy_of_the_kernel_launched",
-                                   "tiles_of_a_box", "tuning_under_a_cap"])
+                                   "tiles_of_a_box", "tuning_under_a_cap",
+                                   "out_of_memory_is_over"])
 def test_host_calls(host_calls, check):
     r = subprocess.run([host_calls, check], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr
